@@ -13,7 +13,12 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libvegas_gfx950.so")
-SOURCES = ["k_sample.hip", "k_merge.hip", "k_batch.hip", "capi.cpp", "batch.cpp", "rtc.cpp", "noalloc.cpp", "probe.hip"]
+# the event kernels of one precision and integrand kind are a compilation each
+# of the same file (source, defines); the longest compilations come first
+PARTS = [(f"k_{w}.hip", [f"-DVEGAS_{w.upper()}_PREC={p}", f"-DVEGAS_{w.upper()}_KIND={k}"])
+         for w in ("batch", "sample") for p in (64, 32) for k in range(4)]
+SOURCES = PARTS + [(f, []) for f in ("k_sample.hip", "k_merge.hip", "k_batch.hip", "capi.cpp", "batch.cpp", "rtc.cpp",
+                                     "noalloc.cpp", "probe.hip")]
 # device sources the library hands to the runtime compiler for user integrands
 RTC_HEADERS = [("kRtcInternal", "vegas_internal.hpp"), ("kRtcCommon", "device_common.hpp"),
                ("kRtcUser", "k_user_rtc.hpp")]
@@ -57,9 +62,10 @@ def build(verbose: bool = False, jobs: int = 8, out: str = LIB, objdir: str | No
     os.makedirs(objdir, exist_ok=True)
     write_rtc_sources(objdir)
 
-    def compile_one(src: str) -> str:
-        obj = os.path.join(objdir, os.path.splitext(src)[0] + ".o")
-        cmd = [hipcc(), *flags(objdir), *(extra or []), "-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj]
+    def compile_one(unit) -> str:
+        src, defines = unit
+        obj = os.path.join(objdir, os.path.splitext(src)[0] + "".join(d.split("=")[1].rjust(3, "_") for d in defines) + ".o")
+        cmd = [hipcc(), *flags(objdir), *defines, *(extra or []), "-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj]
         r = subprocess.run(cmd, capture_output=True, text=True)
         if r.returncode != 0:
             raise RuntimeError(f"hipcc failed for {src}:\n{r.stdout}\n{r.stderr}")

@@ -59,12 +59,18 @@ vegas_status check_params(int kind, int d, const double* q)
     return VEGAS_OK;
 }
 
+// LDS of the runtime-compiled event kernel: table, histogram replicas, wave partials.
+size_t user_lds(int prec, int d, int N, int rep, bool hist)
+{
+    return lds_bytes(prec, USER, d, N, hist ? rep : 0) + red_bytes(2);
+}
+
 // LDS per block of the event kernel with one histogram copy per bin (the
 // smallest launch it has): the grid table, the histogram and the wave
 // partials of the block reduction.  Exactly what the launch asks for.
 size_t event_lds_min(int prec, int kind, int d, int N)
 {
-    if (kind == USER) return lds_bytes(prec, USER, d, N, 1) + sizeof(double) * (kBlock / 64);
+    if (kind == USER) return user_lds(prec, d, N, 1, true);
     return sample_lds(prec, kind, d, N, 1, true);
 }
 
@@ -175,12 +181,6 @@ int sample_blocks(const vegas_ctx* c, int64_t n)
     if (nb < 1) nb = 1;
     if (nb > kMaxBlocks) nb = kMaxBlocks;
     return nb;
-}
-
-// LDS of the runtime-compiled event kernel: table, histogram replicas, wave partials.
-size_t user_lds(int prec, int d, int N, int rep, bool hist)
-{
-    return lds_bytes(prec, USER, d, N, hist ? rep : 0) + sizeof(double) * (kBlock / 64);
 }
 
 size_t event_lds(const vegas_ctx* c, int rep, bool hist)
@@ -373,9 +373,12 @@ vegas_status init_ctx(vegas_ctx** out, const vegas_desc* desc, const char* sourc
     // Beyond d = 8 each event makes more histogram atomics per instruction and
     // the replicas weigh more: at d = 16 (Genz, FP32-mixed) one block of 16
     // replicas ran 14 % faster than three blocks of 4 and 3 % faster than two
-    // of 8, so the factors are steeper there.
+    // of 8, so the factors are steeper there: per 1e7 events, the FP32-mixed
+    // Gaussian took 88 us with one block of 16 and 114 us with two of 8
+    // (d = 16, N = 50), 110 us with one block of 8 and 130 us with two of 4
+    // (N = 100).
     static const double kRepFactorLow[5] = {0.5, 0.65, 0.8, 0.93, 1.0};   // 1, 2, 4, 8, 16 replicas
-    static const double kRepFactorHigh[5] = {0.1, 0.2, 0.35, 0.6, 1.0};
+    static const double kRepFactorHigh[5] = {0.05, 0.1, 0.2, 0.45, 1.0};
     const double* kRepFactor = c->d > 8 ? kRepFactorHigh : kRepFactorLow;
     double best = -1.0;
     int per_cu = 1;

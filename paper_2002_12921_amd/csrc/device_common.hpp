@@ -16,6 +16,18 @@ struct pick_type<false, T, F> {
     using type = F;
 };
 
+// The integers 0..N-1 as a type (std::integer_sequence, likewise).
+template <int... I>
+struct IntSeq {};
+template <int N, int... I>
+struct MakeIntSeq {
+    using type = typename MakeIntSeq<N - 1, N - 1, I...>::type;
+};
+template <int... I>
+struct MakeIntSeq<0, I...> {
+    using type = IntSeq<I...>;
+};
+
 // ---------------------------------------------------------------------------
 // Philox4x32-10 (Salmon, Moraes, Dror, Shaw, SC'11, sec. 3.2): ten rounds of
 // two 32x32->64 multiplies whose halves are XOR-mixed with the other words
@@ -59,9 +71,15 @@ __device__ __forceinline__ U4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c
 // ---------------------------------------------------------------------------
 // Precision policies and grid-table entry types.
 //
-// FP64: table entry (E_b - c, E_{b+1} - E_b) for the integrand's centre c, so
-//   u = x - c = fma(delta, width, E_b - c) is one fma (x itself is not formed;
-//   the centre is 0 for user integrands, whose table holds E_b).
+// FP64: delta = (lo + h)/2^32 (see bin_words) is never formed.  With the width
+//   scaled, W = (E_{b+1} - E_b) 2^-32, the table entry is (E_b - c + h W, W) for
+//   the integrand's centre c, so u = x - c = fma(lo, W, first entry) is one
+//   convert and one fma (x itself is not formed; the centre is 0 for user
+//   integrands).  The width product takes the factors 2^-32 back four at a time:
+//   it is multiplied by 2^128 before each group of four dimensions, so it never
+//   falls below the product of the widths, and the constant Cw holds what a
+//   last, partial group took too much.  (Forming delta took an fma per dimension
+//   and, where 2^-32 and h sat in scalar registers, a copy of h.)
 // FP32: the map works on u' = (x - c) S with S = 2^(ws + 32).  With
 //   delta = (lo + h)/2^32 (see bin_words) and W = RN32(width), the table entry is
 //     (RN32((E_b - c + h W / 2^32) S), W 2^ws),
@@ -92,6 +110,11 @@ template <>
 struct TabEntry<P32, BIMODAL> {
     using type = float4;
 };
+// log2 of an entry's bytes
+template <class P, int KIND>
+struct TabLog2 {
+    static constexpr int value = sizeof(typename TabEntry<P, KIND>::type) == 16 ? 4 : 3;
+};
 
 __device__ __forceinline__ double exp_unit(double z) { return exp(z); }  // e^z
 __device__ __forceinline__ float exp2_unit(float z) { return __builtin_amdgcn_exp2f(z); }
@@ -104,10 +127,30 @@ __device__ __forceinline__ float exp2_unit(float z) { return __builtin_amdgcn_ex
 // every precision and FP64 gets delta exactly; the FP32 map carries RN32(lo).
 struct BinConsts {
     uint32_t mul, add;  // N, floor(N/2)
-    double h64;         // h / 2^32
-    double s32;         // 2^-32, read from memory: in a scalar register the FP64
-                        // fma delta = lo 2^-32 + h64 needs no copy of its addend
+    double h64;         // h / 2^32 (per-event records)
 };
+
+// LDS as 32-bit addresses: a pointer formed from the sum of a dynamic LDS
+// array's start and an offset costs an addition of its own per access, because
+// the start is known only after instruction selection; as an integer it is
+// part of the scalar each offset is formed with.
+template <class T>
+using lds_ptr = __attribute__((address_space(3))) T*;
+
+__device__ __forceinline__ uint32_t lds_address(unsigned char* p)
+{
+    return uint32_t(reinterpret_cast<uint64_t>((lds_ptr<unsigned char>)p));
+}
+
+// Entry b of a table of T at LDS address `base`.  Indexed as a pointer: as a
+// shift and a sum, the compiler merges the shift with the extraction of the
+// bin from its 64-bit product into an alignbit, a mask and an addition, where
+// one shift-add does.
+template <class T>
+__device__ __forceinline__ lds_ptr<const T> entry_of(int b, uint32_t base)
+{
+    return (lds_ptr<const T>)(uint64_t(base)) + b;
+}
 
 __device__ __forceinline__ void bin_words(uint32_t k, const BinConsts& bc, int& b, uint32_t& lo)
 {
@@ -121,12 +164,20 @@ __device__ __forceinline__ void bin_words(uint32_t k, const BinConsts& bc, int& 
 template <class P, int KIND, int DMAX>
 struct EvalConsts {
     using real = typename P::real;
+    // the FP64 discontinuous and bimodal integrands' constants per dimension
+    // take two scalar registers each
+    static constexpr bool kFewScalars = P::is64 && (KIND == GENZ_DISC || KIND == BIMODAL) && DMAX > 8 && DMAX <= 20;
     real p1[DMAX], p2[DMAX];
     double c64[DMAX];   // FP32 path, DISC: c_i / S (exponent summed in FP64, d > 8)
     float c32[DMAX];    // FP32 path, DISC: RN32(c_i / S) (exponent summed in FP32, d <= 8)
     real kexp, dscale;  // dscale: FP32 path, 1/S = 2^-(ws + 32)
     double k2;          // FP32 path: log2(e)/(a S)^2 (GAUSS, BIMODAL), log2(e) (DISC)
     BinConsts bc;
+    // LDS address of each dimension's table, as a scalar the compiler cannot
+    // split (it otherwise regroups the sums: one more addition per dimension);
+    // formed one after another with many dimensions and where kFewScalars
+    static constexpr bool kHoldBase = DMAX <= 24 && !kFewScalars;
+    uint32_t base[kHoldBase ? DMAX : 1];
     double C, Cf, Cw;
     // DISC: x_i > a_i exactly when the event's binning word k_i >= K_i; lane
     // l holds K_l (l < d), read with v_readlane (which ignores EXEC, so it is
@@ -137,9 +188,16 @@ struct EvalConsts {
 
     // thr_g: the d thresholds T_i of the discontinuous integrand in
     // P = b 2^32 + lo (disc_threshold; other kinds: unused, may be null).
+    // tab: LDS address of the table [d][n_bins].
     // Called by every thread of the wave (it takes a ballot).
-    __device__ __forceinline__ void load(const DevConst* __restrict__ c, const uint64_t* __restrict__ thr_g, int d)
+    __device__ __forceinline__ void load(const DevConst* __restrict__ c, const uint64_t* __restrict__ thr_g, int d,
+                                         int n_bins, uint32_t tab)
     {
+        if constexpr (kHoldBase) {
+#pragma unroll
+            for (int i = 0; i < DMAX; ++i)
+                base[i] = __builtin_amdgcn_readfirstlane(tab + (uint32_t(i * n_bins) << TabLog2<P, KIND>::value));
+        }
         // only what the kernel's precision and integrand read (scalar registers
         // are scarce); the FP32 path works on u S, S = 2^(ws + 32), so its
         // constants take the matching powers of 1/S (exact)
@@ -170,7 +228,6 @@ struct EvalConsts {
         bc.mul = N;
         bc.add = N >> 1;
         bc.h64 = (N & 1u) ? 0x1p-33 : 0.0;
-        bc.s32 = c->two_m32;
         C = c->C;
         Cf = c->Cf;
         Cw = c->Cw;
@@ -201,17 +258,24 @@ struct EventEval {
     using real = typename P::real;
     using tab_t = typename TabEntry<P, KIND>::type;
 
-    int b[DMAX];      // bin of each dimension
+    uint32_t off[DMAX];  // LDS address of each dimension's table entry: tab + (i N + bin) entries
     real u[DMAX];     // x_i - centre_i (GAUSS, BIMODAL: mu / muA; DISC, PEAK: a_i); FP32: times S
-    real del[DMAX];   // FP64: position inside the bin; FP32: RN32(lo)
-    real wp;          // width product (FP32: scaled, see ew)
+    real del[DMAX];   // lo (FP32: RN32(lo))
+    real wp;          // width product (scaled, see Cw; FP32: and ew)
     real F;           // integrand significand
     real s;           // GAUSS: sum u_i^2
     double s64;       // GAUSS: sum u_i^2 as accumulated (FP64 in both paths; FP32: of u S)
     int ew;           // FP32: binary exponent taken out of the width product
     int fe;           // FP32: binary exponent of the integrand (f ~ 2^fe F)
 
-    __device__ __forceinline__ void run(const EvalConsts<P, KIND, DMAX>& c, const tab_t* __restrict__ tab,
+    // bin of dimension i
+    __device__ __forceinline__ int bin(int i, int N, uint32_t tab) const
+    {
+        return int((off[i] - tab) >> TabLog2<P, KIND>::value) - i * N;
+    }
+
+    // tab: LDS address of the table [d][N]
+    __device__ __forceinline__ void run(const EvalConsts<P, KIND, DMAX>& c, uint32_t tab,
                                         uint64_t e, uint32_t t,
                                         uint32_t ctr3, uint32_t key0, uint32_t key1, int d_rt, int N)
     {
@@ -224,44 +288,57 @@ struct EventEval {
         // method's tolerance
         constexpr bool kQ32 = !P::is64 && DMAX <= 8;
         using q_t = typename pick_type<kQ32, float, double>::type;
-        real w = real(1);
+        real w = P::is64 ? real(0x1p128) : real(1);
         real sa = real(0), sb = real(0);  // FP64 path: GAUSS/BIMODAL sums of squares; DISC: sum c u
         q_t qa = q_t(0), qb = q_t(0);     // FP32 path: the same sums
         real den = real(1);               // PEAK: product of denominators
         bool inside = true;               // DISC: all x_i > a_i
         int ewl = 0;                      // FP32: exponent taken out of w
         const uint32_t elo = uint32_t(e), ehi = uint32_t(e >> 32);
+        uint32_t next = tab;              // table of the next dimension, where EvalConsts does not hold them
         // one Philox call per group of four dimensions (the last group may be
         // partial: DMAX need not be a multiple of 4)
 #pragma unroll
         for (int g = 0; g < (DMAX + 3) / 4; ++g) {
             if (4 * g < d) {
                 const U4 k = philox4x32_10(elo, ehi, t, ctr3 + uint32_t(g), key0, key1);
+                if constexpr (P::is64)
+                    if (g > 0) w *= real(0x1p128);
                 // the group's four bins and table entries first, so that its
                 // LDS reads are in flight together before any is used
-                int bq[4];
-                uint32_t loq[4];
+                uint32_t oq[4], loq[4];
                 tab_t tq[4];
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const int i = 4 * g + q;
                     if (i < d) {
-                        bin_words(k.w[q], c.bc, bq[q], loq[q]);
-                        tq[q] = (tab + i * N)[bq[q]];
+                        int bi;
+                        bin_words(k.w[q], c.bc, bi, loq[q]);
+                        constexpr int L = TabLog2<P, KIND>::value;
+                        lds_ptr<const tab_t> pq;
+                        if constexpr (EvalConsts<P, KIND, DMAX>::kHoldBase)
+                            pq = entry_of<tab_t>(bi, c.base[i]);
+                        else
+                            pq = entry_of<tab_t>(bi, next);
+                        if constexpr (!EvalConsts<P, KIND, DMAX>::kHoldBase) {
+                            next += uint32_t(N) << L;
+                            asm volatile("" : "+s"(next));
+                        }
+                        oq[q] = uint32_t(uint64_t(pq));
+                        tq[q] = *(const tab_t*)pq;
                     }
                 }
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const int i = 4 * g + q;
                     if (i < d) {
-                        const int bi = bq[q];
                         const uint32_t lo = loq[q];
-                        b[i] = bi;
+                        off[i] = oq[q];
                         const tab_t tb = tq[q];
                         real ui, ubi = real(0), width;
                         real dl;
                         if constexpr (P::is64) {
-                            dl = fma(double(lo), c.bc.s32, c.bc.h64);
+                            dl = double(lo);
                             width = tb.y;
                             ui = fma(dl, tb.y, tb.x);
                             if constexpr (KIND == BIMODAL) ubi = ui - c.p2[i];  // p2 = muB - muA
@@ -418,20 +495,48 @@ __device__ __forceinline__ void neumaier_add(double& s, double& c, double v)
     s = t;
 }
 
-// Block sum of one double (blockDim.x a multiple of 64); result valid in
-// thread 0.  red must hold blockDim.x/64 doubles of LDS.
-__device__ __forceinline__ double block_sum(double v, double* red)
+// v plus the value a DPP control takes from another lane (0 where it takes none).
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ double dpp_add(double v)
 {
-    v = wave_sum(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROW_MASK, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROW_MASK, 0xf, true);
+    return v + __hiloint2double(hi, lo);
+}
+
+// Sum over the wave's 64 lanes, valid in lane 63 (all lanes must be active):
+// prefix sums within the rows of 16 lanes, then row totals passed on.  The
+// exchanges stay in the vector unit; through the LDS crossbar each step waits
+// for a round trip.
+__device__ __forceinline__ double wave_sum_last(double v)
+{
+    v = dpp_add<0x111, 0xf>(v);  // row_shr 1, 2, 4, 8
+    v = dpp_add<0x112, 0xf>(v);
+    v = dpp_add<0x114, 0xf>(v);
+    v = dpp_add<0x118, 0xf>(v);
+    v = dpp_add<0x142, 0xa>(v);  // row_bcast 15 into rows 1 and 3
+    v = dpp_add<0x143, 0xc>(v);  // row_bcast 31 into rows 2 and 3
+    return v;
+}
+
+// Block sums of n doubles: every wave leaves its sums of its lanes' v[0..n-1]
+// in red (n x blockDim.x/64 doubles of LDS), and after one barrier thread j
+// adds column j over the waves in order; returned in threads 0..n-1.
+template <int n>
+__device__ __forceinline__ double block_sums(const double (&v)[n], double* red)
+{
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (lane == 0) red[wave] = v;
-    __syncthreads();
-    double t = 0.0;
-    if (threadIdx.x == 0) {
-        const int nw = int(blockDim.x) >> 6;
-        for (int k = 0; k < nw; ++k) t += red[k];
+#pragma unroll
+    for (int j = 0; j < n; ++j) {
+        const double s = wave_sum_last(v[j]);
+        if (lane == 63) red[wave * n + j] = s;
     }
     __syncthreads();
+    double t = 0.0;
+    if (int(threadIdx.x) < n) {
+        const int nw = int(blockDim.x) >> 6;
+        for (int k = 0; k < nw; ++k) t += red[k * n + int(threadIdx.x)];
+    }
     return t;
 }
 
@@ -491,6 +596,74 @@ __device__ __forceinline__ double wave_inclusive_max(double v)
 __device__ __forceinline__ void lds_atomic_add(double* p, double v)
 {
     __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// Adds into the block's histogram [dim][bin][replica] in LDS.  The table
+// [dim][bin] and the histogram share their indexing, so a histogram address is
+// the entry's table address shifted onto the bin's 2^rl2 replicas, plus the
+// lane's own start: one shift-add per dimension with the shift in a scalar
+// register, for every N, d and replica count.  (A layout with a compile-time
+// stride of 64 bins per dimension reached the same count for d in {4, 8, 12,
+// 16} and 16 replicas only, and padded the bins to 64.)
+template <int TL2>  // log2 of a table entry's bytes
+struct HistAdder {
+    int sh;          // a table address to a histogram address
+    uint32_t start;  // histogram's start and the lane's replica, less the shifted table start
+
+    // tab, hist: LDS addresses of the table and the histogram
+    __device__ __forceinline__ HistAdder(uint32_t tab, uint32_t hist, int rl2)
+    {
+        sh = rl2 + 3 - TL2;
+        start = hist + ((threadIdx.x & ((1u << rl2) - 1u)) << 3) - (sh >= 0 ? tab << sh : tab >> 1);
+    }
+
+    template <int D, bool EXACT>
+    __device__ __forceinline__ void add(const uint32_t (&off)[D], int d, double v2) const
+    {
+        if (TL2 == 4 && sh < 0) {  // one replica of 8 bytes beside 16-byte entries: the shift is to the right
+#pragma unroll
+            for (int i = 0; i < D; ++i)
+                if (EXACT || i < d)
+                    lds_atomic_add((double*)(lds_ptr<double>)(uint64_t((off[i] >> 1) + start)), v2);
+            return;
+        }
+#pragma unroll
+        for (int i = 0; i < D; ++i)
+            if (EXACT || i < d)
+                lds_atomic_add((double*)(lds_ptr<double>)(uint64_t((off[i] << sh) + start)), v2);
+    }
+};
+
+// Sum of bin k's replicas (hist in LDS, [bin][replica], 2^rl2 of them).  Lane
+// k starts at replica k: the lanes of a wave then read different banks, where
+// reading replica 0 of every bin first would have all of them on the same one
+// (16 replicas are 128 bytes, half of the 64 banks).
+template <int RL2>
+__device__ __forceinline__ double replica_sum(const double* hist, int k)
+{
+    const double* h = hist + (k << RL2);
+    constexpr int R = 1 << RL2, Q = R < 8 ? R : 8;  // Q reads in flight
+    double s = 0.0;
+#pragma unroll
+    for (int r0 = 0; r0 < R; r0 += Q) {
+        double v[Q];
+#pragma unroll
+        for (int r = 0; r < Q; ++r) v[r] = h[(r0 + r + k) & (R - 1)];
+#pragma unroll
+        for (int r = 0; r < Q; ++r) s += v[r];
+    }
+    return s;
+}
+
+__device__ __forceinline__ double replica_sum(const double* hist, int k, int rl2)
+{
+    switch (rl2) {
+    case 4: return replica_sum<4>(hist, k);
+    case 3: return replica_sum<3>(hist, k);
+    case 2: return replica_sum<2>(hist, k);
+    case 1: return replica_sum<1>(hist, k);
+    default: return hist[k];
+    }
 }
 
 }  // namespace vegas

@@ -38,8 +38,9 @@ __device__ static void finish_iteration(const MergeArgs& a, double S1, double S2
 }
 
 // Grid tables of dimension i from its edges E[0..N] (any address space).
-//   FP64: (E_b - cA, E_{b+1} - E_b), cA the integrand's centre (0 for user
-//         integrands); the event kernel forms x - cA with one fma
+//   FP64: with W = (E_{b+1} - E_b) 2^-32 (exact), (E_b - cA + h W, W), cA the
+//         integrand's centre (0 for user integrands), h = 1/2 for odd N, else 0;
+//         the event kernel forms x - cA = lo W + first entry with one fma
 //   FP32: with W = RN32(E_{b+1} - E_b), S = 2^(ws + 32) and g = E_b + h W / 2^32
 //         (h = 1/2 for odd N, else 0),
 //         (RN32((g - cA) S), [RN32((g - cB) S),] W 2^ws)
@@ -51,7 +52,8 @@ __device__ __forceinline__ void write_table_entry(int i, int b, double lo, doubl
     const double S = sw * 0x1p32;
     const double h = (N & 1) ? 0x1p-33 : 0.0;     // h / 2^32
     const double w = hi - lo;
-    tab64[size_t(i) * N + b] = make_double2(lo - cA, w);
+    const double w32 = w * 0x1p-32;
+    tab64[size_t(i) * N + b] = make_double2((N & 1) ? fma(0.5, w32, lo - cA) : lo - cA, w32);
     const double W = double(float(w));
     const double g = lo + h * W;
     const float Ws = float(W * sw);

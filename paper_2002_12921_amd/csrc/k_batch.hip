@@ -27,24 +27,22 @@ struct BatchMinWaves {
 // (S1, S2) row.  DE > 0: compiled for exactly DE dimensions (the problem's
 // d), with no per-dimension guards, so the whole event runs as one block of
 // straight-line code; DE = 0: each dimension is guarded against d <= DMAX.
-// hist/hlane: the general layout's histogram, or the fixed layout's lane
-// base (FRL2 > 0).
-template <class P, int KIND, int DMAX, int DE, bool HIST, int FRL2>
+// ltab, lhist: LDS addresses of the table and the histogram.
+template <class P, int KIND, int DMAX, int DE, bool HIST>
 __device__ __forceinline__ void batch_item_events(const BatchArgs& a, const BatchItem& it, const BatchProblem& pr,
-                                                  const typename TabEntry<P, KIND>::type* tab, double* hist,
-                                                  unsigned char* hlane, int rl2, int lrep, int d, int N, double* red)
+                                                  uint32_t ltab, uint32_t lhist, int rl2, int d, int N,
+                                                  double* red)
 {
-    constexpr bool FIX = HIST && FRL2 > 0;
-    constexpr int kDimBytes = kBatchFixBins << (FRL2 + 3);
     constexpr int DM = DE > 0 ? DE : DMAX;
     EvalConsts<P, KIND, DM> cst;
-    cst.load(pr.cst, pr.thr, d);
+    cst.load(pr.cst, pr.thr, d, N, ltab);
+    const HistAdder<TabLog2<P, KIND>::value> hadd(ltab, lhist, rl2);
     const uint32_t key0 = pr.key0, key1 = pr.key1, ctr3 = pr.ctr3;
     double s1 = 0.0, c1 = 0.0, s2 = 0.0, c2 = 0.0, g1 = 0.0, g2 = 0.0;
     int ng = 0;
     for (uint64_t k = threadIdx.x; k < it.n; k += blockDim.x) {
         EventEval<P, KIND, DM, (DE > 0)> ev;
-        ev.run(cst, tab, it.e0 + k, a.t, ctr3, key0, key1, d, N);
+        ev.run(cst, ltab, it.e0 + k, a.t, ctr3, key0, key1, d, N);
         double v, v2;
         {
             // rounded as written in every variant (with or without histograms)
@@ -60,81 +58,55 @@ __device__ __forceinline__ void batch_item_events(const BatchArgs& a, const Batc
             g1 = g2 = 0.0;
             ng = 0;
         }
-        if constexpr (FIX) {
-#pragma unroll
-            for (int i = 0; i < DM; ++i)
-                if (DE > 0 || i < d)
-                    lds_atomic_add(reinterpret_cast<double*>(hlane + (i * kDimBytes + (ev.b[i] << (FRL2 + 3)))), v2);
-        } else if constexpr (HIST) {
-#pragma unroll
-            for (int i = 0; i < DM; ++i)
-                if (DE > 0 || i < d) lds_atomic_add(&(hist + (i * N << rl2))[(ev.b[i] << rl2) | lrep], v2);
-        }
+        if constexpr (HIST) hadd.template add<DM, (DE > 0)>(ev.off, d, v2);
     }
-    (void)lrep;
     kahan_add(s1, c1, g1);
     kahan_add(s2, c2, g2);
-    // block_sum synchronises, which also completes every histogram atomic
-    const double S1 = block_sum(s1 - c1, red);
-    const double S2 = block_sum(s2 - c2, red);
-    double* row = a.partials + it.row_off;
-    if (threadIdx.x == 0) {
-        row[0] = S1;
-        row[1] = S2;
-    }
+    // block_sums synchronises, which also completes every histogram atomic
+    const double v12[2] = {s1 - c1, s2 - c2};
+    const double S = block_sums(v12, red);
+    if (threadIdx.x < 2) a.partials[it.row_off + threadIdx.x] = S;
 }
 
 // The exact-d variant for d in [LO, DE] (an if-chain from DE down), the
 // guarded one below LO.
-template <class P, int KIND, int DMAX, int DE, int LO, bool HIST, int FRL2>
+template <class P, int KIND, int DMAX, int DE, int LO, bool HIST>
 __device__ __forceinline__ void batch_item_dispatch(const BatchArgs& a, const BatchItem& it, const BatchProblem& pr,
-                                                    const typename TabEntry<P, KIND>::type* tab, double* hist,
-                                                    unsigned char* hlane, int rl2, int lrep, int d, int N, double* red)
+                                                    uint32_t ltab, uint32_t lhist, int rl2, int d, int N,
+                                                    double* red)
 {
     if constexpr (DE < LO) {
-        batch_item_events<P, KIND, DMAX, 0, HIST, FRL2>(a, it, pr, tab, hist, hlane, rl2, lrep, d, N, red);
+        batch_item_events<P, KIND, DMAX, 0, HIST>(a, it, pr, ltab, lhist, rl2, d, N, red);
     } else {
         if (d == DE)
-            batch_item_events<P, KIND, DMAX, DE, HIST, FRL2>(a, it, pr, tab, hist, hlane, rl2, lrep, d, N, red);
+            batch_item_events<P, KIND, DMAX, DE, HIST>(a, it, pr, ltab, lhist, rl2, d, N, red);
         else
-            batch_item_dispatch<P, KIND, DMAX, DE - 1, LO, HIST, FRL2>(a, it, pr, tab, hist, hlane, rl2, lrep, d, N,
-                                                                       red);
+            batch_item_dispatch<P, KIND, DMAX, DE - 1, LO, HIST>(a, it, pr, ltab, lhist, rl2, d, N, red);
     }
 }
 
-// Fixed histogram layout (FRL2 = log2 of the replicas, 3 or 4; 0: general),
-// for buckets whose problems all have N <= kBatchFixBins: the histogram
-// starts the LDS with a compile-time stride of 64 bins x 2^FRL2 replicas per
-// dimension, so an atomic's address is one shift-add of the bin onto the
-// lane's replica offset, with the dimension's offset in the instruction's
-// immediate field; the problem's grid table follows it.
-// The Gaussian's buckets up to d = 16 run each item with the loop compiled
-// for the problem's exact d (items are sorted by d, so a block seldom
-// changes variant); other integrands and larger buckets guard each dimension.
-template <class P, int KIND, int DMAX, bool HIST, int FRL2>
+// The buckets up to d = 16 run each item with the loop compiled for the
+// problem's exact d (items are sorted by d, so a block seldom changes
+// variant); larger buckets guard each dimension.
+template <class P, int KIND, int DMAX, bool HIST>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(BatchMinWaves<P, DMAX>::value, 8))) void k_batch_sample(
     BatchArgs a)
 {
-    constexpr bool FIX = HIST && FRL2 > 0;
-    static_assert(!FIX || DMAX <= 16, "fixed layout: d <= 16 only");
-    constexpr int kDimBytes = kBatchFixBins << (FRL2 + 3);
-    constexpr size_t kFixBytes = FIX ? size_t(DMAX) * kDimBytes : 0;
     // the bucket's d range: (DMAX/2, DMAX], and 1..4 for the smallest
     constexpr int kLo = DMAX <= 4 ? 1 : DMAX / 2 + 1;
-    constexpr bool kExact = KIND == GAUSS && DMAX <= 16;
+    constexpr bool kExact = DMAX <= 16;
     using tab_t = typename TabEntry<P, KIND>::type;
     extern __shared__ __align__(128) unsigned char smem[];
-    __shared__ int s_item;
-    __shared__ double red[kBlock / 64];
-    // histogram [dim][bin][replica], lane l adding into replica l mod rep
-    const int rl2 = FIX ? FRL2 : a.hrep_log2, rep = 1 << rl2;
-    const int lrep = int(threadIdx.x) & (rep - 1);
+    // the block's wave partials; between items, the item taken (256 bytes in
+    // all: the host leaves that much of the LDS)
+    __shared__ double red[2 * kBlock / 64];
+    int& s_item = *reinterpret_cast<int*>(red);
+    // table, then the histogram [dim][bin][replica], lane l adding into replica l mod rep
+    const int rl2 = a.hrep_log2;
     int cur = -1;
     int d = 0, N = 0, dN = 0;
-    tab_t* tab = reinterpret_cast<tab_t*>(smem + kFixBytes);
-    double* hist = FIX ? reinterpret_cast<double*>(smem) : nullptr;
-    // the lane's replica within the bin: byte offset lrep * 8 (fixed layout)
-    unsigned char* hlane = smem + (lrep << 3);
+    uint32_t hoff = 0;
+    tab_t* tab = reinterpret_cast<tab_t*>(smem);
     for (;;) {
         if (threadIdx.x == 0) s_item = a.item_lo + int(atomicAdd(a.queue, 1u));
         __syncthreads();
@@ -150,33 +122,52 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(BatchMin
             const tab_t* gtab = P::is64 ? reinterpret_cast<const tab_t*>(pr.tab64)
                                         : reinterpret_cast<const tab_t*>(pr.tab32);
             for (int k = threadIdx.x; k < dN; k += blockDim.x) tab[k] = gtab[k];
-            if constexpr (!FIX) hist = reinterpret_cast<double*>(smem + ((size_t(dN) * sizeof(tab_t) + 127) & ~size_t(127)));
+            hoff = (uint32_t(dN) * uint32_t(sizeof(tab_t)) + 127u) & ~127u;
         }
-        if constexpr (HIST) {
-            const int nh = (FIX ? d * kBatchFixBins : dN) << rl2;
-            for (int k = threadIdx.x; k < nh; k += blockDim.x) hist[k] = 0.0;
-        }
+        double* hist = reinterpret_cast<double*>(smem + hoff);
+        const uint32_t ltab = lds_address(smem);
+        if constexpr (HIST)
+            for (int k = threadIdx.x; k < dN << rl2; k += blockDim.x) hist[k] = 0.0;
         __syncthreads();
 
         if constexpr (kExact)
-            batch_item_dispatch<P, KIND, DMAX, DMAX, kLo, HIST, FRL2>(a, it, pr, tab, hist, hlane, rl2, lrep, d, N,
-                                                                     red);
+            batch_item_dispatch<P, KIND, DMAX, DMAX, kLo, HIST>(a, it, pr, ltab, ltab + hoff, rl2, d, N, red);
         else
-            batch_item_events<P, KIND, DMAX, 0, HIST, FRL2>(a, it, pr, tab, hist, hlane, rl2, lrep, d, N, red);
+            batch_item_events<P, KIND, DMAX, 0, HIST>(a, it, pr, ltab, ltab + hoff, rl2, d, N, red);
 
         if constexpr (HIST) {
             double* row = a.partials + it.row_off;
-            for (int k = threadIdx.x; k < dN; k += blockDim.x) {
-                // bin (i, b) of the row at k = i N + b; fixed layout: 64 bins per dimension
-                const int hk = FIX ? k + (k / N) * (kBatchFixBins - N) : k;
-                double h = 0.0;
-                for (int r = 0; r < rep; ++r) h += hist[(hk << rl2) + r];
-                row[2 + k] = h;
-            }
+            for (int k = threadIdx.x; k < dN; k += blockDim.x) row[2 + k] = replica_sum(hist, k, rl2);
         }
         __syncthreads();
     }
 }
+
+#ifdef VEGAS_BATCH_PREC
+
+// The event kernels of one precision and integrand are one compilation of
+// this file each (VEGAS_BATCH_PREC, VEGAS_BATCH_KIND).
+template <class P, int KIND, bool HIST>
+static const void* batch_fn(int dmax)
+{
+    switch (dmax) {
+    case 4: return reinterpret_cast<const void*>(&k_batch_sample<P, KIND, 4, HIST>);
+    case 8: return reinterpret_cast<const void*>(&k_batch_sample<P, KIND, 8, HIST>);
+    case 16: return reinterpret_cast<const void*>(&k_batch_sample<P, KIND, 16, HIST>);
+    case 32: return reinterpret_cast<const void*>(&k_batch_sample<P, KIND, 32, HIST>);
+    default: return reinterpret_cast<const void*>(&k_batch_sample<P, KIND, 64, HIST>);
+    }
+}
+
+#define VEGAS_PART_NAME2(p, k) batch_fn_##p##_##k
+#define VEGAS_PART_NAME(p, k) VEGAS_PART_NAME2(p, k)
+const void* VEGAS_PART_NAME(VEGAS_BATCH_PREC, VEGAS_BATCH_KIND)(int dmax, bool hist)
+{
+    using P = pick_type<VEGAS_BATCH_PREC == 64, P64, P32>::type;
+    return hist ? batch_fn<P, VEGAS_BATCH_KIND, true>(dmax) : batch_fn<P, VEGAS_BATCH_KIND, false>(dmax);
+}
+
+#else
 
 // Per problem and column group: reduce the problem's item rows, record the
 // iteration, refine (adaptation iterations).  Also resets the work queue for
@@ -264,66 +255,42 @@ hipError_t launch_batch_reset(const BatchArgs& a, int dmax, int n_rec, int kind,
 
 // ---------------------------------------------------------------------------
 
-template <class P, int KIND, bool HIST>
-static const void* batch_fn(int dmax, int fix_l2)
-{
-    if constexpr (HIST) {
-        if (fix_l2 == 3 || fix_l2 == 4) {
-            const bool r16 = fix_l2 == 4;
-            switch (dmax) {
-            case 4: return r16 ? reinterpret_cast<const void*>(&k_batch_sample<P, KIND, 4, true, 4>)
-                               : reinterpret_cast<const void*>(&k_batch_sample<P, KIND, 4, true, 3>);
-            case 8: return r16 ? reinterpret_cast<const void*>(&k_batch_sample<P, KIND, 8, true, 4>)
-                               : reinterpret_cast<const void*>(&k_batch_sample<P, KIND, 8, true, 3>);
-            case 16: return r16 ? reinterpret_cast<const void*>(&k_batch_sample<P, KIND, 16, true, 4>)
-                                : reinterpret_cast<const void*>(&k_batch_sample<P, KIND, 16, true, 3>);
-            default: break;
-            }
-        }
-    }
-    switch (dmax) {
-    case 4: return reinterpret_cast<const void*>(&k_batch_sample<P, KIND, 4, HIST, 0>);
-    case 8: return reinterpret_cast<const void*>(&k_batch_sample<P, KIND, 8, HIST, 0>);
-    case 16: return reinterpret_cast<const void*>(&k_batch_sample<P, KIND, 16, HIST, 0>);
-    case 32: return reinterpret_cast<const void*>(&k_batch_sample<P, KIND, 32, HIST, 0>);
-    default: return reinterpret_cast<const void*>(&k_batch_sample<P, KIND, 64, HIST, 0>);
-    }
-}
+// Parts defined by the other compilations.
+const void* batch_fn_64_0(int dmax, bool hist);
+const void* batch_fn_64_1(int dmax, bool hist);
+const void* batch_fn_64_2(int dmax, bool hist);
+const void* batch_fn_64_3(int dmax, bool hist);
+const void* batch_fn_32_0(int dmax, bool hist);
+const void* batch_fn_32_1(int dmax, bool hist);
+const void* batch_fn_32_2(int dmax, bool hist);
+const void* batch_fn_32_3(int dmax, bool hist);
 
-template <class P, bool HIST>
-static const void* batch_fn_kind(int kind, int dmax, int fix_l2)
+static const void* batch_kernel(int prec, int kind, int dmax, bool hist)
 {
-    switch (kind) {
-    case GAUSS: return batch_fn<P, GAUSS, HIST>(dmax, fix_l2);
-    case BIMODAL: return batch_fn<P, BIMODAL, HIST>(dmax, fix_l2);
-    case GENZ_DISC: return batch_fn<P, GENZ_DISC, HIST>(dmax, fix_l2);
-    default: return batch_fn<P, GENZ_PEAK, HIST>(dmax, fix_l2);
-    }
-}
-
-static const void* batch_kernel(int prec, int kind, int dmax, bool hist, int fix_l2)
-{
-    if (hist)
-        return prec == FP64 ? batch_fn_kind<P64, true>(kind, dmax, fix_l2) : batch_fn_kind<P32, true>(kind, dmax, fix_l2);
-    return prec == FP64 ? batch_fn_kind<P64, false>(kind, dmax, 0) : batch_fn_kind<P32, false>(kind, dmax, 0);
+    using Fn = const void* (*)(int, bool);
+    static const Fn f64[] = {batch_fn_64_0, batch_fn_64_1, batch_fn_64_2, batch_fn_64_3};
+    static const Fn f32[] = {batch_fn_32_0, batch_fn_32_1, batch_fn_32_2, batch_fn_32_3};
+    return (prec == FP64 ? f64 : f32)[kind](dmax, hist);
 }
 
 // Without histograms the launch keeps the same grid (and LDS size): it is a
 // work queue, so residency only sets how many blocks share the items.
 hipError_t launch_batch_sample(int prec, int kind, int dmax, size_t lds, const BatchArgs& a, int blocks,
-                               int threads, bool hist, int fix_l2, hipStream_t s)
+                               int threads, bool hist, hipStream_t s)
 {
     void* args[] = {const_cast<BatchArgs*>(&a)};
-    return hipLaunchKernel(batch_kernel(prec, kind, dmax, hist, fix_l2), dim3(blocks), dim3(threads), args, lds, s);
+    return hipLaunchKernel(batch_kernel(prec, kind, dmax, hist), dim3(blocks), dim3(threads), args, lds, s);
 }
 
-int batch_max_blocks_per_cu(int prec, int kind, int dmax, size_t lds, int threads, int fix_l2)
+int batch_max_blocks_per_cu(int prec, int kind, int dmax, size_t lds, int threads)
 {
     int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, batch_kernel(prec, kind, dmax, true, fix_l2), threads, lds) !=
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, batch_kernel(prec, kind, dmax, true), threads, lds) !=
         hipSuccess)
         return 1;
     return n > 0 ? n : 1;
 }
+
+#endif  // VEGAS_BATCH_PREC
 
 }  // namespace vegas

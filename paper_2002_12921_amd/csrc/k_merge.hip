@@ -53,12 +53,11 @@ __device__ static void prepare_consts(int prec, int kind, int d, int N, const do
     const double log2e = 1.4426950408889634074;
     c->n_bins = N;
     c->pad1 = 0;
-    c->two_m32 = 0x1p-32;
     c->dscale32 = width_scale32(N);
     const int ws = int(rint(log2(double(N))));
     double nd = 1.0;
     for (int i = 0; i < d; ++i) nd = nd * double(N);
-    c->Cw = prec == FP64 ? nd : ldexp(nd, -ws * d);
+    c->Cw = ldexp(nd, prec == FP64 ? -32 * ((4 - d % 4) % 4) : -ws * d);
     double Cf = 0.0;
     c->kexp64 = c->kexp2_64 = c->inv_a = 0.0;
     c->kexp32 = c->ka32 = c->pad0 = 0.0f;

@@ -14,101 +14,78 @@
 
 namespace vegas {
 
-// Histogram modes of the event kernel:
-//   kHistNone    no histograms (an iteration whose grid is not refined);
-//   kHistGeneral table first, then the histogram with runtime strides;
-//   kHistFixed   d in {4, 8, 12, 16}, N <= 64, 16 replicas: the histogram
-//                starts the LDS block with a compile-time stride of 64 bins x
-//                16 replicas (8 KiB) per dimension, so an atomic's address is
-//                one shift-add of the bin onto the lane's replica offset and
-//                the dimension's offset rides in the instruction's immediate
-//                field; the grid table follows the histogram (at d = 16:
-//                128 KiB + the table, one 1024-thread block per CU, as the
-//                general layout's 16 replicas need anyway).
-constexpr int kHistNone = 0, kHistGeneral = 1, kHistFixed = 2;
-constexpr int kFixBins = 64;
-constexpr int kFixRepLog2 = 4;
-constexpr int kFixDimBytes = kFixBins << (kFixRepLog2 + 3);
+// Histogram modes of the event kernel: none (an iteration whose grid is not
+// refined), or LDS replicas behind the table.
+constexpr int kHistNone = 0, kHistRows = 1;
 
-// Fewest waves per SIMD the register allocation must allow.  6 (80 VGPRs) for
-// the FP64 Gaussian, bimodal and product-peak kernels up to d = 8: they then
-// fit without spills, and the launch runs two 768-thread blocks per CU (the
-// fixed histogram layout's LDS admits two blocks), 6 waves per SIMD.  At 8
-// waves (64 VGPRs, two 1024-thread blocks) the d = 8 Gaussian spilled 15
-// registers and took 62.2-63.0 us per 1e7 events, at 7 (896-thread blocks)
-// it still spilled 8 and took 70.0-70.8 us, at 6: 57.9-58.5 us.  4 elsewhere:
-// the discontinuous integrand and larger d would spill heavily, and the
-// FP32-mixed kernels reach 8 waves by themselves.
-// The FP64 discontinuous integrand with histograms at d = 16: its 16 FP64
-// c_i and thresholds leave too few scalar registers, and at 128 VGPRs (4
-// waves) it spilled 18 of them (72 bytes per lane, 37.6 MB of scratch traffic
-// per 1e7 events); it runs one 768-thread block per CU, 3 waves per SIMD,
-// without spills: 132.1-132.3 -> 123.4-123.6 us per 1e7 events.  (At d = 13,
-// in the guarded d <= 16 kernel, 3 waves ran slower: 167.0-167.6 -> 178.4-178.6.)
+// Waves per SIMD the register allocation allows, at least and at most.
+//   FP64 up to d = 8, all but the discontinuous integrand: 6 (80 VGPRs).  They
+//     fit without spills, and the launch runs two 768-thread blocks per CU.  At
+//     8 waves (64 VGPRs, two 1024-thread blocks) the d = 8 Gaussian spilled 15
+//     registers and took 62.2-63.0 us per 1e7 events, at 7 (896-thread blocks)
+//     it still spilled 8 and took 70.0-70.8 us, at 6: 57.9-58.5 us.
+//   FP32-mixed up to d = 8: 8, two 1024-thread blocks per CU (without the
+//     bound, the sums at the kernel's end took some past 64 VGPRs).
+//   FP64 discontinuous integrand, d = 14 to 24: 3, one 768-thread block per CU.
+//     Its FP64 c_i and thresholds leave too few scalar registers, and at 128
+//     VGPRs (4 waves) the d = 16 kernel spilled 18 of them: 132.1-132.3 against
+//     123.4-123.6 us per 1e7 events; d = 20 with N = 100: 232 against 172 us.
+//   Beyond d = 8 with histograms: at most 4.  They run one 1024-thread block per
+//     CU (their LDS holds one block's table and replicated histogram), which the
+//     compiler cannot know from the dynamic LDS size: told so, it may use up to
+//     128 registers and keep an event's table reads in flight together instead
+//     of waiting on each (the d = 20 bimodal kernel waited on every one).
+//   4 to 8 elsewhere.
 template <class P, int KIND, int DMAX, bool EXACT, int HM>
-struct ThreeWaves {
-    static constexpr bool value = P::is64 && KIND == GENZ_DISC && DMAX == 16 && EXACT && HM != 0;
-};
-
-template <class P, int KIND, int DMAX, bool EXACT = false, int HM = 0>
-struct MinWaves {
-    static constexpr int value =
-        ThreeWaves<P, KIND, DMAX, EXACT, HM>::value ? 3 : (P::is64 && KIND != GENZ_DISC && DMAX <= 8) ? 6 : 4;
-};
-
-// Most waves per SIMD the kernel is compiled for.  Beyond d = 8 the kernels
-// with histograms run one 1024-thread block per CU (their LDS holds one
-// block's table and replicated histogram), i.e. 4 waves per SIMD, which the
-// compiler cannot know from the dynamic LDS size: told so, it may use up to
-// 128 registers and keep an event's table reads in flight together instead
-// of waiting on each (the d = 20 bimodal kernel waited on every one).
-template <class P, int KIND, int DMAX, bool EXACT, int HM>
-struct MaxWaves {
-    static constexpr int value = ThreeWaves<P, KIND, DMAX, EXACT, HM>::value ? 3 : (DMAX > 8 && HM != 0) ? 4 : 8;
+struct Waves {
+    static constexpr bool three = P::is64 && KIND == GENZ_DISC && DMAX >= 14 && DMAX <= 24 && EXACT;
+    static constexpr bool six = P::is64 && KIND != GENZ_DISC && DMAX <= 8;
+    static constexpr bool eight = !P::is64 && DMAX <= 8;
+    static constexpr int min = three ? 3 : six ? 6 : eight ? 8 : 4;
+    static constexpr int max = three ? 3 : (DMAX > 8 && HM != 0) ? 4 : six ? 6 : 8;
 };
 
 template <class P, int KIND, int DMAX, bool EXACT, int HM>
 struct MaxThreads {
-    static constexpr int value = ThreeWaves<P, KIND, DMAX, EXACT, HM>::value ? 768 : kBlock;
+    static constexpr int value = Waves<P, KIND, DMAX, EXACT, HM>::three ? 768 : kBlock;
 };
 
 template <class P, int KIND, int DMAX, bool EXACT, int HM>
 __global__ __attribute__((amdgpu_flat_work_group_size(1, MaxThreads<P, KIND, DMAX, EXACT, HM>::value),
-                          amdgpu_waves_per_eu(MinWaves<P, KIND, DMAX, EXACT, HM>::value,
-                                              MaxWaves<P, KIND, DMAX, EXACT, HM>::value))) void k_sample(
+                          amdgpu_waves_per_eu(Waves<P, KIND, DMAX, EXACT, HM>::min,
+                                              Waves<P, KIND, DMAX, EXACT, HM>::max))) void k_sample(
     SampleArgs a)
 {
-    constexpr bool FIX = HM == kHistFixed;
-    static_assert(!FIX || (EXACT && DMAX <= 16), "fixed layout: d <= 16 only");
     using tab_t = typename TabEntry<P, KIND>::type;
     extern __shared__ __align__(128) unsigned char smem[];
     const int dN = a.d * a.N;
     const size_t tab_bytes = (size_t(dN) * sizeof(tab_t) + 127) & ~size_t(127);
     // histogram [dim][bin][replica]: with 16 replicas every lane of a wave
     // adds into its own bank pair (lane mod 16), whatever its bin
-    const int rl2 = FIX ? kFixRepLog2 : a.hrep_log2, rep = 1 << rl2;
-    const int lrep = int(threadIdx.x) & (rep - 1);
-    const size_t hist_bytes = HM == kHistNone ? 0
-                              : FIX           ? size_t(DMAX) * kFixDimBytes
-                                              : size_t(dN) * rep * sizeof(double);
-    tab_t* tab = reinterpret_cast<tab_t*>(smem + (FIX ? hist_bytes : 0));
-    double* hist = reinterpret_cast<double*>(smem + (FIX ? 0 : tab_bytes));
+    const int rl2 = a.hrep_log2, rep = 1 << rl2;
+    const size_t hist_bytes = HM == kHistNone ? 0 : size_t(dN) * rep * sizeof(double);
+    tab_t* tab = reinterpret_cast<tab_t*>(smem);
+    double* hist = reinterpret_cast<double*>(smem + tab_bytes);
     double* red = reinterpret_cast<double*>(smem + tab_bytes + hist_bytes);
-    // the lane's replica within the bin: byte offset lrep * 8 (fixed layout)
-    unsigned char* hlane = smem + (lrep << 3);
+    const uint32_t ltab = lds_address(smem);
+    const HistAdder<TabLog2<P, KIND>::value> hadd(ltab, ltab + uint32_t(tab_bytes), rl2);
 
+    // the table's first entries and the constants are on their way while the
+    // histogram is cleared
     const tab_t* gtab = static_cast<const tab_t*>(a.tab);
-    for (int k = threadIdx.x; k < dN; k += blockDim.x) tab[k] = gtab[k];
-    {   // clear the histogram, 16 bytes per store (hist is 128-byte aligned), then an odd last double
+    const tab_t first = gtab[min(int(threadIdx.x), dN - 1)];
+    EvalConsts<P, KIND, DMAX> cst;
+    cst.load(a.cst, a.thr, a.d, a.N, ltab);
+    if constexpr (HM != kHistNone) {   // 16 bytes per store (hist is 128-byte aligned), then an odd last double
         double2* h2 = reinterpret_cast<double2*>(hist);
         for (int k = threadIdx.x; k < int(hist_bytes / sizeof(double2)); k += blockDim.x)
             h2[k] = make_double2(0.0, 0.0);
         if ((hist_bytes & 8) && threadIdx.x == 0) hist[hist_bytes / sizeof(double) - 1] = 0.0;
     }
+    if (int(threadIdx.x) < dN) tab[threadIdx.x] = first;
+    for (int k = threadIdx.x + blockDim.x; k < dN; k += blockDim.x) tab[k] = gtab[k];
     __syncthreads();
 
-    EvalConsts<P, KIND, DMAX> cst;
-    cst.load(a.cst, a.thr, a.d);
     const int d = EXACT ? DMAX : a.d;
     double s1 = 0.0, c1 = 0.0, s2 = 0.0, c2 = 0.0;
     double g1 = 0.0, g2 = 0.0;
@@ -118,7 +95,7 @@ __global__ __attribute__((amdgpu_flat_work_group_size(1, MaxThreads<P, KIND, DMA
     const uint64_t stride = uint64_t(gridDim.x) * blockDim.x;
     for (uint64_t k = uint64_t(threadIdx.x) * gridDim.x + blockIdx.x; k < a.n; k += stride) {
         EventEval<P, KIND, DMAX, EXACT> ev;
-        ev.run(cst, tab, a.e0 + k, a.t, a.ctr3, a.key0, a.key1, d, a.N);
+        ev.run(cst, ltab, a.e0 + k, a.t, a.ctr3, a.key0, a.key1, d, a.N);
         double v, v2;
         {
             // rounded as written in every variant (with or without histograms)
@@ -134,29 +111,15 @@ __global__ __attribute__((amdgpu_flat_work_group_size(1, MaxThreads<P, KIND, DMA
             g1 = g2 = 0.0;
             ng = 0;
         }
-        if constexpr (HM != kHistNone) {
-#pragma unroll
-            for (int i = 0; i < DMAX; ++i) {
-                if (i < d) {
-                    if constexpr (FIX)
-                        lds_atomic_add(reinterpret_cast<double*>(hlane + (i * kFixDimBytes + (ev.b[i] << (kFixRepLog2 + 3)))), v2);
-                    else
-                        lds_atomic_add(&(hist + (i * a.N << rl2))[(ev.b[i] << rl2) | lrep], v2);
-                }
-            }
-        }
+        if constexpr (HM != kHistNone) hadd.template add<DMAX, EXACT>(ev.off, d, v2);
     }
     kahan_add(s1, c1, g1);
     kahan_add(s2, c2, g2);
 
-    // block_sum synchronises, which also completes every histogram atomic
-    const double S1 = block_sum(s1 - c1, red);
-    const double S2 = block_sum(s2 - c2, red);
-    double* row = a.partials + size_t(blockIdx.x) * 2;
-    if (threadIdx.x == 0) {
-        row[0] = S1;
-        row[1] = S2;
-    }
+    // block_sums synchronises, which also completes every histogram atomic
+    const double v12[2] = {s1 - c1, s2 - c2};
+    const double S = block_sums(v12, red);
+    if (threadIdx.x < 2) a.partials[size_t(blockIdx.x) * 2 + threadIdx.x] = S;
     // the block's histogram (replicas summed) goes into slot
     // (blockIdx / 8) mod kHistSlots with device-scope FP64 atomics: no
     // histogram row to write and read back, and 8 slots keep the atomics on
@@ -164,31 +127,15 @@ __global__ __attribute__((amdgpu_flat_work_group_size(1, MaxThreads<P, KIND, DMA
     // blocks spread over all the slots (blockIdx mod 8 gave each XCD one slot
     // and ran about 1 % slower)
     double* slot = a.hslots + size_t((blockIdx.x >> 3) % kHistSlots) * dN;
-    if constexpr (FIX) {
-        // bin (i, b) of the fixed layout, 16 replicas read 2 at a time
-        for (int k = threadIdx.x; k < DMAX * kFixBins; k += blockDim.x) {
-            const int i = k / kFixBins, bb = k % kFixBins;
-            if (bb < a.N) {
-                const double2* h2 = reinterpret_cast<const double2*>(hist + (k << kFixRepLog2));
-                double h = 0.0;
-#pragma unroll
-                for (int r = 0; r < (1 << kFixRepLog2) / 2; ++r) {
-                    const double2 p = h2[r];
-                    h += p.x;
-                    h += p.y;
-                }
-                atomicAdd(&slot[i * a.N + bb], h);
-            }
-        }
-    } else if constexpr (HM != kHistNone) {
+    if constexpr (HM != kHistNone) {
         for (int k = threadIdx.x; k < dN; k += blockDim.x) {
-            const int base = k << rl2;
-            double h = 0.0;
-            for (int r = 0; r < rep; ++r) h += hist[base + r];
+            const double h = replica_sum(hist, k, rl2);
             atomicAdd(&slot[k], h);
         }
     }
 }
+
+#ifndef VEGAS_SAMPLE_PREC
 
 // Per-event records for parity checks: b, delta, x, w, f of each event.
 template <class P, int KIND, int DMAX>
@@ -196,17 +143,18 @@ __global__ __launch_bounds__(kBlock) void k_dump(DumpArgs a)
 {
     using tab_t = typename TabEntry<P, KIND>::type;
     extern __shared__ __align__(16) unsigned char smem[];
+    const uint32_t ltab = lds_address(smem);
     const int dN = a.d * a.N;
     tab_t* tab = reinterpret_cast<tab_t*>(smem);
     const tab_t* gtab = static_cast<const tab_t*>(a.tab);
     for (int k = threadIdx.x; k < dN; k += blockDim.x) tab[k] = gtab[k];
     __syncthreads();
     EvalConsts<P, KIND, DMAX> cst;
-    cst.load(a.cst, a.thr, a.d);
+    cst.load(a.cst, a.thr, a.d, a.N, ltab);
     const uint64_t stride = uint64_t(gridDim.x) * kBlock;
     for (uint64_t k = uint64_t(blockIdx.x) * kBlock + threadIdx.x; k < a.n; k += stride) {
         EventEval<P, KIND, DMAX> ev;
-        ev.run(cst, tab, a.e0 + k, a.t, a.ctr3, a.key0, a.key1, a.d, a.N);
+        ev.run(cst, ltab, a.e0 + k, a.t, a.ctr3, a.key0, a.key1, a.d, a.N);
         double* row = a.out + k * size_t(3 * a.d + 2);
         // x = centre + u; delta as the kernel represents it (FP32: (RN32(lo) +
         // h)/2^32, and u carries the factor S); w and f with their exponents
@@ -214,8 +162,8 @@ __global__ __launch_bounds__(kBlock) void k_dump(DumpArgs a)
 #pragma unroll
         for (int i = 0; i < DMAX; ++i) {
             if (i < a.d) {
-                row[i] = double(ev.b[i]);
-                row[a.d + i] = P::is64 ? double(ev.del[i]) : double(ev.del[i]) * 0x1p-32 + cst.bc.h64;
+                row[i] = double(ev.bin(i, a.N, ltab));
+                row[a.d + i] = double(ev.del[i]) * 0x1p-32 + cst.bc.h64;
                 row[2 * a.d + i] = double(ev.u[i]) * ds + a.cst->cA64[i];
             }
         }
@@ -236,6 +184,7 @@ __global__ __launch_bounds__(kBlock) void k_adjoint(AdjointArgs a)
     using tab_t = typename TabEntry<P, GAUSS>::type;
     using real = typename P::real;
     extern __shared__ __align__(16) unsigned char smem[];
+    const uint32_t ltab = lds_address(smem);
     const int dN = a.d * a.N;
     const size_t tab_bytes = (size_t(dN) * sizeof(tab_t) + 15) & ~size_t(15);
     tab_t* tab = reinterpret_cast<tab_t*>(smem);
@@ -246,7 +195,7 @@ __global__ __launch_bounds__(kBlock) void k_adjoint(AdjointArgs a)
 
     const DevConst* c = a.cst;
     EvalConsts<P, GAUSS, DMAX> cst;
-    cst.load(c, nullptr, a.d);
+    cst.load(c, nullptr, a.d, a.N, ltab);
     // the FP32 path's u carries the factor S = 2^(ws + 32): its constants take S^-1, S^-2 (exact)
     const double ds = P::is64 ? 1.0 : double(c->dscale32) * 0x1p-32;
     const real ka = P::is64 ? real(c->kexp64) : real(double(c->ka32) * ds);
@@ -263,7 +212,7 @@ __global__ __launch_bounds__(kBlock) void k_adjoint(AdjointArgs a)
     const uint64_t stride = uint64_t(gridDim.x) * kBlock;
     for (uint64_t k = uint64_t(blockIdx.x) * kBlock + threadIdx.x; k < a.n; k += stride) {
         EventEval<P, GAUSS, DMAX, EXACT> ev;
-        ev.run(cst, tab, k, a.t, a.ctr3, a.key0, a.key1, d, a.N);
+        ev.run(cst, ltab, k, a.t, a.ctr3, a.key0, a.key1, d, a.N);
         const double v = ev.value(cst);
 #pragma unroll
         for (int j = 0; j < DMAX; ++j)
@@ -272,14 +221,12 @@ __global__ __launch_bounds__(kBlock) void k_adjoint(AdjointArgs a)
         g[DMAX] += v * (da * inv_a);
     }
 
+    // sums over the block, column j in thread j: d components of mu, then a
+    const double t = block_sums(g, red);
     double* row = a.partials + size_t(blockIdx.x) * (d + 1);
-#pragma unroll
-    for (int j = 0; j <= DMAX; ++j) {
-        if (j < d || j == DMAX) {
-            const double t = block_sum(g[j], red);
-            if (threadIdx.x == 0) row[j < d ? j : d] = j < d ? t * double(ka2) : t;
-        }
-    }
+    const int j = int(threadIdx.x);
+    if (j < d) row[j] = t * double(ka2);
+    if (j == DMAX) row[d] = t;
 }
 
 // Final step of the adjoint: the rows' fixed-order sums scaled by gout/M,
@@ -310,6 +257,7 @@ k_sample_grad(SampleArgs a, double* gpart)
     using tab_t = typename TabEntry<P, GAUSS>::type;
     using real = typename P::real;
     extern __shared__ __align__(128) unsigned char smem[];
+    const uint32_t ltab = lds_address(smem);
     const int dN = a.d * a.N;
     const size_t tab_bytes = (size_t(dN) * sizeof(tab_t) + 127) & ~size_t(127);
     tab_t* tab = reinterpret_cast<tab_t*>(smem);
@@ -320,7 +268,7 @@ k_sample_grad(SampleArgs a, double* gpart)
 
     const DevConst* c = a.cst;
     EvalConsts<P, GAUSS, DMAX> cst;
-    cst.load(c, nullptr, a.d);
+    cst.load(c, nullptr, a.d, a.N, ltab);
     const double ds = P::is64 ? 1.0 : double(c->dscale32) * 0x1p-32;
     const real ka = P::is64 ? real(c->kexp64) : real(double(c->ka32) * ds);
     const real ka2 = real(2) * ka;
@@ -336,7 +284,7 @@ k_sample_grad(SampleArgs a, double* gpart)
     const uint64_t stride = uint64_t(gridDim.x) * blockDim.x;
     for (uint64_t k = uint64_t(threadIdx.x) * gridDim.x + blockIdx.x; k < a.n; k += stride) {
         EventEval<P, GAUSS, DMAX, EXACT> ev;
-        ev.run(cst, tab, a.e0 + k, a.t, a.ctr3, a.key0, a.key1, d, a.N);
+        ev.run(cst, ltab, a.e0 + k, a.t, a.ctr3, a.key0, a.key1, d, a.N);
         double v, v2;
         {
 #pragma clang fp contract(off)
@@ -359,103 +307,120 @@ k_sample_grad(SampleArgs a, double* gpart)
     }
     kahan_add(s1, c1, g1);
     kahan_add(s2, c2, g2);
-    const double S1 = block_sum(s1 - c1, red);
-    const double S2 = block_sum(s2 - c2, red);
-    if (threadIdx.x == 0) {
-        double* row = a.partials + size_t(blockIdx.x) * 2;
-        row[0] = S1;
-        row[1] = S2;
-    }
+    // the same sums in the same order as the event kernel's, then the components'
+    const double v12[2] = {s1 - c1, s2 - c2};
+    const double S = block_sums(v12, red);
+    if (threadIdx.x < 2) a.partials[size_t(blockIdx.x) * 2 + threadIdx.x] = S;
+    const double t = block_sums(g, red + 2 * (blockDim.x >> 6));
     double* grow = gpart + size_t(blockIdx.x) * (d + 1);
-#pragma unroll
-    for (int j = 0; j <= DMAX; ++j) {
-        if (j < d || j == DMAX) {
-            const double t = block_sum(g[j], red);
-            if (threadIdx.x == 0) grow[j < d ? j : d] = j < d ? t * double(ka2) : t;
-        }
-    }
+    const int j = int(threadIdx.x);
+    if (j < d) grow[j] = t * double(ka2);
+    if (j == DMAX) grow[d] = t;
 }
 
+#endif  // !VEGAS_SAMPLE_PREC
+
 // ---------------------------------------------------------------------------
-// Dispatch over (precision, integrand, dimension bucket).
+// Dispatch.  The event kernels are compiled for every d up to kExactDim and
+// for the buckets' own dimensions beyond; other d run guarded in the next
+// larger bucket.  Guards split an event into a block per dimension and keep
+// its table reads from being in flight together: per 1e7 events, d = 13
+// FP32-mixed with N = 37, 144 us guarded and 78 us exact with histograms (93
+// and 66 us without), and d = 5 product peak FP64 with N = 100, 71 and 46 us.
+// (The event kernels of one precision and integrand are one
+// compilation of this file each: VEGAS_SAMPLE_PREC, VEGAS_SAMPLE_KIND.)
+
+constexpr int kExactDim = 20;
 
 static int dim_bucket(int d)
 {
-    if (d <= 4) return 4;
-    if (d <= 8) return 8;
-    if (d <= 12) return 12;
-    if (d <= 16) return 16;
-    if (d <= 20) return 20;
+    if (d <= kExactDim) return d;
     if (d <= 24) return 24;
     if (d <= 32) return 32;
     if (d <= 48) return 48;
     return 64;
 }
 
+// Parts defined by the other compilations: the kernel for (d, histogram mode).
+using SampleFn = const void* (*)(int d, int hm);
+const void* sample_fn_64_0(int d, int hm);
+const void* sample_fn_64_1(int d, int hm);
+const void* sample_fn_64_2(int d, int hm);
+const void* sample_fn_64_3(int d, int hm);
+const void* sample_fn_32_0(int d, int hm);
+const void* sample_fn_32_1(int d, int hm);
+const void* sample_fn_32_2(int d, int hm);
+const void* sample_fn_32_3(int d, int hm);
+
+#ifdef VEGAS_SAMPLE_PREC
+
+template <class P, int KIND, int HM, int... D>
+static const void* exact_fn(int d, IntSeq<D...>)
+{
+    static const void* const fn[] = {reinterpret_cast<const void*>(&k_sample<P, KIND, D + 1, true, HM>)...};
+    return fn[d - 1];
+}
+
+template <class P, int KIND, int HM>
+static const void* sample_fn(int d)
+{
+    if (d <= kExactDim) return exact_fn<P, KIND, HM>(d, typename MakeIntSeq<kExactDim>::type());
+    // the FP64 discontinuous integrand's constants do not fit the registers
+    // beyond d = 24: without guards, the kernels spilled them in the loop
+    constexpr bool kWhole = !(P::is64 && KIND == GENZ_DISC);
+    switch (dim_bucket(d)) {
+    case 24:
+        return d == 24 ? reinterpret_cast<const void*>(&k_sample<P, KIND, 24, true, HM>)
+                       : reinterpret_cast<const void*>(&k_sample<P, KIND, 24, false, HM>);
+    case 32:
+        return d == 32 ? reinterpret_cast<const void*>(&k_sample<P, KIND, 32, kWhole, HM>)
+                       : reinterpret_cast<const void*>(&k_sample<P, KIND, 32, false, HM>);
+    case 48:
+        return d == 48 ? reinterpret_cast<const void*>(&k_sample<P, KIND, 48, kWhole, HM>)
+                       : reinterpret_cast<const void*>(&k_sample<P, KIND, 48, false, HM>);
+    default:
+        return d == 64 ? reinterpret_cast<const void*>(&k_sample<P, KIND, 64, kWhole, HM>)
+                       : reinterpret_cast<const void*>(&k_sample<P, KIND, 64, false, HM>);
+    }
+}
+
+#define VEGAS_PART_NAME2(p, k) sample_fn_##p##_##k
+#define VEGAS_PART_NAME(p, k) VEGAS_PART_NAME2(p, k)
+const void* VEGAS_PART_NAME(VEGAS_SAMPLE_PREC, VEGAS_SAMPLE_KIND)(int d, int hm)
+{
+    using P = pick_type<VEGAS_SAMPLE_PREC == 64, P64, P32>::type;
+    return hm == kHistNone ? sample_fn<P, VEGAS_SAMPLE_KIND, kHistNone>(d) : sample_fn<P, VEGAS_SAMPLE_KIND, kHistRows>(d);
+}
+
+#else
+
+static const void* sample_kernel(int prec, int kind, int d, bool hist)
+{
+    static const SampleFn f64[] = {sample_fn_64_0, sample_fn_64_1, sample_fn_64_2, sample_fn_64_3};
+    static const SampleFn f32[] = {sample_fn_32_0, sample_fn_32_1, sample_fn_32_2, sample_fn_32_3};
+    const int hm = hist ? kHistRows : kHistNone;
+    return (prec == FP64 ? f64 : f32)[kind](d, hm);
+}
+
 #define VEGAS_DMAX_SWITCH(DM, CALL)            \
     switch (DM) {                              \
     case 4: { constexpr int D_ = 4; CALL; }    \
     case 8: { constexpr int D_ = 8; CALL; }    \
-    case 12: { constexpr int D_ = 12; CALL; }  \
     case 16: { constexpr int D_ = 16; CALL; }  \
-    case 20: { constexpr int D_ = 20; CALL; }  \
-    case 24: { constexpr int D_ = 24; CALL; }  \
     case 32: { constexpr int D_ = 32; CALL; }  \
-    case 48: { constexpr int D_ = 48; CALL; }  \
     default: { constexpr int D_ = 64; CALL; }  \
     }
 
-// The histogram mode of a launch: none, or the fixed layout where it applies
-// (d in {4, 8, 12, 16}, N <= 64, 16 replicas), or the general one.
-static int hist_mode(int d, int N, int rep, bool hist)
+// The records' kernel guards every dimension.
+static int dump_bucket(int d)
 {
-    if (!hist) return kHistNone;
-    return (d == 4 || d == 8 || d == 12 || d == 16) && N <= kFixBins && rep == (1 << kFixRepLog2) ? kHistFixed
-                                                                                                 : kHistGeneral;
-}
-
-template <class P, int KIND>
-static const void* sample_fn(int d, int hm)
-{
-    if (hm == kHistFixed) {
-        if (d == 4) return reinterpret_cast<const void*>(&k_sample<P, KIND, 4, true, kHistFixed>);
-        if (d == 8) return reinterpret_cast<const void*>(&k_sample<P, KIND, 8, true, kHistFixed>);
-        if (d == 12) return reinterpret_cast<const void*>(&k_sample<P, KIND, 12, true, kHistFixed>);
-        return reinterpret_cast<const void*>(&k_sample<P, KIND, 16, true, kHistFixed>);
-    }
-    if (hm == kHistNone) {
-        if (d == dim_bucket(d)) {
-            VEGAS_DMAX_SWITCH(d, return reinterpret_cast<const void*>(&k_sample<P, KIND, D_, true, kHistNone>))
-        }
-        VEGAS_DMAX_SWITCH(dim_bucket(d), return reinterpret_cast<const void*>(&k_sample<P, KIND, D_, false, kHistNone>))
-    }
-    if (d == dim_bucket(d)) {
-        VEGAS_DMAX_SWITCH(d, return reinterpret_cast<const void*>(&k_sample<P, KIND, D_, true, kHistGeneral>))
-    }
-    VEGAS_DMAX_SWITCH(dim_bucket(d), return reinterpret_cast<const void*>(&k_sample<P, KIND, D_, false, kHistGeneral>))
-}
-
-template <class P>
-static const void* sample_fn_kind(int kind, int d, int hm)
-{
-    switch (kind) {
-    case GAUSS: return sample_fn<P, GAUSS>(d, hm);
-    case BIMODAL: return sample_fn<P, BIMODAL>(d, hm);
-    case GENZ_DISC: return sample_fn<P, GENZ_DISC>(d, hm);
-    default: return sample_fn<P, GENZ_PEAK>(d, hm);
-    }
-}
-
-static const void* sample_kernel(int prec, int kind, int d, int N, int rep, bool hist)
-{
-    const int hm = hist_mode(d, N, rep, hist);
-    return prec == FP64 ? sample_fn_kind<P64>(kind, d, hm) : sample_fn_kind<P32>(kind, d, hm);
+    return d <= 4 ? 4 : d <= 8 ? 8 : d <= 16 ? 16 : d <= 32 ? 32 : 64;
 }
 
 template <class P, int KIND>
 static const void* dump_fn(int d)
 {
-    VEGAS_DMAX_SWITCH(dim_bucket(d), return reinterpret_cast<const void*>(&k_dump<P, KIND, D_>))
+    VEGAS_DMAX_SWITCH(dump_bucket(d), return reinterpret_cast<const void*>(&k_dump<P, KIND, D_>))
 }
 
 template <class P>
@@ -469,29 +434,65 @@ static const void* dump_fn_kind(int kind, int d)
     }
 }
 
+template <class P, int... D>
+static const void* adjoint_exact(int d, IntSeq<D...>)
+{
+    static const void* const fn[] = {reinterpret_cast<const void*>(&k_adjoint<P, D + 1, true>)...};
+    return fn[d - 1];
+}
+
+template <class P, int... D>
+static const void* grad_exact(int d, IntSeq<D...>)
+{
+    static const void* const fn[] = {reinterpret_cast<const void*>(&k_sample_grad<P, D + 1, true>)...};
+    return fn[d - 1];
+}
+
 template <class P>
 static const void* adjoint_fn(int d)
 {
-    if (d == dim_bucket(d)) {
-        VEGAS_DMAX_SWITCH(d, return reinterpret_cast<const void*>(&k_adjoint<P, D_, true>))
+    switch (dim_bucket(d)) {
+    case 24:
+        return d == 24 ? reinterpret_cast<const void*>(&k_adjoint<P, 24, true>)
+                       : reinterpret_cast<const void*>(&k_adjoint<P, 24, false>);
+    case 32:
+        return d == 32 ? reinterpret_cast<const void*>(&k_adjoint<P, 32, true>)
+                       : reinterpret_cast<const void*>(&k_adjoint<P, 32, false>);
+    case 48:
+        return d == 48 ? reinterpret_cast<const void*>(&k_adjoint<P, 48, true>)
+                       : reinterpret_cast<const void*>(&k_adjoint<P, 48, false>);
+    case 64:
+        return d == 64 ? reinterpret_cast<const void*>(&k_adjoint<P, 64, true>)
+                       : reinterpret_cast<const void*>(&k_adjoint<P, 64, false>);
+    default: return adjoint_exact<P>(d, typename MakeIntSeq<kExactDim>::type());
     }
-    VEGAS_DMAX_SWITCH(dim_bucket(d), return reinterpret_cast<const void*>(&k_adjoint<P, D_, false>))
 }
 
 template <class P>
 static const void* sample_grad_fn(int d)
 {
-    if (d == dim_bucket(d)) {
-        VEGAS_DMAX_SWITCH(d, return reinterpret_cast<const void*>(&k_sample_grad<P, D_, true>))
+    switch (dim_bucket(d)) {
+    case 24:
+        return d == 24 ? reinterpret_cast<const void*>(&k_sample_grad<P, 24, true>)
+                       : reinterpret_cast<const void*>(&k_sample_grad<P, 24, false>);
+    case 32:
+        return d == 32 ? reinterpret_cast<const void*>(&k_sample_grad<P, 32, true>)
+                       : reinterpret_cast<const void*>(&k_sample_grad<P, 32, false>);
+    case 48:
+        return d == 48 ? reinterpret_cast<const void*>(&k_sample_grad<P, 48, true>)
+                       : reinterpret_cast<const void*>(&k_sample_grad<P, 48, false>);
+    case 64:
+        return d == 64 ? reinterpret_cast<const void*>(&k_sample_grad<P, 64, true>)
+                       : reinterpret_cast<const void*>(&k_sample_grad<P, 64, false>);
+    default: return grad_exact<P>(d, typename MakeIntSeq<kExactDim>::type());
     }
-    VEGAS_DMAX_SWITCH(dim_bucket(d), return reinterpret_cast<const void*>(&k_sample_grad<P, D_, false>))
 }
 
 hipError_t launch_sample_grad(int prec, const SampleArgs& a, double* gpart, int blocks, int threads, hipStream_t s)
 {
     const void* fn = prec == FP64 ? sample_grad_fn<P64>(a.d) : sample_grad_fn<P32>(a.d);
     const size_t tab = size_t(a.d) * a.N * tab_entry_bytes(prec, GAUSS);
-    const size_t lds = ((tab + 127) & ~size_t(127)) + sizeof(double) * (kBlock / 64);
+    const size_t lds = ((tab + 127) & ~size_t(127)) + red_bytes(2 + dim_bucket(a.d) + 1);
     void* args[] = {const_cast<SampleArgs*>(&a), &gpart};
     return hipLaunchKernel(fn, dim3(blocks), dim3(threads), args, lds, s);
 }
@@ -499,21 +500,16 @@ hipError_t launch_sample_grad(int prec, const SampleArgs& a, double* gpart, int 
 size_t sample_lds(int prec, int kind, int d, int N, int rep, bool hist)
 {
     // the wave partials of the block sums follow the table and histogram
-    const size_t red = sizeof(double) * (kBlock / 64);
-    switch (hist_mode(d, N, rep, hist)) {
-    case kHistNone: return lds_bytes(prec, kind, d, N, 0) + red;
-    case kHistFixed: return size_t(d) * kFixDimBytes + lds_bytes(prec, kind, d, N, 0) + red;
-    default: return lds_bytes(prec, kind, d, N, rep) + red;
-    }
+    return lds_bytes(prec, kind, d, N, hist ? rep : 0) + red_bytes(2);
 }
 
 hipError_t launch_sample(int prec, int kind, const SampleArgs& a, int blocks, int threads, hipStream_t s)
 {
-    const int rep = 1 << a.hrep_log2;
     const bool hist = a.hist != 0;
-    const void* fn = sample_kernel(prec, kind, a.d, a.N, rep, hist);
+    const void* fn = sample_kernel(prec, kind, a.d, hist);
     void* args[] = {const_cast<SampleArgs*>(&a)};
-    return hipLaunchKernel(fn, dim3(blocks), dim3(threads), args, sample_lds(prec, kind, a.d, a.N, rep, hist), s);
+    return hipLaunchKernel(fn, dim3(blocks), dim3(threads), args,
+                           sample_lds(prec, kind, a.d, a.N, 1 << a.hrep_log2, hist), s);
 }
 
 hipError_t launch_dump(int prec, int kind, const DumpArgs& a, hipStream_t s)
@@ -532,7 +528,7 @@ hipError_t launch_adjoint(int prec, const AdjointArgs& a, int blocks, hipStream_
 {
     const void* fn = prec == FP64 ? adjoint_fn<P64>(a.d) : adjoint_fn<P32>(a.d);
     const size_t tab = size_t(a.d) * a.N * tab_entry_bytes(prec, GAUSS);
-    const size_t lds = ((tab + 15) & ~size_t(15)) + sizeof(double) * (kBlock / 64);
+    const size_t lds = ((tab + 15) & ~size_t(15)) + red_bytes(dim_bucket(a.d) + 1);
     void* args[] = {const_cast<AdjointArgs*>(&a)};
     hipError_t e = hipLaunchKernel(fn, dim3(blocks), dim3(kBlock), args, lds, s);
     if (e != hipSuccess) return e;
@@ -543,12 +539,14 @@ hipError_t launch_adjoint(int prec, const AdjointArgs& a, int blocks, hipStream_
 int sample_max_blocks_per_cu(int prec, int kind, int d, int N, int threads, int rep)
 {
     int n = 0;
-    const void* fn = sample_kernel(prec, kind, d, N, rep, true);
+    const void* fn = sample_kernel(prec, kind, d, true);
     hipFuncAttributes at;
     if (hipFuncGetAttributes(&at, fn) == hipSuccess && threads > at.maxThreadsPerBlock) return 0;  // not launchable
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, threads, sample_lds(prec, kind, d, N, rep, true)) != hipSuccess)
         return 1;
     return n > 0 ? n : 1;
 }
+
+#endif  // VEGAS_SAMPLE_PREC
 
 }  // namespace vegas

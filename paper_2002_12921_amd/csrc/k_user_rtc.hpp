@@ -31,15 +31,21 @@ namespace user {
 constexpr int D = VEGAS_DIM;
 static_assert(D >= 1 && D <= kMaxDim, "VEGAS_DIM out of range");
 
-__device__ __forceinline__ BinConsts bin_consts(int N, const DevConst* c)
-{
+// Binning constants and the LDS address of each dimension's table (scalars the
+// compiler cannot split, as in the built-in kernels).
+struct MapConsts {
     BinConsts bc;
-    bc.mul = uint32_t(N);
-    bc.add = uint32_t(N) >> 1;
-    bc.h64 = (N & 1) ? 0x1p-33 : 0.0;
-    bc.s32 = c->two_m32;
-    return bc;
-}
+    uint32_t base[D];
+
+    __device__ __forceinline__ MapConsts(int N, uint32_t tab, int entry_log2)
+    {
+        bc.mul = uint32_t(N);
+        bc.add = uint32_t(N) >> 1;
+        bc.h64 = (N & 1) ? 0x1p-33 : 0.0;
+#pragma unroll
+        for (int i = 0; i < D; ++i) base[i] = __builtin_amdgcn_readfirstlane(tab + (uint32_t(i * N) << entry_log2));
+    }
+};
 
 #ifdef VEGAS_FP32
 // FP32-mixed context.  The table is the built-in FP32 one with centre 0:
@@ -48,102 +54,85 @@ __device__ __forceinline__ BinConsts bin_consts(int N, const DevConst* c)
 // the width product is kept in FP32 with its binary exponent moved out every
 // 8 dimensions, and the value f w = 2^ew (f wp) C is formed in FP64.
 using tab_t = float2;
-struct Event {
-    int b[D];
-    float del[D];  // RN32(lo)
-    float x[D];
-    float wp;
-    int ew;
+using map_real = float;
+constexpr int kEntryLog2 = 3;
+#else
+// FP64 context: x_i = fma(lo, W, E_b + h W), W the bin's width times 2^-32, the
+// built-in FP64 map with centre 0; the width product is multiplied by 2^128
+// before each group of four dimensions.
+using tab_t = double2;
+using map_real = double;
+constexpr int kEntryLog2 = 4;
+#endif
 
-    __device__ __forceinline__ void run(const tab_t* __restrict__ tab, const BinConsts& bc, uint64_t e, uint32_t t,
-                                        uint32_t ctr3, uint32_t key0, uint32_t key1, int N, float ds)
+struct Event {
+    uint32_t off[D];   // LDS address of each dimension's table entry
+    map_real del[D];   // lo (FP32: RN32(lo))
+    map_real x[D];
+    map_real wp;
+    int ew;            // FP32: binary exponent moved out of wp
+
+    __device__ __forceinline__ void run(const MapConsts& mc, uint64_t e, uint32_t t, uint32_t ctr3, uint32_t key0,
+                                        uint32_t key1, float ds)
     {
 #pragma clang fp contract(off)
         const uint32_t elo = uint32_t(e), ehi = uint32_t(e >> 32);
-        float w = 1.0f;
+        map_real w = sizeof(map_real) == 8 ? map_real(0x1p128) : map_real(1);
         int ewl = 0;
 #pragma unroll
         for (int g = 0; g < (D + 3) / 4; ++g) {
             const U4 k = philox4x32_10(elo, ehi, t, ctr3 + uint32_t(g), key0, key1);
+#ifndef VEGAS_FP32
+            if (g > 0) w *= 0x1p128;
+#endif
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const int i = 4 * g + q;
                 if (i < D) {
                     int bi;
                     uint32_t lo;
-                    bin_words(k.w[q], bc, bi, lo);
-                    const tab_t tb = (tab + i * N)[bi];
-                    const float dl = float(lo);
-                    b[i] = bi;
-                    del[i] = dl;
-                    x[i] = fmaf(dl, tb.y, tb.x) * ds;
+                    bin_words(k.w[q], mc.bc, bi, lo);
+                    const lds_ptr<const tab_t> p = entry_of<tab_t>(bi, mc.base[i]);
+                    off[i] = uint32_t(uint64_t(p));
+                    const tab_t tb = *(const tab_t*)p;
+                    del[i] = map_real(lo);
+#ifdef VEGAS_FP32
+                    x[i] = fmaf(del[i], tb.y, tb.x) * ds;
+#else
+                    x[i] = fma(del[i], tb.y, tb.x);
+#endif
                     w *= tb.y;
                 }
             }
+#ifdef VEGAS_FP32
             if ((g & 1) == 1 && 4 * g + 4 < D) {
                 int e2;
                 w = frexpf(w, &e2);
                 ewl += e2;
             }
+#endif
         }
         wp = w;
         ew = ewl;
     }
-    __device__ __forceinline__ double delta(int i, const BinConsts& bc) const { return double(del[i]) * 0x1p-32 + bc.h64; }
+    __device__ __forceinline__ int bin(int i, const MapConsts& mc) const { return int((off[i] - mc.base[i]) >> kEntryLog2); }
+    __device__ __forceinline__ double delta(int i, const MapConsts& mc) const { return double(del[i]) * 0x1p-32 + mc.bc.h64; }
+#ifdef VEGAS_FP32
     __device__ __forceinline__ double weight(double Cw) const { return ldexp(double(wp), ew) * Cw; }
     __device__ __forceinline__ double value(float f, double C) const
     {
 #pragma clang fp contract(off)
         return ldexp(double(f) * double(wp), ew) * C;  // the product of two floats is exact in FP64
     }
-};
 #else
-// FP64 context: delta = (lo + h)/2^32 is exact, x_i = fma(delta, W_b, E_b),
-// the built-in FP64 map with centre 0 (the table of a user context holds E_b
-// itself).
-using tab_t = double2;
-struct Event {
-    int b[D];
-    double del[D];
-    double x[D];
-    double wp;
-
-    __device__ __forceinline__ void run(const tab_t* __restrict__ tab, const BinConsts& bc, uint64_t e, uint32_t t,
-                                        uint32_t ctr3, uint32_t key0, uint32_t key1, int N, float)
-    {
-#pragma clang fp contract(off)
-        const uint32_t elo = uint32_t(e), ehi = uint32_t(e >> 32);
-        double w = 1.0;
-#pragma unroll
-        for (int g = 0; g < (D + 3) / 4; ++g) {
-            const U4 k = philox4x32_10(elo, ehi, t, ctr3 + uint32_t(g), key0, key1);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int i = 4 * g + q;
-                if (i < D) {
-                    int bi;
-                    uint32_t lo;
-                    bin_words(k.w[q], bc, bi, lo);
-                    const tab_t tb = (tab + i * N)[bi];
-                    const double dl = fma(double(lo), bc.s32, bc.h64);
-                    b[i] = bi;
-                    del[i] = dl;
-                    x[i] = fma(dl, tb.y, tb.x);
-                    w *= tb.y;
-                }
-            }
-        }
-        wp = w;
-    }
-    __device__ __forceinline__ double delta(int i, const BinConsts&) const { return del[i]; }
     __device__ __forceinline__ double weight(double Cw) const { return wp * Cw; }
     __device__ __forceinline__ double value(double f, double C) const
     {
 #pragma clang fp contract(off)
         return f * wp * C;
     }
-};
 #endif
+};
 
 // 2^-(ws + 32): the FP32 map's scale back to x (unused in FP64)
 __device__ __forceinline__ float map_scale(const DevConst* c) { return ldexpf(c->dscale32, -32); }
@@ -158,28 +147,29 @@ __device__ __forceinline__ void sample(const SampleArgs& a, const double* __rest
     const int dN = D * N;
     const size_t tab_bytes = (size_t(dN) * sizeof(tab_t) + 127) & ~size_t(127);
     const int rl2 = a.hrep_log2, rep = 1 << rl2;
-    const int lrep = int(threadIdx.x) & (rep - 1);
     const size_t hist_bytes = HIST ? size_t(dN) * rep * sizeof(double) : 0;
     tab_t* tab = reinterpret_cast<tab_t*>(smem);
     double* hist = reinterpret_cast<double*>(smem + tab_bytes);
     double* red = reinterpret_cast<double*>(smem + tab_bytes + hist_bytes);
+    const uint32_t ltab = lds_address(smem);
+    const HistAdder<kEntryLog2> hadd(ltab, ltab + uint32_t(tab_bytes), rl2);
+    const MapConsts mc(N, ltab, kEntryLog2);
 
     const tab_t* gtab = static_cast<const tab_t*>(a.tab);
     for (int k = threadIdx.x; k < dN; k += blockDim.x) tab[k] = gtab[k];
     if constexpr (HIST)
         for (int k = threadIdx.x; k < dN * rep; k += blockDim.x) hist[k] = 0.0;
+    const double C = a.cst->C;  // N^d (scaled, see DevConst)
+    const float ds = map_scale(a.cst);
     __syncthreads();
 
-    const BinConsts bc = bin_consts(N, a.cst);
-    const double C = a.cst->C;  // N^d (FP32: times 2^(-ws d))
-    const float ds = map_scale(a.cst);
     double s1 = 0.0, c1 = 0.0, s2 = 0.0, c2 = 0.0;
     double g1 = 0.0, g2 = 0.0;
     int ng = 0;
     const uint64_t stride = uint64_t(gridDim.x) * blockDim.x;
     for (uint64_t k = uint64_t(threadIdx.x) * gridDim.x + blockIdx.x; k < a.n; k += stride) {
         Event ev;
-        ev.run(tab, bc, a.e0 + k, a.t, a.ctr3, a.key0, a.key1, N, ds);
+        ev.run(mc, a.e0 + k, a.t, a.ctr3, a.key0, a.key1, ds);
         const vegas_real f = vegas_integrand(ev.x, D, params);
         double v, v2;
         {
@@ -195,30 +185,18 @@ __device__ __forceinline__ void sample(const SampleArgs& a, const double* __rest
             g1 = g2 = 0.0;
             ng = 0;
         }
-        if constexpr (HIST) {
-#pragma unroll
-            for (int i = 0; i < D; ++i) lds_atomic_add(&(hist + (i * N << rl2))[(ev.b[i] << rl2) | lrep], v2);
-        }
+        if constexpr (HIST) hadd.template add<D, true>(ev.off, D, v2);
     }
     kahan_add(s1, c1, g1);
     kahan_add(s2, c2, g2);
 
-    // block_sum synchronises, which also completes every histogram atomic
-    const double S1 = block_sum(s1 - c1, red);
-    const double S2 = block_sum(s2 - c2, red);
-    double* row = a.partials + size_t(blockIdx.x) * 2;
-    if (threadIdx.x == 0) {
-        row[0] = S1;
-        row[1] = S2;
-    }
+    // block_sums synchronises, which also completes every histogram atomic
+    const double v12[2] = {s1 - c1, s2 - c2};
+    const double S = block_sums(v12, red);
+    if (threadIdx.x < 2) a.partials[size_t(blockIdx.x) * 2 + threadIdx.x] = S;
     if constexpr (HIST) {
         double* slot = a.hslots + size_t((blockIdx.x >> 3) % kHistSlots) * dN;
-        for (int k = threadIdx.x; k < dN; k += blockDim.x) {
-            const int base = k << rl2;
-            double h = 0.0;
-            for (int r = 0; r < rep; ++r) h += hist[base + r];
-            atomicAdd(&slot[k], h);
-        }
+        for (int k = threadIdx.x; k < dN; k += blockDim.x) atomicAdd(&slot[k], replica_sum(hist, k, rl2));
     }
 }
 
@@ -250,18 +228,18 @@ extern "C" __global__ __launch_bounds__(256) void vegas_user_dump(vegas::DumpArg
     const tab_t* gtab = static_cast<const tab_t*>(a.tab);
     for (int k = threadIdx.x; k < D * N; k += blockDim.x) tab[k] = gtab[k];
     __syncthreads();
-    const BinConsts bc = user::bin_consts(N, a.cst);
+    const user::MapConsts mc(N, lds_address(smem), user::kEntryLog2);
     const double Cw = a.cst->Cw;
     const float ds = user::map_scale(a.cst);
     const uint64_t stride = uint64_t(gridDim.x) * blockDim.x;
     for (uint64_t k = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; k < a.n; k += stride) {
         user::Event ev;
-        ev.run(tab, bc, a.e0 + k, a.t, a.ctr3, a.key0, a.key1, N, ds);
+        ev.run(mc, a.e0 + k, a.t, a.ctr3, a.key0, a.key1, ds);
         double* row = a.out + k * size_t(3 * D + 2);
 #pragma unroll
         for (int i = 0; i < D; ++i) {
-            row[i] = double(ev.b[i]);
-            row[D + i] = ev.delta(i, bc);
+            row[i] = double(ev.bin(i, mc));
+            row[D + i] = ev.delta(i, mc);
             row[2 * D + i] = double(ev.x[i]);
         }
         row[3 * D] = ev.weight(Cw);

@@ -37,9 +37,10 @@ enum Prec { FP64 = 0, FP32 = 1 };
 // Derived per-problem constants, computed on the device from the raw FP64
 // parameters whenever they change.  The event kernels compute
 //   F  = the integrand's significand in the kernel precision,
-//   wp = product of the bin widths (FP32: each scaled by 2^ws, ws = round(log2 N)),
+//   wp = product of the bin widths (FP32: each scaled by 2^ws, ws = round(log2 N);
+//        FP64: times 2^(32 pad), pad the dimensions that the last group of four lacks),
 // and the event value v = f w = 2^(ew + fe) (F * wp) * C with C = Cf * Cw,
-// Cf the integrand normalisation and Cw = N^d (FP32: N^d 2^(-ws d)).
+// Cf the integrand normalisation and Cw = N^d (FP32: N^d 2^(-ws d); FP64: N^d 2^(-32 pad)).
 struct DevConst {
     double C;        // Cf * Cw
     double Cf;       // f = 2^fe F Cf
@@ -49,7 +50,6 @@ struct DevConst {
     double inv_a;    // GAUSS, BIMODAL: 1/a (adjoint)
     int32_t n_bins;  // N (binning)
     int32_t pad1;
-    double two_m32;  // 2^-32
     float kexp32;    // (unused by the kernels; kept for the layout)
     float dscale32;  // 2^-ws
     float ka32;      // GAUSS: RN32(1/a^2) (adjoint)
@@ -73,7 +73,7 @@ struct Layout {
     size_t params;    // double[kMaxParams]
     size_t cst;       // DevConst
     size_t edges;     // double[d][N+1]
-    size_t tab64;     // double2[d][N]  (E_b, E_{b+1}-E_b)
+    size_t tab64;     // double2[d][N]  (offset from the centre, width 2^-32)
     size_t tab32;     // float2 or float4 [d][N]  (offsets from the centres, scaled width)
     size_t thr;       // uint64[d]  Genz discontinuous: x_i > a_i as an integer threshold
     size_t partials;  // double[kMaxBlocks][2]  per-block (S1, S2) of the event kernel
@@ -128,6 +128,9 @@ inline size_t lds_bytes(int prec, int kind, int d, int N, int rep = 1)
     const size_t tab = size_t(d) * N * tab_entry_bytes(prec, kind);
     return ((tab + 127) & ~size_t(127)) + size_t(d) * N * 8 * size_t(rep);
 }
+
+// LDS of a block's sums of n values per thread: a partial per wave and value.
+inline size_t red_bytes(int n) { return sizeof(double) * size_t(n) * (kBlock / 64); }
 
 // Device pointers of one problem's state.
 struct ProblemPtrs {
@@ -318,13 +321,9 @@ hipError_t launch_reset_results(double* records, int32_t* rec_flag, DevResult* r
 hipError_t launch_copy_last(const DevResult* result, double* out2, hipStream_t s);
 int sample_max_blocks_per_cu(int prec, int kind, int d, int N, int threads, int rep);
 
-// Fixed histogram layout of the batch event kernel (buckets with d <= 16 whose
-// problems all have n_bins <= kBatchFixBins, 8 or 16 replicas): fix_l2 = log2
-// of the replicas, 0 for the general layout.
-constexpr int kBatchFixBins = 64;
 hipError_t launch_batch_sample(int prec, int kind, int dmax, size_t lds, const BatchArgs& a, int blocks,
-                               int threads, bool hist, int fix_l2, hipStream_t s);
-int batch_max_blocks_per_cu(int prec, int kind, int dmax, size_t lds, int threads, int fix_l2);
+                               int threads, bool hist, hipStream_t s);
+int batch_max_blocks_per_cu(int prec, int kind, int dmax, size_t lds, int threads);
 hipError_t launch_batch_finish(const BatchArgs& a, int dmax, int kind, int rec_idx, int flags, hipStream_t s);
 hipError_t launch_batch_reset(const BatchArgs& a, int dmax, int n_rec, int kind, hipStream_t s);
 hipError_t launch_batch_combine(const BatchArgs& a, int n_rec, hipStream_t s);

@@ -1,0 +1,83 @@
+"""The event kernels over the dimensions they are compiled for, with and
+without histograms and at every replica count, against the FP64 oracle on the
+same points.  Tolerances are the paths' own: 1e-12 for FP64 sums and bins;
+FP32-mixed 1e-6 up to d = 8, growing like d / 8 beyond."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2002_12921_amd import Vegas
+
+pytestmark = pytest.mark.gpu
+
+KINDS = {"gauss": oracle.GAUSS, "bimodal": oracle.BIMODAL, "genz_disc": oracle.GENZ_DISC, "genz_peak": oracle.GENZ_PEAK}
+
+
+def _params(kind, d):
+    r = np.random.default_rng(100 + d)
+    if kind == "gauss":
+        return [0.2] + list(r.uniform(0.3, 0.7, d))
+    if kind == "bimodal":
+        return [0.25] + list(r.uniform(0.3, 0.4, d)) + list(r.uniform(0.6, 0.7, d))
+    if kind == "genz_disc":
+        return list(r.uniform(0.5, 1.5, d)) + list(r.uniform(0.01, 0.1, d))
+    return list(r.uniform(0.7, 1.4, d)) + list(r.uniform(0.3, 0.7, d))
+
+
+def _check(kind, prec, d, N, M, replicas=(0,)):
+    params = _params(kind, d)
+    pr = oracle.Problem(d, N, KINDS[kind], params, seed=11)
+    # a grid away from uniform, its own in every dimension
+    r = np.random.default_rng(d)
+    E = np.zeros((d, N + 1))
+    E[:, 1:] = np.cumsum(r.uniform(0.5, 1.5, (d, N)), axis=1)
+    E /= E[:, -1:]
+    E[:, -1] = 1.0
+    o1, o2, Ho = oracle.accumulate(pr, E, 0, M)
+    tol = 1e-12 if prec == "fp64" else 1e-6 * max(1.0, d / 8)
+    sums = set()
+    for rep in replicas:
+        v = Vegas(d, N, kind, params, prec, seed=11)
+        v.set_edges(E)
+        if rep:
+            v.set_hist_replicas(rep)
+        v.iterate(M)
+        S1, S2, H = v.last_iteration()
+        assert abs(S1 - o1) <= tol * abs(o1) and abs(S2 - o2) <= tol * abs(o2), (d, rep)
+        assert np.all(np.abs(H - Ho) <= tol * Ho.sum(axis=1, keepdims=True)), (d, rep)
+        sums.add((S1, S2))
+    w = Vegas(d, N, kind, params, prec, seed=11)
+    w.set_edges(E)
+    w.iterate(M, hist=False)
+    S1, S2, H = w.last_iteration()
+    sums.add((S1, S2))
+    assert len(sums) == 1, (d, sums)  # the same bits with and without histograms, whatever the replicas
+    assert not H.any()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32_mixed"])
+@pytest.mark.parametrize("kind", list(KINDS))
+def test_every_dimension(kind, prec):
+    """d = 1..21, 24, 25 and 32: the kernels without guards, the guarded ones
+    on either side of a bucket's edge, and odd and even bin counts."""
+    for d in list(range(1, 22)) + [24, 25, 32]:
+        _check(kind, prec, d, 11 if d % 2 else 12, 6007)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32_mixed"])
+@pytest.mark.parametrize("kind,d,N", [("gauss", 1, 2), ("gauss", 6, 255), ("bimodal", 7, 65), ("genz_peak", 13, 64),
+                                      ("genz_disc", 18, 50)])
+def test_replica_counts(kind, d, N, prec):
+    """Every histogram replica count that fits gives the same sums and bins."""
+    fits = [r for r in (1, 2, 4, 8, 16) if d * N * (16 + 8 * r) + 512 <= 160 * 1024]
+    _check(kind, prec, d, N, 9001, [0] + fits)
+
+
+def test_largest_blocks_lds():
+    """The largest grids that fit the LDS (d * n_bins = 6816 in FP64, 10224 in
+    FP32-mixed) still run, and one more bin is still refused."""
+    from paper_2002_12921_amd import VegasError
+    for prec, d, N in (("fp64", 48, 142), ("fp32_mixed", 48, 213)):
+        _check("gauss", prec, d, N, 3001)
+        with pytest.raises(VegasError):
+            Vegas(d, N + 1, "gauss", _params("gauss", d), prec)
