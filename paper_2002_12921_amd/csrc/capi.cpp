@@ -377,9 +377,15 @@ vegas_status init_ctx(vegas_ctx** out, const vegas_desc* desc, const char* sourc
     // Gaussian took 88 us with one block of 16 and 114 us with two of 8
     // (d = 16, N = 50), 110 us with one block of 8 and 130 us with two of 4
     // (N = 100).
-    static const double kRepFactorLow[5] = {0.5, 0.65, 0.8, 0.93, 1.0};   // 1, 2, 4, 8, 16 replicas
+    // Where the kernel takes the dimensions in sets, 8 and 4 replicas have no
+    // conflicts either, and up to d = 8 more resident waves win over them: per
+    // 1e7 events, the d = 8 Gaussian with N = 200, FP32-mixed, took 46 us with 4
+    // replicas in two blocks and 47 with 8 in one; with N = 160, FP64, 57 and 58
+    // us; but d = 7, N = 255, FP64, 72 us with two (conflicting) replicas in two
+    // blocks and 60 with 8 in one.
+    static const double kRepFactorLow[5] = {0.4, 0.55, 0.8, 0.93, 1.0};   // 1, 2, 4, 8, 16 replicas
+    static const double kRepFactorSets[5] = {0.4, 0.55, 0.95, 0.98, 1.0};
     static const double kRepFactorHigh[5] = {0.05, 0.1, 0.2, 0.45, 1.0};
-    const double* kRepFactor = c->d > 8 ? kRepFactorHigh : kRepFactorLow;
     double best = -1.0;
     int per_cu = 1;
     // 768 comes after 512, so it is taken only where it holds strictly more
@@ -398,6 +404,9 @@ vegas_status init_ctx(vegas_ctx** out, const vegas_desc* desc, const char* sourc
                        bpc < 1) {
                 bpc = 1;
             }
+            const double* kRepFactor = c->d > 8                                                       ? kRepFactorHigh
+                                       : !source && sample_in_sets(c->prec, c->kind, c->d, c->N, 1 << l2) ? kRepFactorSets
+                                                                                                      : kRepFactorLow;
             const double score = double(bpc * th / 64) * kRepFactor[l2] * (th == 256 ? 0.92 : 1.0);
             if (score > best + 1e-9) {
                 best = score;

@@ -258,7 +258,8 @@ struct EventEval {
     using real = typename P::real;
     using tab_t = typename TabEntry<P, KIND>::type;
 
-    uint32_t off[DMAX];  // LDS address of each dimension's table entry: tab + (i N + bin) entries
+    int bin[DMAX];       // bin of each dimension
+    uint32_t off[DMAX];  // LDS address of its table entry
     real u[DMAX];     // x_i - centre_i (GAUSS, BIMODAL: mu / muA; DISC, PEAK: a_i); FP32: times S
     real del[DMAX];   // lo (FP32: RN32(lo))
     real wp;          // width product (scaled, see Cw; FP32: and ew)
@@ -267,12 +268,6 @@ struct EventEval {
     double s64;       // GAUSS: sum u_i^2 as accumulated (FP64 in both paths; FP32: of u S)
     int ew;           // FP32: binary exponent taken out of the width product
     int fe;           // FP32: binary exponent of the integrand (f ~ 2^fe F)
-
-    // bin of dimension i
-    __device__ __forceinline__ int bin(int i, int N, uint32_t tab) const
-    {
-        return int((off[i] - tab) >> TabLog2<P, KIND>::value) - i * N;
-    }
 
     // tab: LDS address of the table [d][N]
     __device__ __forceinline__ void run(const EvalConsts<P, KIND, DMAX>& c, uint32_t tab,
@@ -306,21 +301,20 @@ struct EventEval {
                     if (g > 0) w *= real(0x1p128);
                 // the group's four bins and table entries first, so that its
                 // LDS reads are in flight together before any is used
+                int bq[4];
                 uint32_t oq[4], loq[4];
                 tab_t tq[4];
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const int i = 4 * g + q;
                     if (i < d) {
-                        int bi;
-                        bin_words(k.w[q], c.bc, bi, loq[q]);
+                        bin_words(k.w[q], c.bc, bq[q], loq[q]);
                         constexpr int L = TabLog2<P, KIND>::value;
                         lds_ptr<const tab_t> pq;
-                        if constexpr (EvalConsts<P, KIND, DMAX>::kHoldBase)
-                            pq = entry_of<tab_t>(bi, c.base[i]);
-                        else
-                            pq = entry_of<tab_t>(bi, next);
-                        if constexpr (!EvalConsts<P, KIND, DMAX>::kHoldBase) {
+                        if constexpr (EvalConsts<P, KIND, DMAX>::kHoldBase) {
+                            pq = entry_of<tab_t>(bq[q], c.base[i]);
+                        } else {
+                            pq = entry_of<tab_t>(bq[q], next);
                             next += uint32_t(N) << L;
                             asm volatile("" : "+s"(next));
                         }
@@ -334,6 +328,7 @@ struct EventEval {
                     if (i < d) {
                         const uint32_t lo = loq[q];
                         off[i] = oq[q];
+                        bin[i] = bq[q];
                         const tab_t tb = tq[q];
                         real ui, ubi = real(0), width;
                         real dl;
@@ -598,13 +593,19 @@ __device__ __forceinline__ void lds_atomic_add(double* p, double v)
     __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// Adds into the block's histogram [dim][bin][replica] in LDS.  The table
-// [dim][bin] and the histogram share their indexing, so a histogram address is
-// the entry's table address shifted onto the bin's 2^rl2 replicas, plus the
-// lane's own start: one shift-add per dimension with the shift in a scalar
-// register, for every N, d and replica count.  (A layout with a compile-time
-// stride of 64 bins per dimension reached the same count for d in {4, 8, 12,
-// 16} and 16 replicas only, and padded the bins to 64.)
+// Adds into the block's histogram in LDS.
+//
+// What bounds an atomic is that the 16 lanes the LDS serves together (lanes
+// 16 q .. 16 q + 15 of a wave) hit 16 different bank pairs: 9.4 cycles per wave
+// then, 17 where two of them can meet, 31 at random.
+
+// [dimension][bin][replica], 2^rl2 replicas: 16 of them give every lane a bank
+// pair of its own.  The table [dimension][bin] and the histogram share their
+// indexing, so a histogram address is the entry's table address shifted onto
+// the bin's replicas, plus the lane's own start: one shift-add per dimension
+// with the shift in a scalar register, for every N, d and replica count.  (A
+// layout with a compile-time stride of 64 bins per dimension reached the same
+// count for d in {4, 8, 12, 16} and 16 replicas only, and padded the bins to 64.)
 template <int TL2>  // log2 of a table entry's bytes
 struct HistAdder {
     int sh;          // a table address to a histogram address
@@ -631,6 +632,93 @@ struct HistAdder {
         for (int i = 0; i < D; ++i)
             if (EXACT || i < d)
                 lds_atomic_add((double*)(lds_ptr<double>)(uint64_t((off[i] << sh) + start)), v2);
+    }
+};
+
+// [set][bin][dimension of the set][replica], for fewer than 16 replicas: the
+// dimensions are taken in sets of G = 2^GL with R = 16 / G replicas, so that a
+// bin's counters of a whole set fill one row of 128 bytes, and the lanes of
+// each G-th part of 16 go through the set's dimensions in an order of their own
+// (dimension k xor part in step k): the 16 lanes then add into the 16 places
+// of their rows, as with 16 replicas, for G / 16 of the LDS.  It costs GL
+// selects per dimension.  Per 1e7 events, conflicting replicas -> sets: d = 20, N
+// = 100 bimodal FP32-mixed (8 replicas) 194 -> 156 us, d = 16, N = 100 Gaussian
+// 108 -> 91 us FP32-mixed and 123 -> 104 us FP64, d = 8, N = 200 (4 replicas)
+// FP32-mixed 66 -> 46 us.  (Interleaving the table the same way would make the
+// address the plain layout's, but left a dimension's entries on every G-th
+// bank: 191 us for that bimodal.)
+template <int GL, int D, bool HOLD>
+struct HistSets {
+    static constexpr int G = 1 << GL, R = 16 >> GL;
+    // the row's start and the lane's place in step i, held where registers
+    // allow (HOLD), else the place in each step of a whole and of the last set
+    static constexpr bool kHold = HOLD;
+    uint32_t at[kHold ? D : G], last[G], set_bytes;
+
+    // the dimension of its set that the lane takes in step k of a set of m
+    static __device__ __forceinline__ uint32_t order(int k, int m)
+    {
+        const uint32_t part = (threadIdx.x & 15u) / R;
+        if (GL == 2 && m == 4) return uint32_t(k) ^ part;
+        if (m >= 2 && k < 2) return uint32_t(k) ^ (part & 1u);
+        return uint32_t(k);
+    }
+
+    __device__ __forceinline__ HistSets(uint32_t hist, int N)
+    {
+        set_bytes = uint32_t(N) * 128u;
+        auto place = [&](int k, int m) { return (order(k, m) * R + (threadIdx.x & uint32_t(R - 1))) << 3; };
+        if constexpr (kHold) {
+#pragma unroll
+            for (int i = 0; i < D; ++i)
+                at[i] = hist + uint32_t(i / G) * set_bytes + place(i % G, D - i / G * G < G ? D % G : G);
+        } else {
+#pragma unroll
+            for (int k = 0; k < G; ++k) {
+                at[k] = hist + place(k, G);
+                last[k] = hist + place(k, D % G);
+            }
+        }
+    }
+
+    // Exchanges x and y in the lanes whose part has bit BIT.
+    template <int BIT>
+    static __device__ __forceinline__ void exchange(int& x, int& y)
+    {
+        const bool other = ((threadIdx.x & 15u) / R) & (1u << BIT);
+        const int a = x, b = y;
+        x = other ? b : a;
+        y = other ? a : b;
+    }
+
+    __device__ __forceinline__ void add(const int (&bin)[D], double v2) const
+    {
+        int b[D];
+#pragma unroll
+        for (int i = 0; i < D; ++i) b[i] = bin[i];
+#pragma unroll
+        for (int s = 0; s < D; s += G) {
+            if (s + 1 < D) exchange<0>(b[s], b[s + 1]);
+            if constexpr (GL == 2) {
+                if (s + 3 < D) {
+                    exchange<0>(b[s + 2], b[s + 3]);
+                    exchange<1>(b[s], b[s + 2]);
+                    exchange<1>(b[s + 1], b[s + 3]);
+                }
+            }
+        }
+        struct Row {
+            double r[16];
+        };
+#pragma unroll
+        for (int i = 0; i < D; ++i) {
+            uint32_t row;
+            if constexpr (kHold)
+                row = at[i];
+            else
+                row = (D - i / G * G < G ? last[i % G] : at[i % G]) + uint32_t(i / G) * set_bytes;
+            lds_atomic_add((double*)(lds_ptr<double>)((lds_ptr<Row>)(uint64_t(row)) + b[i]), v2);
+        }
     }
 };
 

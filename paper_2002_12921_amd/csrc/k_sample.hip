@@ -15,8 +15,9 @@
 namespace vegas {
 
 // Histogram modes of the event kernel: none (an iteration whose grid is not
-// refined), or LDS replicas behind the table.
-constexpr int kHistNone = 0, kHistRows = 1;
+// refined), or LDS replicas behind the table with the dimensions in sets of
+// one (HistAdder), two or four (HistSets).
+constexpr int kHistNone = 0, kHistSets1 = 1, kHistSets2 = 2, kHistSets4 = 3;
 
 // Waves per SIMD the register allocation allows, at least and at most.
 //   FP64 up to d = 8, all but the discontinuous integrand: 6 (80 VGPRs).  They
@@ -30,6 +31,8 @@ constexpr int kHistNone = 0, kHistRows = 1;
 //     Its FP64 c_i and thresholds leave too few scalar registers, and at 128
 //     VGPRs (4 waves) the d = 16 kernel spilled 18 of them: 132.1-132.3 against
 //     123.4-123.6 us per 1e7 events; d = 20 with N = 100: 232 against 172 us.
+//     FP32-mixed likewise at d = 17 to 19 (FP64 c_i beside 20 bins; N = 100, d =
+//     19: 211 against 134 us).
 //   Beyond d = 8 with histograms: at most 4.  They run one 1024-thread block per
 //     CU (their LDS holds one block's table and replicated histogram), which the
 //     compiler cannot know from the dynamic LDS size: told so, it may use up to
@@ -38,7 +41,8 @@ constexpr int kHistNone = 0, kHistRows = 1;
 //   4 to 8 elsewhere.
 template <class P, int KIND, int DMAX, bool EXACT, int HM>
 struct Waves {
-    static constexpr bool three = P::is64 && KIND == GENZ_DISC && DMAX >= 14 && DMAX <= 24 && EXACT;
+    static constexpr bool three =
+        KIND == GENZ_DISC && EXACT && (P::is64 ? DMAX >= 14 && DMAX <= 24 : DMAX >= 17 && DMAX <= 19);
     static constexpr bool six = P::is64 && KIND != GENZ_DISC && DMAX <= 8;
     static constexpr bool eight = !P::is64 && DMAX <= 8;
     static constexpr int min = three ? 3 : six ? 6 : eight ? 8 : 4;
@@ -57,18 +61,22 @@ __global__ __attribute__((amdgpu_flat_work_group_size(1, MaxThreads<P, KIND, DMA
     SampleArgs a)
 {
     using tab_t = typename TabEntry<P, KIND>::type;
+    constexpr int GL = HM == kHistNone ? 0 : HM - 1;  // log2 of the dimensions in a set
     extern __shared__ __align__(128) unsigned char smem[];
     const int dN = a.d * a.N;
     const size_t tab_bytes = (size_t(dN) * sizeof(tab_t) + 127) & ~size_t(127);
-    // histogram [dim][bin][replica]: with 16 replicas every lane of a wave
-    // adds into its own bank pair (lane mod 16), whatever its bin
-    const int rl2 = a.hrep_log2, rep = 1 << rl2;
-    const size_t hist_bytes = HM == kHistNone ? 0 : size_t(dN) * rep * sizeof(double);
+    const int rl2 = GL > 0 ? 4 - GL : a.hrep_log2;
+    // counters of the histogram: whole sets
+    const int nh = GL > 0 ? ((DMAX + (1 << GL) - 1) >> GL << GL) * a.N : dN;
+    const size_t hist_bytes = HM == kHistNone ? 0 : size_t(nh) * sizeof(double) << rl2;
     tab_t* tab = reinterpret_cast<tab_t*>(smem);
     double* hist = reinterpret_cast<double*>(smem + tab_bytes);
     double* red = reinterpret_cast<double*>(smem + tab_bytes + hist_bytes);
     const uint32_t ltab = lds_address(smem);
+    static_assert(GL == 0 || EXACT, "sets of dimensions: kernels without guards only");
     const HistAdder<TabLog2<P, KIND>::value> hadd(ltab, ltab + uint32_t(tab_bytes), rl2);
+    constexpr bool kHoldRows = DMAX <= 24 && !(KIND == GENZ_DISC && DMAX > 12);
+    const HistSets<GL, DMAX, kHoldRows> hsets(ltab + uint32_t(tab_bytes), a.N);
 
     // the table's first entries and the constants are on their way while the
     // histogram is cleared
@@ -111,7 +119,10 @@ __global__ __attribute__((amdgpu_flat_work_group_size(1, MaxThreads<P, KIND, DMA
             g1 = g2 = 0.0;
             ng = 0;
         }
-        if constexpr (HM != kHistNone) hadd.template add<DMAX, EXACT>(ev.off, d, v2);
+        if constexpr (GL > 0)
+            hsets.add(ev.bin, v2);
+        else if constexpr (HM != kHistNone)
+            hadd.template add<DMAX, EXACT>(ev.off, d, v2);
     }
     kahan_add(s1, c1, g1);
     kahan_add(s2, c2, g2);
@@ -128,9 +139,15 @@ __global__ __attribute__((amdgpu_flat_work_group_size(1, MaxThreads<P, KIND, DMA
     // and ran about 1 % slower)
     double* slot = a.hslots + size_t((blockIdx.x >> 3) % kHistSlots) * dN;
     if constexpr (HM != kHistNone) {
-        for (int k = threadIdx.x; k < dN; k += blockDim.x) {
-            const double h = replica_sum(hist, k, rl2);
-            atomicAdd(&slot[k], h);
+        for (int k = threadIdx.x; k < nh; k += blockDim.x) {
+            if constexpr (GL == 0) {
+                atomicAdd(&slot[k], replica_sum(hist, k, rl2));
+            } else {
+                // counter k: bin b of dimension i of its set
+                const int s = k / (a.N << GL), r = k - s * (a.N << GL);
+                const int i = (s << GL) + (r & ((1 << GL) - 1)), b = r >> GL;
+                if (i < DMAX) atomicAdd(&slot[i * a.N + b], replica_sum<4 - GL>(hist, k));
+            }
         }
     }
 }
@@ -162,7 +179,7 @@ __global__ __launch_bounds__(kBlock) void k_dump(DumpArgs a)
 #pragma unroll
         for (int i = 0; i < DMAX; ++i) {
             if (i < a.d) {
-                row[i] = double(ev.bin(i, a.N, ltab));
+                row[i] = double(ev.bin[i]);
                 row[a.d + i] = double(ev.del[i]) * 0x1p-32 + cst.bc.h64;
                 row[2 * a.d + i] = double(ev.u[i]) * ds + a.cst->cA64[i];
             }
@@ -332,6 +349,12 @@ k_sample_grad(SampleArgs a, double* gpart)
 
 constexpr int kExactDim = 20;
 
+// Largest d whose kernels take the dimensions in sets: beyond, their bins and
+// constants do not fit the registers (d = 64, FP32-mixed Gaussian: 183 us per
+// 3e6 events with 4 conflicting replicas, 312 us with sets and spills; d = 32
+// discontinuous: 118 and 145 us).
+constexpr int sets_dim(int kind) { return kind == GENZ_DISC ? 20 : kind == GENZ_PEAK ? 24 : 32; }
+
 static int dim_bucket(int d)
 {
     if (d <= kExactDim) return d;
@@ -361,26 +384,36 @@ static const void* exact_fn(int d, IntSeq<D...>)
     return fn[d - 1];
 }
 
+template <int KIND>
+constexpr int kSetsDim = sets_dim(KIND);
+
+// d in (kExactDim, 64] but for the buckets' own: guarded, sets of one only
+template <class P, int KIND, int HM, int DMAX>
+static const void* guarded_fn()
+{
+    return reinterpret_cast<const void*>(&k_sample<P, KIND, DMAX, false, (HM > kHistSets1 ? kHistSets1 : HM)>);
+}
+
+template <class P, int KIND, int HM, int DMAX>
+static const void* whole_fn()
+{
+    // the FP64 discontinuous integrand's constants do not fit the registers
+    // beyond d = 24: without guards, the kernels spilled them in the loop
+    if constexpr (P::is64 && KIND == GENZ_DISC && DMAX > 24)
+        return guarded_fn<P, KIND, HM, DMAX>();
+    else
+        return reinterpret_cast<const void*>(&k_sample<P, KIND, DMAX, true, (DMAX > kSetsDim<KIND> && HM > kHistSets1 ? kHistSets1 : HM)>);
+}
+
 template <class P, int KIND, int HM>
 static const void* sample_fn(int d)
 {
     if (d <= kExactDim) return exact_fn<P, KIND, HM>(d, typename MakeIntSeq<kExactDim>::type());
-    // the FP64 discontinuous integrand's constants do not fit the registers
-    // beyond d = 24: without guards, the kernels spilled them in the loop
-    constexpr bool kWhole = !(P::is64 && KIND == GENZ_DISC);
     switch (dim_bucket(d)) {
-    case 24:
-        return d == 24 ? reinterpret_cast<const void*>(&k_sample<P, KIND, 24, true, HM>)
-                       : reinterpret_cast<const void*>(&k_sample<P, KIND, 24, false, HM>);
-    case 32:
-        return d == 32 ? reinterpret_cast<const void*>(&k_sample<P, KIND, 32, kWhole, HM>)
-                       : reinterpret_cast<const void*>(&k_sample<P, KIND, 32, false, HM>);
-    case 48:
-        return d == 48 ? reinterpret_cast<const void*>(&k_sample<P, KIND, 48, kWhole, HM>)
-                       : reinterpret_cast<const void*>(&k_sample<P, KIND, 48, false, HM>);
-    default:
-        return d == 64 ? reinterpret_cast<const void*>(&k_sample<P, KIND, 64, kWhole, HM>)
-                       : reinterpret_cast<const void*>(&k_sample<P, KIND, 64, false, HM>);
+    case 24: return d == 24 ? whole_fn<P, KIND, HM, 24>() : guarded_fn<P, KIND, HM, 24>();
+    case 32: return d == 32 ? whole_fn<P, KIND, HM, 32>() : guarded_fn<P, KIND, HM, 32>();
+    case 48: return d == 48 ? whole_fn<P, KIND, HM, 48>() : guarded_fn<P, KIND, HM, 48>();
+    default: return d == 64 ? whole_fn<P, KIND, HM, 64>() : guarded_fn<P, KIND, HM, 64>();
     }
 }
 
@@ -389,16 +422,32 @@ static const void* sample_fn(int d)
 const void* VEGAS_PART_NAME(VEGAS_SAMPLE_PREC, VEGAS_SAMPLE_KIND)(int d, int hm)
 {
     using P = pick_type<VEGAS_SAMPLE_PREC == 64, P64, P32>::type;
-    return hm == kHistNone ? sample_fn<P, VEGAS_SAMPLE_KIND, kHistNone>(d) : sample_fn<P, VEGAS_SAMPLE_KIND, kHistRows>(d);
+    switch (hm) {
+    case kHistNone: return sample_fn<P, VEGAS_SAMPLE_KIND, kHistNone>(d);
+    case kHistSets1: return sample_fn<P, VEGAS_SAMPLE_KIND, kHistSets1>(d);
+    case kHistSets2: return sample_fn<P, VEGAS_SAMPLE_KIND, kHistSets2>(d);
+    default: return sample_fn<P, VEGAS_SAMPLE_KIND, kHistSets4>(d);
+    }
 }
 
 #else
 
-static const void* sample_kernel(int prec, int kind, int d, bool hist)
+// The histogram mode of a launch.  Sets of two or four take the place of
+// conflicting replicas where 8 or 4 of them are used (in practice where 16
+// exceed the LDS, d N > 1150 or so), the kernel is one of those that can, and
+// the last set's padding fits.
+static int hist_mode(int prec, int kind, int d, int N, int rep, bool hist)
+{
+    if (!hist) return kHistNone;
+    const bool whole = d == dim_bucket(d) && d <= sets_dim(kind);
+    const int gl = !whole ? 0 : rep == 8 && d >= 2 ? 1 : rep == 4 && d >= 4 ? 2 : 0;
+    return gl > 0 && lds_bytes(prec, kind, d, N, rep, gl) + red_bytes(2) <= kLdsLimit ? 1 + gl : kHistSets1;
+}
+
+static const void* sample_kernel(int prec, int kind, int d, int hm)
 {
     static const SampleFn f64[] = {sample_fn_64_0, sample_fn_64_1, sample_fn_64_2, sample_fn_64_3};
     static const SampleFn f32[] = {sample_fn_32_0, sample_fn_32_1, sample_fn_32_2, sample_fn_32_3};
-    const int hm = hist ? kHistRows : kHistNone;
     return (prec == FP64 ? f64 : f32)[kind](d, hm);
 }
 
@@ -500,16 +549,22 @@ hipError_t launch_sample_grad(int prec, const SampleArgs& a, double* gpart, int 
 size_t sample_lds(int prec, int kind, int d, int N, int rep, bool hist)
 {
     // the wave partials of the block sums follow the table and histogram
-    return lds_bytes(prec, kind, d, N, hist ? rep : 0) + red_bytes(2);
+    const int hm = hist_mode(prec, kind, d, N, rep, hist);
+    return lds_bytes(prec, kind, d, N, hist ? rep : 0, hm > kHistSets1 ? hm - 1 : 0) + red_bytes(2);
+}
+
+bool sample_in_sets(int prec, int kind, int d, int N, int rep)
+{
+    return hist_mode(prec, kind, d, N, rep, true) > kHistSets1;
 }
 
 hipError_t launch_sample(int prec, int kind, const SampleArgs& a, int blocks, int threads, hipStream_t s)
 {
     const bool hist = a.hist != 0;
-    const void* fn = sample_kernel(prec, kind, a.d, hist);
+    const int rep = 1 << a.hrep_log2;
+    const void* fn = sample_kernel(prec, kind, a.d, hist_mode(prec, kind, a.d, a.N, rep, hist));
     void* args[] = {const_cast<SampleArgs*>(&a)};
-    return hipLaunchKernel(fn, dim3(blocks), dim3(threads), args,
-                           sample_lds(prec, kind, a.d, a.N, 1 << a.hrep_log2, hist), s);
+    return hipLaunchKernel(fn, dim3(blocks), dim3(threads), args, sample_lds(prec, kind, a.d, a.N, rep, hist), s);
 }
 
 hipError_t launch_dump(int prec, int kind, const DumpArgs& a, hipStream_t s)
@@ -539,7 +594,7 @@ hipError_t launch_adjoint(int prec, const AdjointArgs& a, int blocks, hipStream_
 int sample_max_blocks_per_cu(int prec, int kind, int d, int N, int threads, int rep)
 {
     int n = 0;
-    const void* fn = sample_kernel(prec, kind, d, true);
+    const void* fn = sample_kernel(prec, kind, d, hist_mode(prec, kind, d, N, rep, true));
     hipFuncAttributes at;
     if (hipFuncGetAttributes(&at, fn) == hipSuccess && threads > at.maxThreadsPerBlock) return 0;  // not launchable
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, threads, sample_lds(prec, kind, d, N, rep, true)) != hipSuccess)

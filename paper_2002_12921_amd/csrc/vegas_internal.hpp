@@ -122,11 +122,13 @@ inline size_t tab_entry_bytes(int prec, int kind)
 }
 
 // LDS of the event kernel: grid table, then the histogram with `rep`
-// replicas per bin ([dim][bin][replica]; lane l adds into replica l mod rep).
-inline size_t lds_bytes(int prec, int kind, int d, int N, int rep = 1)
+// replicas per bin (lane l adds into replica l mod rep), its dimensions in
+// sets of 2^gl (the last set is padded).
+inline size_t lds_bytes(int prec, int kind, int d, int N, int rep = 1, int gl = 0)
 {
     const size_t tab = size_t(d) * N * tab_entry_bytes(prec, kind);
-    return ((tab + 127) & ~size_t(127)) + size_t(d) * N * 8 * size_t(rep);
+    const size_t dims = size_t((d + (1 << gl) - 1) >> gl << gl);
+    return ((tab + 127) & ~size_t(127)) + dims * N * 8 * size_t(rep);
 }
 
 // LDS of a block's sums of n values per thread: a partial per wave and value.
@@ -300,6 +302,8 @@ struct BatchArgs {
 
 hipError_t launch_sample(int prec, int kind, const SampleArgs& a, int blocks, int threads, hipStream_t s);
 size_t sample_lds(int prec, int kind, int d, int N, int rep, bool hist = true);
+// whether the event kernel with this many replicas takes the dimensions in sets
+bool sample_in_sets(int prec, int kind, int d, int N, int rep);
 hipError_t launch_dump(int prec, int kind, const DumpArgs& a, hipStream_t s);
 hipError_t launch_sample_grad(int prec, const SampleArgs& a, double* gpart, int blocks, int threads, hipStream_t s);
 hipError_t launch_grad_scale(const double* G, const double* gout, void* grad, int n, int grad_fp32, hipStream_t s);

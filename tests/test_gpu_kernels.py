@@ -66,10 +66,14 @@ def test_every_dimension(kind, prec):
 
 @pytest.mark.parametrize("prec", ["fp64", "fp32_mixed"])
 @pytest.mark.parametrize("kind,d,N", [("gauss", 1, 2), ("gauss", 6, 255), ("bimodal", 7, 65), ("genz_peak", 13, 64),
-                                      ("genz_disc", 18, 50)])
+                                      ("genz_disc", 18, 50), ("bimodal", 20, 100), ("gauss", 9, 255),
+                                      ("genz_disc", 19, 119), ("gauss", 32, 60), ("genz_peak", 3, 40)])
 def test_replica_counts(kind, d, N, prec):
-    """Every histogram replica count that fits gives the same sums and bins."""
-    fits = [r for r in (1, 2, 4, 8, 16) if d * N * (16 + 8 * r) + 512 <= 160 * 1024]
+    """Every histogram replica count that fits gives the same sums and bins: one
+    dimension after another, and in sets of two (8 replicas) and four (4), the
+    last set whole, partial or padded past the LDS."""
+    entry = 8 if prec == "fp32_mixed" and kind != "bimodal" else 16
+    fits = [r for r in (1, 2, 4, 8, 16) if d * N * (entry + 8 * r) + 512 <= 160 * 1024]
     _check(kind, prec, d, N, 9001, [0] + fits)
 
 
