@@ -450,13 +450,6 @@ struct EventEval {
 
 // ---------------------------------------------------------------------------
 // Reductions.
-__device__ __forceinline__ double wave_sum(double v)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
-}
-
 // Event kernels add kGroup events per thread in plain FP64, then fold the
 // group's sums into Kahan-compensated S1, S2.
 constexpr int kGroup = 8;
@@ -490,13 +483,13 @@ __device__ __forceinline__ void neumaier_add(double& s, double& c, double v)
     s = t;
 }
 
-// v plus the value a DPP control takes from another lane (0 where it takes none).
+// The value a DPP control takes from another lane (0 where it takes none).
 template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ double dpp_add(double v)
+__device__ __forceinline__ double dpp_move(double v)
 {
     const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROW_MASK, 0xf, true);
     const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROW_MASK, 0xf, true);
-    return v + __hiloint2double(hi, lo);
+    return __hiloint2double(hi, lo);
 }
 
 // Sum over the wave's 64 lanes, valid in lane 63 (all lanes must be active):
@@ -505,12 +498,12 @@ __device__ __forceinline__ double dpp_add(double v)
 // for a round trip.
 __device__ __forceinline__ double wave_sum_last(double v)
 {
-    v = dpp_add<0x111, 0xf>(v);  // row_shr 1, 2, 4, 8
-    v = dpp_add<0x112, 0xf>(v);
-    v = dpp_add<0x114, 0xf>(v);
-    v = dpp_add<0x118, 0xf>(v);
-    v = dpp_add<0x142, 0xa>(v);  // row_bcast 15 into rows 1 and 3
-    v = dpp_add<0x143, 0xc>(v);  // row_bcast 31 into rows 2 and 3
+    v += dpp_move<0x111, 0xf>(v);  // row_shr 1, 2, 4, 8
+    v += dpp_move<0x112, 0xf>(v);
+    v += dpp_move<0x114, 0xf>(v);
+    v += dpp_move<0x118, 0xf>(v);
+    v += dpp_move<0x142, 0xa>(v);  // row_bcast 15 into rows 1 and 3
+    v += dpp_move<0x143, 0xc>(v);  // row_bcast 31 into rows 2 and 3
     return v;
 }
 
@@ -535,57 +528,73 @@ __device__ __forceinline__ double block_sums(const double (&v)[n], double* red)
     return t;
 }
 
-// Fixed-order sum of the (d + 1)-column rows part[rows][d + 1] of an
-// adjoint: one wave per column j (and j + 16, ...), lane l adding rows l,
-// l + 64, ... in order with two-sums, then an exact two-sum butterfly across
-// the wave (the same pair on every lane); column j times `scale` goes to
-// out[j], in FP64 or rounded once to FP32 (out_fp32).  Called by a whole
-// block of kMergeThreads threads.
-__device__ __forceinline__ void adjoint_merge_block(const double* part, int rows, int d, double scale, void* out,
-                                                    int out_fp32)
-{
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int j = wave; j <= d; j += kMergeThreads / 64) {
-        double s = 0.0, c = 0.0;
-        for (int r = lane; r < rows; r += 64) twosum_add(s, c, part[size_t(r) * (d + 1) + j]);
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const double s2 = __shfl_xor(s, o, 64), c2 = __shfl_xor(c, o, 64);
-            twosum_add(s, c, s2);
-            c += c2;
-        }
-        if (lane == 0) {
-            const double g = (s + c) * scale;
-            if (out_fp32)
-                static_cast<float*>(out)[j] = float(g);
-            else
-                static_cast<double*>(out)[j] = g;
-        }
-    }
-}
+// Inclusive prefix sum over the 64 lanes of a wave: the steps of wave_sum_last
+// leave in every lane the sum of the lanes up to it.
+__device__ __forceinline__ double wave_inclusive_scan(double v) { return wave_sum_last(v); }
 
-// Inclusive prefix sum over the 64 lanes of a wave (lane order).
-__device__ __forceinline__ double wave_inclusive_scan(double v)
-{
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const double o = __shfl_up(v, off, 64);
-        if (lane >= off) v += o;
-    }
-    return v;
-}
-
-// Running maximum over the 64 lanes of a wave (lane order).
+// Running maximum over the 64 lanes of a wave (lane order) of values >= 0.
 __device__ __forceinline__ double wave_inclusive_max(double v)
 {
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const double o = __shfl_up(v, off, 64);
-        if (lane >= off) v = fmax(v, o);
-    }
+    v = fmax(v, dpp_move<0x111, 0xf>(v));
+    v = fmax(v, dpp_move<0x112, 0xf>(v));
+    v = fmax(v, dpp_move<0x114, 0xf>(v));
+    v = fmax(v, dpp_move<0x118, 0xf>(v));
+    v = fmax(v, dpp_move<0x142, 0xa>(v));
+    v = fmax(v, dpp_move<0x143, 0xc>(v));
     return v;
+}
+
+// The pair sums (s + c) over the 64 lanes of a wave by exact two-sums, the
+// total in lane 63.
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ void dpp_pair_add(double& s, double& c)
+{
+    const double s2 = dpp_move<CTRL, ROW_MASK>(s), c2 = dpp_move<CTRL, ROW_MASK>(c);
+    twosum_add(s, c, s2);
+    c += c2;
+}
+
+__device__ __forceinline__ void wave_pair_sum_last(double& s, double& c)
+{
+    dpp_pair_add<0x111, 0xf>(s, c);
+    dpp_pair_add<0x112, 0xf>(s, c);
+    dpp_pair_add<0x114, 0xf>(s, c);
+    dpp_pair_add<0x118, 0xf>(s, c);
+    dpp_pair_add<0x142, 0xa>(s, c);
+    dpp_pair_add<0x143, 0xc>(s, c);
+}
+
+// Fixed-order sum of column j of the rows part[rows][d + 1] of an adjoint by
+// one wave: lane l adds rows l, l + 64, ... in order with two-sums (eight loads
+// in flight), then the lanes' pairs are added.  The column times `scale` goes
+// to out[j], in FP64 or rounded once to FP32 (out_fp32).
+__device__ __forceinline__ void adjoint_merge_column(const double* part, int rows, int d, int j, double scale,
+                                                     void* out, int out_fp32)
+{
+    const int lane = threadIdx.x & 63;
+    double s = 0.0, c = 0.0;
+    for (int r0 = lane; r0 < rows; r0 += 64 * 8) {
+        double v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = r0 + 64 * u < rows ? part[size_t(r0 + 64 * u) * (d + 1) + j] : 0.0;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) twosum_add(s, c, v[u]);
+    }
+    wave_pair_sum_last(s, c);
+    if (lane == 63) {
+        const double g = (s + c) * scale;
+        if (out_fp32)
+            static_cast<float*>(out)[j] = float(g);
+        else
+            static_cast<double*>(out)[j] = g;
+    }
+}
+
+// Value of lane l, the same l in every lane.
+__device__ __forceinline__ double lane_value(double v, int l)
+{
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
+                            __builtin_amdgcn_readlane(__double2loint(v), l));
 }
 
 __device__ __forceinline__ void lds_atomic_add(double* p, double v)

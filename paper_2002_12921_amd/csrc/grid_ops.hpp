@@ -10,7 +10,14 @@ namespace vegas {
 // variance of that mean, var_t = (S2/M - I_t^2)/(M - 1).  The iteration is
 // recorded (unless NO_RECORD: then it only becomes the last iteration's
 // estimate); the combination over recorded iterations runs in k_combine.
-__device__ static void finish_iteration(const MergeArgs& a, double S1, double S2)
+//
+// prior: the result's counts before this iteration, read by the caller ahead of
+// the sums (a read here would be a round trip to memory at the end).
+struct PriorCounts {
+    int64_t n_events, n_nonfinite;
+};
+
+__device__ static void finish_iteration(const MergeArgs& a, double S1, double S2, const PriorCounts& prior)
 {
     const double M = a.M;
     const double I = S1 / M;
@@ -33,8 +40,8 @@ __device__ static void finish_iteration(const MergeArgs& a, double S1, double S2
     R->last_integral = I;
     R->last_var = var;
     R->n_iter = rec + 1;
-    R->n_events += int64_t(M);
-    if (!ok) R->n_nonfinite += 1;
+    R->n_events = prior.n_events + int64_t(M);
+    if (!ok) R->n_nonfinite = prior.n_nonfinite + 1;
 }
 
 // Grid tables of dimension i from its edges E[0..N] (any address space).
@@ -80,39 +87,49 @@ __device__ __forceinline__ void write_table_entry(int i, int b, double lo, doubl
 // value below E_{b+1} by more than the two roundings can add, so no x of a
 // bin exceeds the next bin's lower edge.  Hence x > a holds exactly when
 // P >= T for the smallest such P, which is found here once per grid (a
-// bisection over lo in the bin that holds a), and the event kernels, FP64
+// search over lo in the bin that holds a), and the event kernels, FP64
 // and FP32 alike, decide with one integer comparison what the FP64 x would.
-// The threshold within bin b (edges Eb <= a < Eb1) of a grid of N bins.
-__device__ static uint64_t disc_bin_threshold(double Eb, double Eb1, int b, int N, double a)
+// The threshold within bin b (edges Eb <= a < Eb1) of a grid of N bins, by a
+// whole wave (every lane returns it): 64 probes a step narrow the 2^32
+// positions by 6 bits each, where a bisection by one lane takes 33 dependent
+// steps.
+__device__ static uint64_t disc_bin_threshold_wave(double Eb, double Eb1, int b, int N, double a)
 {
 #pragma clang fp contract(off)
+    const int lane = threadIdx.x & 63;
     const double w = Eb1 - Eb;
     const double h = (N & 1) ? 0.5 : 0.0;
-    uint64_t lo = 0, hi = uint64_t(1) << 32;  // hi: no event of bin b lies above a
-    while (lo < hi) {
-        const uint64_t mid = (lo + hi) >> 1;
-        const double x = Eb + ((double(mid) + h) * 0x1p-32) * w;
-        if (x > a)
-            hi = mid;
-        else
-            lo = mid + 1;
+    uint64_t lo = 0;  // no position below lo lies above a
+#pragma unroll
+    for (int shift = 26; shift >= -4; shift -= 6) {
+        const int sh = shift < 0 ? 0 : shift;
+        const uint64_t p = lo + (uint64_t(lane + 1) << sh) - 1;
+        const double x = Eb + ((double(p) + h) * 0x1p-32) * w;
+        const bool below = p < (uint64_t(1) << 32) && !(x > a) && (shift >= 0 || lane < 4);
+        lo += uint64_t(__popcll(__ballot(below))) << sh;
     }
     return (uint64_t(b) << 32) + lo;
 }
 
-__device__ static uint64_t disc_threshold(const double* E, int N, double a)
+// The threshold of a dimension with edges E[0..N], by one wave.
+__device__ static uint64_t disc_threshold_wave(const double* E, int N, double a)
 {
-    int b = 0;  // the bin holding a: the last b with E_b <= a (E_0 = 0 <= a < 1 = E_N)
-    for (int k = 1; k < N; ++k)
-        if (E[k] <= a) b = k;
-    return disc_bin_threshold(E[b], E[b + 1], b, N, a);
+    // the bin holding a: the last b with E_b <= a (E_0 = 0 <= a < 1 = E_N),
+    // i.e. the count of interior edges at or below it
+    const int lane = threadIdx.x & 63;
+    int b = 0;
+    for (int k0 = 1; k0 < N; k0 += 64) b += __popcll(__ballot(k0 + lane < N && E[min(k0 + lane, N)] <= a));
+    return disc_bin_threshold_wave(E[b], E[b + 1], b, N, a);
 }
 
 __device__ static void write_tables(int i, const double* E, const DevConst* __restrict__ c, int kind,
                                     int N, double2* tab64, float* tab32, uint64_t* thr)
 {
     for (int b = threadIdx.x; b < N; b += blockDim.x) write_table_entry(i, b, E[b], E[b + 1], c, kind, N, tab64, tab32);
-    if (kind == GENZ_DISC && threadIdx.x == 0) thr[i] = disc_threshold(E, N, c->cA64[i]);
+    if (kind == GENZ_DISC && threadIdx.x < 64) {
+        const uint64_t T = disc_threshold_wave(E, N, c->cA64[i]);
+        if (threadIdx.x == 0) thr[i] = T;
+    }
 }
 
 // Scale of the FP32 table's widths: 2^-ws with ws = round(log2 N), so the
@@ -183,9 +200,9 @@ __device__ static void refine_dim(const MergeArgs& a, int i, const double* h, co
             th += h[b];
             ts += Cs[b];
         }
-        th = wave_sum(th);
-        ts = wave_sum(ts);
-        if (t == 0) {
+        th = wave_sum_last(th);
+        ts = wave_sum_last(ts);
+        if (t == 63) {
             tot[0] = th;
             tot[1] = ts;
         }
@@ -271,12 +288,12 @@ __device__ static void refine_dim_wave(const MergeArgs& a, int i, double hb, dou
         else
             sm = (hl + hb + hr) / 3.0;
     }
-    const double th = wave_sum(hb), ts = wave_sum(sm);
+    const double th = lane_value(wave_sum_last(hb), 63), ts = lane_value(wave_sum_last(sm), 63);
     // empty, or not finite (an overflowing or NaN integrand): the grid and its tables stay
     if (!(th > 0.0 && th <= __DBL_MAX__ && ts > 0.0 && ts <= __DBL_MAX__)) return;
     const double r = in ? damp(sm / ts, a.alpha) : 0.0;
     const double C = wave_inclusive_max(wave_inclusive_scan(r));  // non-decreasing under rounding
-    const double R = __shfl(C, N - 1, 64);
+    const double R = lane_value(C, N - 1);
     // new edge k = b (only 1 <= k <= N - 1 is used): lower bound of level in C
     const double level = double(b) * R / double(N);
     int pos = 0;
@@ -303,8 +320,8 @@ __device__ static void refine_dim_wave(const MergeArgs& a, int i, double hb, dou
         // the bin holding a_i is the count of interior edges at or below it
         const double th = a.cst->cA64[i];
         const int bth = __popcll(__ballot(b >= 1 && b <= N - 1 && e <= th));
-        const double El = __shfl(lo, bth, 64), Eu = __shfl(hi, bth, 64);
-        if (b == 0) a.thr[i] = disc_bin_threshold(El, Eu, bth, N, th);
+        const uint64_t T = disc_bin_threshold_wave(lane_value(lo, bth), lane_value(hi, bth), bth, N, th);
+        if (b == 0) a.thr[i] = T;
     }
 }
 
@@ -322,15 +339,13 @@ __device__ static inline void refine_any(const MergeArgs& a, int i, const double
     refine_dim(a, i, h, Eo);
 }
 
-// One column group of the reduction (group 0: S1, S2; group 1+i: the
-// histogram of dimension i): the partial rows are summed in a fixed order,
-// folded into the chunk accumulator (when there is one), and at the end of
-// the iteration the group records the statistics or refines its dimension.
-// Histogram groups (when the rows carry H, as in batches): wave w adds rows
-// w, w + 16, ... (lane = column, so each load instruction reads consecutive
-// columns of one row), 32 loads in flight, with two-sums.  When the event
-// kernel accumulated H in slots instead, the group adds the slots.  Group 0 spreads its rows over all lanes and folds
-// each wave with a butterfly.  After one barrier wave 0 adds the 16 wave
+// One column group of a batch problem's reduction, by a block of kMergeThreads
+// (group 0: S1, S2; group 1+i: the histogram of dimension i): the partial rows
+// are summed in a fixed order, and the group records the statistics or refines
+// its dimension.  Histogram groups: wave w adds rows w, w + 16, ... (lane =
+// column, so each load instruction reads consecutive columns of one row), 32
+// loads in flight, with two-sums.  Group 0 spreads its rows over all lanes and
+// folds each wave with a butterfly.  After one barrier wave 0 adds the 16 wave
 // partials in order.  For N <= 64 wave 0 then refines with the column values
 // still in its registers.
 __device__ static void merge_group(const MergeArgs& a, const int g)
@@ -339,18 +354,18 @@ __device__ static void merge_group(const MergeArgs& a, const int g)
     const int off = g == 0 ? 0 : 2 + (g - 1) * a.N;
     if (g > 0 && (a.flags & MERGE_NO_HIST)) {
         // an iteration without histograms: its histogram row reads zero
-        if (a.flags & MERGE_END)
-            for (int k = threadIdx.x; k < ncol; k += blockDim.x) a.last[off + k] = 0.0;
+        for (int k = threadIdx.x; k < ncol; k += blockDim.x) a.last[off + k] = 0.0;
         return;
     }
     constexpr int kWaves = kMergeThreads / 64;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     __shared__ double ws_s[kWaves][kMaxBins + 1], ws_c[kWaves][kMaxBins + 1];
     __shared__ double fin[kMaxBins + 1], Eo[kMaxBins + 1];
-    const bool end = a.flags & MERGE_END;
-    const bool refine = end && (a.flags & MERGE_REFINE) && g > 0;
+    const bool refine = (a.flags & MERGE_REFINE) && g > 0;
     const bool wave_refine = refine && a.N <= 64;
-    // the edges the refinement needs, fetched while the rows are summed
+    // the edges and counts needed at the end, fetched while the rows are summed
+    PriorCounts prior{};
+    if (g == 0 && threadIdx.x == 0) prior = {a.result->n_events, a.result->n_nonfinite};
     double Eb = 0.0, Eb1 = 0.0;
     if (wave_refine && wave == 0) {
         const double* E = a.edges + size_t(g - 1) * (a.N + 1);
@@ -358,38 +373,6 @@ __device__ static void merge_group(const MergeArgs& a, const int g)
         Eb1 = lane < a.N ? E[lane + 1] : 0.0;
     } else if (refine && !wave_refine && int(threadIdx.x) <= a.N) {
         Eo[threadIdx.x] = a.edges[size_t(g - 1) * (a.N + 1) + threadIdx.x];
-    }
-    if (g > 0 && a.hslots) {
-        // histogram accumulated by the event kernel in kHistSlots slots (over
-        // every chunk of the iteration): at its end, add the slots in order,
-        // clear them for the next iteration, record, refine
-        if (!end) return;
-        const size_t dN = size_t(a.d) * a.N;
-        double mine = 0.0;
-        for (int col = threadIdx.x; col < ncol; col += blockDim.x) {
-            double* h = a.hslots + size_t(g - 1) * a.N + col;
-            double v[kHistSlots];
-#pragma unroll
-            for (int q = 0; q < kHistSlots; ++q) v[q] = h[q * dN];
-            double sum = 0.0;
-#pragma unroll
-            for (int q = 0; q < kHistSlots; ++q) {
-                sum += v[q];
-                h[q * dN] = 0.0;
-            }
-            a.last[off + col] = sum;
-            fin[col] = sum;
-            if (col == int(threadIdx.x)) mine = sum;
-        }
-        if (!refine) return;
-        if (wave_refine) {
-            // columns 0..N-1 are lanes 0..N-1 of wave 0
-            if (wave == 0) refine_dim_wave(a, g - 1, mine, Eb, Eb1);
-            return;
-        }
-        __syncthreads();
-        refine_dim(a, g - 1, fin, Eo);
-        return;
     }
     if (g == 0) {
         // S1, S2: lane pairs take rows (thread t: row lane t / 2, column t % 2),
@@ -433,7 +416,7 @@ __device__ static void merge_group(const MergeArgs& a, const int g)
     }
     __syncthreads();
     if (wave != 0) {
-        if (!end || !refine || wave_refine) return;
+        if (!refine || wave_refine) return;
     } else {
         double mine = 0.0;  // the value of column `lane` (first pass)
         for (int col = lane; col < ncol; col += 64) {
@@ -442,34 +425,14 @@ __device__ static void merge_group(const MergeArgs& a, const int g)
                 twosum_add(s, c, ws_s[w][col]);
                 c += ws_c[w][col];
             }
-            const double val = s + c;
-            double hi, lo;
-            if (a.flags & MERGE_BEGIN) {
-                hi = val;
-                lo = 0.0;
-            } else {  // double-double accumulation across chunks
-                hi = a.acc[off + col];
-                lo = a.acc[a.pstride + off + col];
-                const double t = hi + val;
-                const double bp = t - hi;
-                lo += (hi - (t - bp)) + (val - bp);
-                hi = t;
-            }
-            if (a.acc) {
-                a.acc[off + col] = hi;
-                a.acc[a.pstride + off + col] = lo;
-            }
-            if (end) {
-                const double v = hi + lo;
-                a.last[off + col] = v;
-                fin[col] = v;
-                if (col == lane) mine = v;
-            }
+            const double v = s + c;
+            a.last[off + col] = v;
+            fin[col] = v;
+            if (col == lane) mine = v;
         }
-        if (!end) return;
         if (g == 0) {
-            const double S2 = __shfl(mine, 1, 64);
-            if (lane == 0) finish_iteration(a, mine, S2);
+            const double S2 = lane_value(mine, 1);
+            if (lane == 0) finish_iteration(a, mine, S2, prior);
             return;
         }
         if (wave_refine) {
@@ -486,26 +449,37 @@ __device__ static void merge_group(const MergeArgs& a, const int g)
 // Inverse-variance combination of the recorded iterations flagged for it
 // ("value +- error", Table 1): I = sum(I_t/var_t)/sum(1/var_t),
 // sigma = sum(1/var_t)^(-1/2), chi^2/dof = sum (I_t - I)^2/var_t / (m - 1).
-// Sums run in record order, as the method states them (one thread).
+// By one wave: 64 records at a time are read and divided together, their terms
+// then added in record order (lane by lane), as the method states the sums.
 __device__ static void combine_records(const double* records, const int32_t* rec_flag, int n_rec, DevResult* R)
 {
+    const int lane = threadIdx.x & 63;
     double sw = 0.0, swi = 0.0;
     int m = 0;
-    for (int k = 0; k < n_rec; ++k) {
-        if (rec_flag[k]) {
-            sw = sw + 1.0 / records[2 * k + 1];
-            swi = swi + records[2 * k] / records[2 * k + 1];
-            ++m;
+    for (int k0 = 0; k0 < n_rec; k0 += 64) {
+        const int k = k0 + lane;
+        const bool use = k < n_rec && rec_flag[k] != 0;
+        const double I = use ? records[2 * k] : 0.0, var = use ? records[2 * k + 1] : 1.0;
+        const double w = 1.0 / var, wi = I / var;
+        uint64_t mask = __ballot(use);
+        m += __popcll(mask);
+        for (; mask; mask &= mask - 1) {
+            const int l = __ffsll((unsigned long long)mask) - 1;
+            sw += lane_value(w, l);
+            swi += lane_value(wi, l);
         }
     }
     const double mean = swi / sw;
     double chi2 = 0.0;
-    for (int k = 0; k < n_rec; ++k) {
-        if (rec_flag[k]) {
-            const double u = records[2 * k] - mean;
-            chi2 = chi2 + u * u / records[2 * k + 1];
-        }
+    for (int k0 = 0; k0 < n_rec; k0 += 64) {
+        const int k = k0 + lane;
+        const bool use = k < n_rec && rec_flag[k] != 0;
+        const double I = use ? records[2 * k] : 0.0, var = use ? records[2 * k + 1] : 1.0;
+        const double u = I - mean, t = u * u / var;
+        for (uint64_t mask = __ballot(use); mask; mask &= mask - 1)
+            chi2 += lane_value(t, __ffsll((unsigned long long)mask) - 1);
     }
+    if (lane != 0) return;
     const double nan = __builtin_nan("");
     R->integral = m > 0 ? mean : nan;
     R->sigma = m > 0 ? sqrt(1.0 / sw) : nan;

@@ -180,7 +180,6 @@ __global__ __launch_bounds__(kMergeThreads) void k_batch_finish(BatchArgs a, int
     if (g > pr.d) return;
     MergeArgs m{};
     m.partials = a.partials + pr.row0;
-    m.acc = nullptr;
     m.last = pr.last;
     m.edges = pr.edges;
     m.tab64 = pr.tab64;
@@ -229,7 +228,6 @@ __global__ __launch_bounds__(kMergeThreads) void k_batch_reset(BatchArgs a, int 
 
 __global__ void k_batch_combine(BatchArgs a, int n_rec)
 {
-    if (threadIdx.x != 0) return;
     const BatchProblem pr = a.probs[blockIdx.x];
     const int n = pr.result->n_iter < n_rec ? int(pr.result->n_iter) : n_rec;
     combine_records(pr.records, pr.rec_flag, n, pr.result);

@@ -1,24 +1,131 @@
 // Reduction, statistics and refinement kernels of one Vegas iteration.
 //
-// k_merge sums the per-block partial rows (S1, S2, H[d][N]) of the event
-// kernel into one row, in a fixed order, with one block per column group:
-// group 0 holds S1 and S2, group 1+i the N histogram bins of dimension i.
-// Each block folds its sums into the iteration's double-double accumulator
-// (several chunks form one iteration) and, at the end of the iteration,
-// either records the statistics (group 0) or refines its dimension of the
-// grid (groups 1..d, when asked).  No block waits for another and no
+// k_merge reduces what the event kernel left: the per-block rows (S1, S2), in a
+// fixed order, and the kHistSlots histogram accumulators.  Block 0 adds the
+// rows, folds them into the iteration's double-double accumulator (several
+// chunks form one iteration) and, at its end, records the statistics; at the
+// end block 1+i adds dimension i's slots in order, clears them, records the row
+// and, when asked, refines the dimension's grid; with MERGE_GRAD, block
+// d+1+j sums column j of the gradient rows.  No block waits for another and no
 // device-wide fence is needed: the next kernel on the stream sees the result.
+//
+// What bounds it is latency: a launch, a round trip to memory, the sums'
+// dependent steps.  So everything a block needs is read at its start, in one
+// round; sums and scans across a wave go through DPP (an exchange through the
+// LDS crossbar waits some 130 cycles, and a refinement made 30 of them, a
+// statistics block 14); and blocks are 256 threads, as many as N <= 255 bins
+// need.  (Behind a finished kernel even an empty one takes 4 us; alone, the d = 8
+// reduction with refinement takes 2.0 us, 3.2 with crossbar exchanges and
+// 1024-thread blocks; 3 iterations of 2000 events with a wait: 37 -> 31 us.)
 #include "grid_ops.hpp"
 
 namespace vegas {
 
-__global__ __launch_bounds__(kMergeThreads) void k_merge(MergeArgs a)
+constexpr int kSlotThreads = 256;
+
+// S1, S2: waves 0 and 2 take the rows' S1, waves 1 and 3 their S2, half of the
+// rows each.
+__device__ static void merge_sums(const MergeArgs& a)
 {
-    if (int(blockIdx.x) == a.d + 1) {  // MERGE_GRAD: the gradient rows, scaled by 1/M
-        adjoint_merge_block(a.gpart, a.rows, a.d, 1.0 / a.M, a.grad_out, 0);
+    __shared__ double ps[4], pc[4];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const bool begin = a.flags & MERGE_BEGIN, end = a.flags & MERGE_END;
+    // the accumulator and the counts, read while the rows are
+    PriorCounts prior{};
+    double hi0 = 0.0, lo0 = 0.0;
+    if (wave == 0) {
+        if (end && !(a.flags & MERGE_NO_RECORD)) prior = {a.result->n_events, a.result->n_nonfinite};
+        if (!begin && lane < 2) {
+            hi0 = a.acc[lane];
+            lo0 = a.acc[a.pstride + lane];
+        }
+    }
+    double s = 0.0, c = 0.0;
+    for (int r0 = (wave >> 1) * 64 + lane; r0 < a.rows; r0 += 128 * 4) {
+        double v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = r0 + 128 * u < a.rows ? a.partials[size_t(r0 + 128 * u) * 2 + (wave & 1)] : 0.0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) twosum_add(s, c, v[u]);
+    }
+    wave_pair_sum_last(s, c);
+    if (lane == 63) {
+        ps[wave] = s;
+        pc[wave] = c;
+    }
+    __syncthreads();
+    if (wave != 0) return;
+    double v = 0.0;
+    if (lane < 2) {
+        double t = ps[lane], e = pc[lane];
+        twosum_add(t, e, ps[lane + 2]);
+        e += pc[lane + 2];
+        const double val = t + e;
+        double hi = val, lo = 0.0;
+        if (!begin) {  // double-double accumulation across chunks
+            hi = hi0;
+            lo = lo0;
+            twosum_add(hi, lo, val);
+        }
+        a.acc[lane] = hi;
+        a.acc[a.pstride + lane] = lo;
+        v = hi + lo;
+        if (end) a.last[lane] = v;
+    }
+    if (!end) return;
+    const double S2 = lane_value(v, 1);
+    if (lane == 0) finish_iteration(a, v, S2, prior);
+}
+
+// Dimension i at the end of an iteration: its slots' sum, and the refinement.
+__device__ static void merge_slots(const MergeArgs& a, int i)
+{
+    const int t = threadIdx.x, N = a.N;
+    double* last = a.last + 2 + size_t(i) * N;
+    if (a.flags & MERGE_NO_HIST) {  // an iteration without histograms: its row reads zero
+        if (t < N) last[t] = 0.0;
         return;
     }
-    merge_group(a, blockIdx.x);
+    __shared__ double fin[kMaxBins + 1], Eo[kMaxBins + 1];
+    const bool refine = a.flags & MERGE_REFINE;
+    if (N <= 64 && t >= 64) return;  // one wave does it all
+    const double* E = a.edges + size_t(i) * (N + 1);
+    const double Eb = refine && t <= N ? E[t] : 0.0;
+    const double Eb1 = refine && t < N ? E[t + 1] : 0.0;
+    double mine = 0.0;
+    if (t < N) {
+        const size_t dN = size_t(a.d) * N;
+        double* h = a.hslots + size_t(i) * N + t;
+        double v[kHistSlots];
+#pragma unroll
+        for (int q = 0; q < kHistSlots; ++q) v[q] = h[q * dN];
+#pragma unroll
+        for (int q = 0; q < kHistSlots; ++q) {
+            mine += v[q];
+            h[q * dN] = 0.0;
+        }
+        last[t] = mine;
+    }
+    if (!refine) return;
+    if (N <= 64) {
+        refine_dim_wave(a, i, mine, Eb, Eb1);
+        return;
+    }
+    fin[t] = mine;
+    Eo[t] = Eb;
+    __syncthreads();
+    refine_dim(a, i, fin, Eo);
+}
+
+__global__ __launch_bounds__(kSlotThreads) void k_merge(MergeArgs a)
+{
+    const int g = blockIdx.x;
+    if (g == 0)
+        merge_sums(a);
+    else if (g <= a.d)
+        merge_slots(a, g - 1);
+    else if (threadIdx.x < 64)  // MERGE_GRAD: a column of the gradient rows, scaled by 1/M
+        adjoint_merge_column(a.gpart, a.rows, a.d, g - a.d - 1, 1.0 / a.M, a.grad_out, 0);
 }
 
 // grad = gout * G, rounded once to the output's precision.
@@ -35,7 +142,7 @@ __global__ void k_grad_scale(const double* G, const double* gout, void* grad, in
 }
 
 // Stand-alone refinement from the stored histograms of the last iteration.
-__global__ __launch_bounds__(kMergeThreads) void k_refine(MergeArgs a)
+__global__ __launch_bounds__(kSlotThreads) void k_refine(MergeArgs a)
 {
     __shared__ double h[kMaxBins], Eo[kMaxBins + 1];
     const int i = blockIdx.x;
@@ -45,73 +152,91 @@ __global__ __launch_bounds__(kMergeThreads) void k_refine(MergeArgs a)
     refine_any(a, i, h, Eo);
 }
 
-// Derived constants of the integrand (see DevConst), by one thread.
+// Derived constants of the integrand (see DevConst), by a block of at least 64
+// threads: thread i < kMaxDim those of dimension i, and its factor of the
+// normalisation; thread 0 then the product over the dimensions, in order.  (By
+// one thread the stores of the 64 dimensions and the functions of each
+// dimension followed one another: k_set_params at d = 8 took 5.4 us, now 3.1.)
 __device__ static void prepare_consts(int prec, int kind, int d, int N, const double* __restrict__ q,
                                       DevConst* __restrict__ c)
 {
+    __shared__ double factor[kMaxDim];
     const double pi = 3.14159265358979323846;
     const double log2e = 1.4426950408889634074;
+    const int i = threadIdx.x;
+    if (i < kMaxDim) {
+        double p1 = 0.0, p2 = 0.0, cA = 0.0, cB = 0.0, f = 1.0;
+        float p1f = 0.0f;
+        if (i < d) {
+            table_centres(kind, d, i, q, cA, cB);
+            if (kind == GAUSS || kind == BIMODAL) {
+                p1 = q[1 + i];
+                if (kind == BIMODAL) p2 = q[1 + d + i] - q[1 + i];  // FP64 map: u_B = u_A - (muB - muA)
+            } else if (kind == GENZ_DISC) {
+                // nu exp(sum c x) = [nu e^{sum c a}] exp(sum c (x - a)); per dimension
+                // nu e^{c a} = c / (e^{c (1 - a)} - 1)
+                const double cc = q[i], aa = q[d + i];
+                f = cc / expm1(cc * (1.0 - aa));
+                p1 = cc;
+                p2 = aa;
+            } else if (kind == GENZ_PEAK) {
+                // nu prod 1/(c^-2 + u^2) = [nu prod c^2] prod 1/(1 + c^2 u^2)
+                const double cc = q[i], aa = q[d + i];
+                f = cc / (atan(cc * (1.0 - aa)) + atan(cc * aa));
+                p1 = cc * cc;
+                p2 = aa;
+                p1f = float(cc * cc);
+            }
+        }
+        c->p1_64[i] = p1;
+        c->p2_64[i] = p2;
+        c->cA64[i] = cA;
+        c->cB64[i] = cB;
+        c->p1_32[i] = p1f;
+        c->p2_32[i] = 0.0f;
+        factor[i] = f;
+    }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
     c->n_bins = N;
     c->pad1 = 0;
     c->dscale32 = width_scale32(N);
     const int ws = int(rint(log2(double(N))));
     double nd = 1.0;
-    for (int i = 0; i < d; ++i) nd = nd * double(N);
-    c->Cw = ldexp(nd, prec == FP64 ? -32 * ((4 - d % 4) % 4) : -ws * d);
-    double Cf = 0.0;
-    c->kexp64 = c->kexp2_64 = c->inv_a = 0.0;
-    c->kexp32 = c->ka32 = c->pad0 = 0.0f;
-    for (int i = 0; i < kMaxDim; ++i) {
-        c->p1_64[i] = c->p2_64[i] = c->cA64[i] = c->cB64[i] = 0.0;
-        c->p1_32[i] = c->p2_32[i] = 0.0f;
-    }
-    for (int i = 0; i < d; ++i) table_centres(kind, d, i, q, c->cA64[i], c->cB64[i]);
+    for (int k = 0; k < d; ++k) nd = nd * double(N);
+    const double Cw = ldexp(nd, prec == FP64 ? -32 * ((4 - d % 4) % 4) : -ws * d);
+    double kexp64 = 0.0, kexp2_64 = 0.0, inv_a = 0.0, Cf = 1.0;
+    float kexp32 = 0.0f, ka32 = 0.0f;
     if (kind == GAUSS || kind == BIMODAL) {
         const double a = q[0];
         Cf = pow(a * sqrt(pi), double(-d));
         if (kind == BIMODAL) Cf = 0.5 * Cf;
-        c->kexp64 = 1.0 / (a * a);
-        c->kexp2_64 = log2e / (a * a);
-        c->inv_a = 1.0 / a;
-        c->kexp32 = float(log2e / (a * a));
-        c->ka32 = float(1.0 / (a * a));
-        for (int i = 0; i < d; ++i) {
-            c->p1_64[i] = q[1 + i];
-            if (kind == BIMODAL) c->p2_64[i] = q[1 + d + i] - q[1 + i];  // FP64 map: u_B = u_A - (muB - muA)
-        }
-    } else if (kind == GENZ_DISC) {
-        // nu exp(sum c x) = [nu e^{sum c a}] exp(sum c (x - a)); per dimension
-        // nu e^{c a} = c / (e^{c (1 - a)} - 1)
-        Cf = 1.0;
-        c->kexp2_64 = log2e;
-        for (int i = 0; i < d; ++i) {
-            const double cc = q[i], aa = q[d + i];
-            Cf = Cf * (cc / expm1(cc * (1.0 - aa)));
-            c->p1_64[i] = cc;
-            c->p2_64[i] = aa;
-        }
-    } else if (kind == USER) {
-        // the caller's f carries its own normalisation; C = N^d
-        Cf = 1.0;
+        kexp64 = 1.0 / (a * a);
+        kexp2_64 = log2e / (a * a);
+        inv_a = 1.0 / a;
+        kexp32 = float(log2e / (a * a));
+        ka32 = float(1.0 / (a * a));
     } else {
-        // nu prod 1/(c^-2 + u^2) = [nu prod c^2] prod 1/(1 + c^2 u^2)
-        Cf = 1.0;
-        for (int i = 0; i < d; ++i) {
-            const double cc = q[i], aa = q[d + i];
-            Cf = Cf * (cc / (atan(cc * (1.0 - aa)) + atan(cc * aa)));
-            c->p1_64[i] = cc * cc;
-            c->p2_64[i] = aa;
-            c->p1_32[i] = float(cc * cc);
-        }
+        if (kind == GENZ_DISC) kexp2_64 = log2e;
+        // (a user integrand carries its own normalisation: C = N^d)
+        if (kind != USER)
+            for (int k = 0; k < d; ++k) Cf = Cf * factor[k];
     }
+    c->Cw = Cw;
+    c->kexp64 = kexp64;
+    c->kexp2_64 = kexp2_64;
+    c->inv_a = inv_a;
+    c->kexp32 = kexp32;
+    c->ka32 = ka32;
+    c->pad0 = 0.0f;
     c->Cf = Cf;
-    c->C = Cf * c->Cw;
+    c->C = Cf * Cw;
 }
 
 __global__ void k_prepare(int prec, int kind, int d, int N, const double* __restrict__ q,
                           DevConst* __restrict__ c)
 {
-    if (threadIdx.x == 0 && blockIdx.x == 0) prepare_consts(prec, kind, d, N, q, c);
+    prepare_consts(prec, kind, d, N, q, c);
 }
 
 // New integrand parameters in one launch (block i: dimension i): every block
@@ -124,6 +249,10 @@ __global__ __launch_bounds__(256) void k_set_params(int prec, int kind, int d, i
                                                     const void* __restrict__ rest, int n, int is_fp32, ProblemPtrs p)
 {
     __shared__ double q[kMaxParams];
+    const int i = blockIdx.x, b = threadIdx.x;
+    // the block's edges, read beside the parameters (N <= 255: a bin per thread)
+    const double* E = p.edges + size_t(i) * (N + 1);
+    const double lo = E[min(b, N)], hi = E[min(b + 1, N)];
     for (int k = threadIdx.x; k < n; k += blockDim.x) {
         // value k: src[k], or with rest given, src[0] and rest[k - 1]
         const void* a = rest && k > 0 ? rest : src;
@@ -131,18 +260,18 @@ __global__ __launch_bounds__(256) void k_set_params(int prec, int kind, int d, i
         q[k] = is_fp32 ? double(static_cast<const float*>(a)[j]) : static_cast<const double*>(a)[j];
     }
     __syncthreads();
-    const int i = blockIdx.x;
     if (i == 0) {
         for (int k = threadIdx.x; k < n; k += blockDim.x) p.params[k] = q[k];
-        if (threadIdx.x == 0) prepare_consts(prec, kind, d, N, q, p.cst);
     }
     double cA, cB;
     table_centres(kind, d, i, q, cA, cB);
     const float ds = width_scale32(N);
-    const double* E = p.edges + size_t(i) * (N + 1);
-    for (int b = threadIdx.x; b < N; b += blockDim.x)
-        write_table_entry(i, b, E[b], E[b + 1], cA, cB, ds, kind, N, p.tab64, p.tab32);
-    if (kind == GENZ_DISC && threadIdx.x == 0) p.thr[i] = disc_threshold(E, N, cA);
+    if (b < N) write_table_entry(i, b, lo, hi, cA, cB, ds, kind, N, p.tab64, p.tab32);
+    if (kind == GENZ_DISC && threadIdx.x < 64) {
+        const uint64_t T = disc_threshold_wave(E, N, cA);
+        if (threadIdx.x == 0) p.thr[i] = T;
+    }
+    if (i == 0) prepare_consts(prec, kind, d, N, q, p.cst);
 }
 
 // Uniform grid E_k = k/N and a clean state (tables: k_build_tables).
@@ -181,7 +310,7 @@ __global__ void k_build_tables(ProblemPtrs p, int kind, int N)
 
 __global__ void k_combine(const double* records, const int32_t* rec_flag, int n_rec, DevResult* R)
 {
-    if (threadIdx.x == 0) combine_records(records, rec_flag, n_rec, R);
+    combine_records(records, rec_flag, n_rec, R);
 }
 
 __global__ void k_reset_results(double* records, int32_t* rec_flag, DevResult* R)
@@ -207,8 +336,9 @@ __global__ void k_copy_last(const DevResult* R, double* out)
 
 hipError_t launch_merge(const MergeArgs& a, hipStream_t s)
 {
-    const int blocks = a.d + 1 + ((a.flags & MERGE_GRAD) ? 1 : 0);
-    hipLaunchKernelGGL(k_merge, dim3(blocks), dim3(kMergeThreads), 0, s, a);
+    // blocks 1..d have work at the end of an iteration only
+    const int blocks = (a.flags & MERGE_END) ? a.d + 1 + ((a.flags & MERGE_GRAD) ? a.d + 1 : 0) : 1;
+    hipLaunchKernelGGL(k_merge, dim3(blocks), dim3(kSlotThreads), 0, s, a);
     return hipGetLastError();
 }
 
@@ -220,7 +350,7 @@ hipError_t launch_grad_scale(const double* G, const double* gout, void* grad, in
 
 hipError_t launch_refine(const MergeArgs& a, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_refine, dim3(a.d), dim3(kMergeThreads), 0, s, a);
+    hipLaunchKernelGGL(k_refine, dim3(a.d), dim3(kSlotThreads), 0, s, a);
     return hipGetLastError();
 }
 

@@ -248,9 +248,10 @@ __global__ __launch_bounds__(kBlock) void k_adjoint(AdjointArgs a)
 
 // Final step of the adjoint: the rows' fixed-order sums scaled by gout/M,
 // stored in FP64 or rounded once to FP32 (grad_fp32).
-__global__ __launch_bounds__(kMergeThreads) void k_adjoint_merge(AdjointArgs a, int rows)
+// One wave per component.
+__global__ __launch_bounds__(64) void k_adjoint_merge(AdjointArgs a, int rows)
 {
-    adjoint_merge_block(a.partials, rows, a.d, *a.gout / double(a.n), a.grad, a.grad_fp32);
+    adjoint_merge_column(a.partials, rows, a.d, blockIdx.x, *a.gout / double(a.n), a.grad, a.grad_fp32);
 }
 
 // Forward pass with the gradient (Gaussian, frozen grid, no histograms):
@@ -587,7 +588,7 @@ hipError_t launch_adjoint(int prec, const AdjointArgs& a, int blocks, hipStream_
     void* args[] = {const_cast<AdjointArgs*>(&a)};
     hipError_t e = hipLaunchKernel(fn, dim3(blocks), dim3(kBlock), args, lds, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_adjoint_merge, dim3(1), dim3(kMergeThreads), 0, s, a, blocks);
+    hipLaunchKernelGGL(k_adjoint_merge, dim3(a.d + 1), dim3(64), 0, s, a, blocks);
     return hipGetLastError();
 }
 

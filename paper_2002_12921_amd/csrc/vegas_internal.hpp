@@ -225,9 +225,9 @@ enum MergeFlags {
 };
 
 struct MergeArgs {
-    const double* partials;  // [rows][rstride]: S1, S2 (and H when hslots is null)
-    double* hslots;          // [kHistSlots][d*N] histogram accumulators, or null: the rows hold H
-    double* acc;             // [2][pstride]
+    const double* partials;  // [rows][rstride]: S1, S2 (and H in batches)
+    double* hslots;          // [kHistSlots][d*N] histogram accumulators (single problems)
+    double* acc;             // [2][pstride] (single problems)
     double* last;            // [pstride]
     double* edges;           // [d][N+1]
     double2* tab64;
@@ -243,7 +243,7 @@ struct MergeArgs {
     double* grad_out;        // MERGE_GRAD: [d + 1] (1/M) sum of the rows
     double* last_out;        // at END, when not null: (I_t, sigma_t) of the iteration
     int rows;
-    int rstride;             // doubles per partial row: 2, or pstride when the rows hold H
+    int rstride;             // doubles per partial row (batches; single problems: 2)
     int d, N, pstride, kind;
     int flags;
     int rec_idx;

@@ -85,3 +85,48 @@ def test_largest_blocks_lds():
         _check("gauss", prec, d, N, 3001)
         with pytest.raises(VegasError):
             Vegas(d, N + 1, "gauss", _params("gauss", d), prec)
+
+
+@pytest.mark.parametrize("N,a", [(2, 0.0), (3, 0.5), (50, 0.123456), (64, 0.999), (65, 0.25), (255, 0.7)])
+def test_disc_threshold_search(N, a):
+    """The discontinuity's position at every bin count the refinement has a
+    variant for, at and beside the first and last positions of a bin: events
+    counted inside are the oracle's, after a refinement (one wave or the block
+    rebuilds the thresholds) and with new parameters from the device."""
+    import torch
+    d, M = 2, 30_011
+    params = [0.7, 1.3, a, 0.2]
+    v = Vegas(d, N, "genz_disc", params, "fp64", seed=3)
+    for step in range(3):
+        E = v.edges()
+        if step == 2:  # an edge of the current grid as the threshold
+            params = [0.7, 1.3, float(E[0, N // 2]), float(np.nextafter(E[1, 1], 0))]
+            v.set_params_device(torch.tensor(params, dtype=torch.float64, device="cuda"))
+        pr = oracle.Problem(d, N, oracle.GENZ_DISC, params, seed=3)
+        v.iterate(M, refine=True)
+        S1, S2, H = v.last_iteration()
+        o1, o2, Ho = oracle.accumulate(pr, E, step, M)
+        assert abs(S1 - o1) <= 1e-12 * o1 and abs(S2 - o2) <= 1e-12 * o2, step
+        assert np.all(np.abs(H - Ho) <= 1e-12 * Ho.sum(axis=1, keepdims=True)), step
+        assert np.max(np.abs(v.edges() - oracle.refine(H, E, 1.5))) <= 1e-12, step
+
+
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 200])
+def test_combination_over_many_records(n):
+    """The combination reads its records 64 at a time: every n around that, with
+    iterations left out, equals the sums taken one after another."""
+    v = Vegas(1, 10, "gauss", [0.3, 0.4], "fp64", seed=5)
+    I, var = [], []
+    for k in range(n):
+        use = k % 3 != 1 or n == 1
+        v.iterate(257, combine=use)
+        S1, S2, _ = v.last_iteration()
+        if use:
+            i, s = oracle.iteration_stats(S1, S2, 257)
+            I.append(i)
+            var.append(s)
+    r = v.result()
+    m, s, c = oracle.combine(np.array(I), np.array(var))
+    assert r["n_iter"] == n and r["n_combined"] == len(I)
+    assert abs(r["integral"] - m) <= 1e-13 * abs(m) and abs(r["sigma"] - s) <= 1e-13 * s
+    assert (np.isnan(c) and np.isnan(r["chi2_dof"])) or abs(r["chi2_dof"] - c) <= 1e-11 * max(c, 1.0)
