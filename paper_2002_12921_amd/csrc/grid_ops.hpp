@@ -446,13 +446,24 @@ __device__ static void merge_group(const MergeArgs& a, const int g)
     refine_dim(a, g - 1, fin, Eo);
 }
 
+// Says that the thread's writes are done (they are visible to the host, and to
+// every stream, before the mark is).
+__device__ inline void host_post(const HostPost& p)
+{
+    __threadfence_system();
+    __hip_atomic_store(p.mark, p.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Inverse-variance combination of the recorded iterations flagged for it
 // ("value +- error", Table 1): I = sum(I_t/var_t)/sum(1/var_t),
 // sigma = sum(1/var_t)^(-1/2), chi^2/dof = sum (I_t - I)^2/var_t / (m - 1).
 // By one wave: 64 records at a time are read and divided together, their terms
 // then added in record order (lane by lane), as the method states the sums.
-__device__ static void combine_records(const double* records, const int32_t* rec_flag, int n_rec, DevResult* R)
+// host.to (may be null): the whole result block is written there too.
+__device__ static void combine_records(const double* records, const int32_t* rec_flag, int n_rec, DevResult* R,
+                                       HostPost host)
 {
+    DevResult out = *R;  // (n_combined and the combination are replaced)
     const int lane = threadIdx.x & 63;
     double sw = 0.0, swi = 0.0;
     int m = 0;
@@ -481,10 +492,18 @@ __device__ static void combine_records(const double* records, const int32_t* rec
     }
     if (lane != 0) return;
     const double nan = __builtin_nan("");
-    R->integral = m > 0 ? mean : nan;
-    R->sigma = m > 0 ? sqrt(1.0 / sw) : nan;
-    R->chi2_dof = m > 1 ? chi2 / double(m - 1) : nan;
-    R->n_combined = m;
+    out.integral = m > 0 ? mean : nan;
+    out.sigma = m > 0 ? sqrt(1.0 / sw) : nan;
+    out.chi2_dof = m > 1 ? chi2 / double(m - 1) : nan;
+    out.n_combined = m;
+    R->integral = out.integral;
+    R->sigma = out.sigma;
+    R->chi2_dof = out.chi2_dof;
+    R->n_combined = out.n_combined;
+    if (host.to) {
+        *static_cast<DevResult*>(host.to) = out;
+        host_post(host);
+    }
 }
 
 }  // namespace vegas

@@ -230,7 +230,7 @@ __global__ void k_batch_combine(BatchArgs a, int n_rec)
 {
     const BatchProblem pr = a.probs[blockIdx.x];
     const int n = pr.result->n_iter < n_rec ? int(pr.result->n_iter) : n_rec;
-    combine_records(pr.records, pr.rec_flag, n, pr.result);
+    combine_records(pr.records, pr.rec_flag, n, pr.result, HostPost{});
 }
 
 hipError_t launch_batch_combine(const BatchArgs& a, int n_rec, hipStream_t s)

@@ -17,6 +17,8 @@
 // need.  (Behind a finished kernel even an empty one takes 4 us; alone, the d = 8
 // reduction with refinement takes 2.0 us, 3.2 with crossbar exchanges and
 // 1024-thread blocks; 3 iterations of 2000 events with a wait: 37 -> 31 us.)
+#include <cstring>
+
 #include "grid_ops.hpp"
 
 namespace vegas {
@@ -308,9 +310,32 @@ __global__ void k_build_tables(ProblemPtrs p, int kind, int N)
     write_tables(i, p.edges + size_t(i) * (N + 1), p.cst, kind, N, p.tab64, p.tab32, p.thr);
 }
 
-__global__ void k_combine(const double* records, const int32_t* rec_flag, int n_rec, DevResult* R)
+// host.to (may be null): pinned host memory the result block is written to as
+// well, which saves the copy behind this kernel (a kernel's gap and a call).
+__global__ __launch_bounds__(64) void k_combine(const double* records, const int32_t* rec_flag, int n_rec, DevResult* R,
+                                                HostPost host)
 {
-    combine_records(records, rec_flag, n_rec, R);
+    combine_records(records, rec_flag, n_rec, R, host);
+}
+
+// n values to pinned host memory, by one block, which then posts the mark.
+__global__ __launch_bounds__(1024) void k_copy_out(const double* __restrict__ src, int n, HostPost host)
+{
+    double* dst = static_cast<double*>(host.to);
+    for (int k = threadIdx.x; k < n; k += blockDim.x) dst[k] = src[k];
+    __threadfence_system();
+    __syncthreads();
+    if (threadIdx.x == 0) host_post(host);
+}
+
+// New edges of dimensions i0, i0 + 1, ... (block i: dimension i0 + i), carried
+// by the launch itself: the edges, the tables and the threshold.
+__global__ __launch_bounds__(256) void k_set_edges(EdgeValues v, int i0, ProblemPtrs p, int kind, int N)
+{
+    const int i = i0 + blockIdx.x;
+    const double* E = v.e + size_t(blockIdx.x) * (N + 1);
+    for (int k = threadIdx.x; k <= N; k += blockDim.x) p.edges[size_t(i) * (N + 1) + k] = E[k];
+    write_tables(i, E, p.cst, kind, N, p.tab64, p.tab32, p.thr);
 }
 
 __global__ void k_reset_results(double* records, int32_t* rec_flag, DevResult* R)
@@ -381,10 +406,30 @@ hipError_t launch_build_tables(const ProblemPtrs& p, int kind, int d, int N, hip
 }
 
 hipError_t launch_combine(const double* records, const int32_t* rec_flag, int n_rec, DevResult* result,
-                          hipStream_t s)
+                          const HostPost& host, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_combine, dim3(1), dim3(64), 0, s, records, rec_flag, n_rec, result);
+    hipLaunchKernelGGL(k_combine, dim3(1), dim3(64), 0, s, records, rec_flag, n_rec, result, host);
     return hipGetLastError();
+}
+
+hipError_t launch_copy_out(const double* src, int n, const HostPost& host, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_copy_out, dim3(1), dim3(n > 256 ? 1024 : 256), 0, s, src, n, host);
+    return hipGetLastError();
+}
+
+hipError_t launch_set_edges(const double* host_edges, const ProblemPtrs& p, int kind, int d, int N, hipStream_t s)
+{
+    const int per = kEdgeValues / (N + 1);  // dimensions a launch carries
+    for (int i0 = 0; i0 < d; i0 += per) {
+        EdgeValues v;
+        const int n = d - i0 < per ? d - i0 : per;
+        std::memcpy(v.e, host_edges + size_t(i0) * (N + 1), sizeof(double) * size_t(n) * (N + 1));
+        hipLaunchKernelGGL(k_set_edges, dim3(n), dim3(256), 0, s, v, i0, p, kind, N);
+        const hipError_t he = hipGetLastError();
+        if (he != hipSuccess) return he;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_set_params(int prec, int kind, int d, int N, const void* src, int n, int is_fp32,

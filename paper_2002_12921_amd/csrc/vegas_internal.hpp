@@ -192,6 +192,20 @@ struct SampleArgs {
     int hist;            // 0: no histograms this launch (only S1, S2 are written)
 };
 
+// Where a kernel writes results for the host (pinned memory), and the mark it
+// stores behind them: a number of the context's that no earlier call used.
+struct HostPost {
+    void* to;
+    uint64_t* mark;
+    uint64_t seq;
+};
+
+// Edges carried in a launch's arguments (within 4 KiB with the others).
+constexpr int kEdgeValues = 480;
+struct EdgeValues {
+    double e[kEdgeValues];
+};
+
 struct DumpArgs {
     const DevConst* cst;
     const void* tab;
@@ -315,8 +329,13 @@ hipError_t launch_prepare(int prec, int kind, int d, int N, const double* params
 hipError_t launch_init_state(const ProblemPtrs& p, int d, int N, int pstride, hipStream_t s);
 hipError_t launch_build_tables(const ProblemPtrs& p, int kind, int d, int N, hipStream_t s);
 hipError_t launch_zero(double* x, size_t n, hipStream_t s);
+// host.to: receives the result block as well, or null
 hipError_t launch_combine(const double* records, const int32_t* rec_flag, int n_rec, DevResult* result,
-                          hipStream_t s);
+                          const HostPost& host, hipStream_t s);
+hipError_t launch_copy_out(const double* src, int n, const HostPost& host, hipStream_t s);
+// host_edges[d][N+1] are taken during the call, in launches of
+// kEdgeValues / (N + 1) dimensions each
+hipError_t launch_set_edges(const double* host_edges, const ProblemPtrs& p, int kind, int d, int N, hipStream_t s);
 // rest: null (all n values in src), or values 1..n-1 (src holds value 0)
 hipError_t launch_set_params(int prec, int kind, int d, int N, const void* src, int n, int is_fp32,
                              const ProblemPtrs& p, hipStream_t s, const void* rest = nullptr);

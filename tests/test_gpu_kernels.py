@@ -130,3 +130,27 @@ def test_combination_over_many_records(n):
     assert r["n_iter"] == n and r["n_combined"] == len(I)
     assert abs(r["integral"] - m) <= 1e-13 * abs(m) and abs(r["sigma"] - s) <= 1e-13 * s
     assert (np.isnan(c) and np.isnan(r["chi2_dof"])) or abs(r["chi2_dof"] - c) <= 1e-11 * max(c, 1.0)
+
+
+@pytest.mark.parametrize("d,N", [(1, 2), (1, 255), (2, 255), (3, 255), (9, 50), (18, 50), (19, 50), (16, 255), (25, 255)])
+def test_edges_there_and_back(d, N):
+    """Edges carried by one launch, by two and as a copy, and read back by a
+    kernel (up to 4096 values) or a copy: the same bits, and the tables built
+    from them give the oracle's sums; results waited for through work of more
+    than a millisecond are those of that work."""
+    _check("genz_disc" if d < 4 else "gauss", "fp64", d, N, 3001)
+    params = _params("gauss", d)
+    v = Vegas(d, N, "gauss", params, "fp64", seed=3)
+    r = np.random.default_rng(N)
+    E = np.zeros((d, N + 1))
+    E[:, 1:] = np.cumsum(r.uniform(0.5, 1.5, (d, N)), axis=1)
+    E /= E[:, -1:]
+    E[:, -1] = 1.0
+    v.set_edges(E)
+    assert np.array_equal(v.edges(), E)
+    v.iterate(30_000_000, hist=False)
+    first = v.result()
+    S1, S2, _ = v.last_iteration()
+    assert first["n_iter"] == 1 and abs(first["integral"] - S1 / 3e7) <= 1e-13 * abs(first["integral"])
+    v.iterate(1000, hist=False)
+    assert v.result()["n_iter"] == 2
