@@ -406,8 +406,8 @@ vegas_status vegas_batch_results(vegas_batch* batch, vegas_result_t* host_out,
 /* Schedule chosen at plan time.  The plan groups problems by dimension
  * bucket (d <= 4, 8, 16, 32, 64), one launch of the persistent event kernel
  * per bucket, and tunes on the batch itself, timing with HIP events: first
- * the tile (events per work item, which also sets events per thread) over
- * 8192 ... 131072, then each bucket's launch shape, threads per block
+ * the tile (most events of a work item; the last items of a bucket are
+ * smaller) over 8192 ... 131072, then each bucket's launch shape, threads per block
  * {1024, 512, 256} x histogram replicas {1, 2, 4, 8, 16} (those whose LDS
  * fits), each bucket keeping its fastest.  A bucket's time is that of its
  * launches in one run: n_adapt with histograms and n_iter - n_adapt without.

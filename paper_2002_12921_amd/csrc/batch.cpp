@@ -25,6 +25,7 @@ constexpr int kBatchMaxIter = 1024;
 constexpr int kMaxProblems = 65535;
 const uint64_t kTileCandidates[] = {1u << 13, 1u << 14, 1u << 15, 1u << 16, 1u << 17};
 constexpr uint64_t kTileMin = 1u << 13;
+constexpr uint64_t kTileStep = 1u << 12;  // items are whole groups of kGroup events per thread, at any block size
 constexpr int kTuneWarmRuns = 3;  // untimed schedule timings before the tuning's own
 
 size_t a256(size_t x) { return (x + 255) & ~size_t(255); }
@@ -123,6 +124,7 @@ struct vegas_batch {
     int blocks = 0;  // the largest bucket launch (reported by vegas_batch_schedule)
     uint64_t tile = 0;
     int n_items = 0;
+    int groups = 0;  // column groups of all problems (S1 and S2; each dimension)
     double tuned_ms = 0.0;
     hipStream_t priv = nullptr;
     hipGraph_t graph = nullptr;
@@ -150,10 +152,27 @@ struct vegas_batch {
 
 namespace {
 
-// Work items for tile size T, in decreasing cost (dimension), then problem,
-// then event order; each problem's items are contiguous, and so are its rows.
+// What an event costs relative to the other dimensions of its bucket: a Philox
+// call per four dimensions, and each dimension's map and term.
+uint64_t event_cost(int d) { return 6 * uint64_t((d + 3) / 4) + uint64_t(d); }
+
+// Work items, in decreasing cost (dimension), then problem, then event order;
+// each problem's items are contiguous, and so are its rows. An item is at most
+// T events, and no more than half of what is left of its bucket per block of the
+// launch, so that the last ones are small (kTileMin) and the blocks end
+// together. With T = 65536 events throughout (the best), the d <= 8 launch of
+// the 256-problem batch took 362 us (1456 items on 512 blocks), now 309; the
+// d <= 4 one 259 and 245, d <= 16 1303 and 1279; a whole item per block of what
+// is left instead of half of one 330, 242 and 1275.
 void build_items(vegas_batch* b, uint64_t T, std::vector<BatchItem>& items)
 {
+    auto bucket_of = [&](int d) -> size_t {
+        size_t q = 0;
+        while (b->buckets[q].dmax != dmax_of(d)) ++q;
+        return q;
+    };
+    std::vector<double> left(b->buckets.size(), 0.0);  // cost of the bucket's events not yet in items
+    for (int p = 0; p < b->n; ++p) left[bucket_of(b->dims[p])] += double(b->events[p]) * double(event_cost(b->dims[p]));
     std::vector<int> order(b->n);
     for (int p = 0; p < b->n; ++p) order[p] = p;
     std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return b->dims[x] > b->dims[y]; });
@@ -164,14 +183,19 @@ void build_items(vegas_batch* b, uint64_t T, std::vector<BatchItem>& items)
         pr.first_item = int(items.size());
         pr.row0 = row;
         const uint64_t M = uint64_t(b->events[p]);
-        for (uint64_t e0 = 0; e0 < M; e0 += T) {
+        const size_t q = bucket_of(b->dims[p]);
+        const double cost = double(event_cost(b->dims[p]));
+        for (uint64_t e0 = 0; e0 < M;) {
+            const uint64_t share = uint64_t(left[q] / (2.0 * cost * b->buckets[q].blocks)) / kTileStep * kTileStep;
             BatchItem it{};
             it.prob = p;
             it.e0 = e0;
-            it.n = std::min<uint64_t>(T, M - e0);
+            it.n = std::min(std::max(std::min(share, T), kTileMin), M - e0);
             it.row_off = row;
             row += uint64_t(pr.pstride);
             items.push_back(it);
+            e0 += it.n;
+            left[q] -= double(it.n) * cost;
         }
         pr.n_items = int(items.size()) - pr.first_item;
     }
@@ -226,7 +250,7 @@ vegas_status enqueue_iteration(vegas_batch* b, int k, hipStream_t s, const hipEv
         if (ev) VEGAS_HIP(hipEventRecord(ev[2 * q + 1], s));
     }
     const int flags = adapt ? (MERGE_REFINE | MERGE_NO_COMBINE) : MERGE_NO_HIST;
-    VEGAS_HIP(launch_batch_finish(a, b->dmax, b->kind, k, flags, s));
+    VEGAS_HIP(launch_batch_finish(a, b->dmax, b->groups, b->kind, k, flags, s));
     return VEGAS_OK;
 }
 
@@ -435,6 +459,7 @@ vegas_status vegas_batch_plan(vegas_batch** out, const vegas_desc* descs, const 
     for (int p = 0; p < n; ++p) {
         maxd = std::max(maxd, descs[p].dim);
         b->dims.push_back(descs[p].dim);
+        b->groups += 1 + descs[p].dim;
         b->bins.push_back(descs[p].n_bins);
         b->events.push_back(n_events[p]);
     }
@@ -588,6 +613,7 @@ vegas_status vegas_batch_plan(vegas_batch** out, const vegas_desc* descs, const 
             for (int pass = 0; pass < 2; ++pass)
                 for (size_t c = 0; c < shapes[q].size(); ++c) {
                     apply_shape(bk, shapes[q][c]);
+                    if ((st = upload_schedule(b, tile)) != VEGAS_OK) return bail(st);  // (items go by its blocks)
                     if ((st = time_schedule(b, tm, per)) != VEGAS_OK) return bail(st);
                     best_s[c] = std::min(best_s[c], per[q]);
                 }

@@ -339,15 +339,16 @@ __device__ static inline void refine_any(const MergeArgs& a, int i, const double
     refine_dim(a, i, h, Eo);
 }
 
-// One column group of a batch problem's reduction, by a block of kMergeThreads
+// One column group of a batch problem's reduction, by a block of T threads
 // (group 0: S1, S2; group 1+i: the histogram of dimension i): the partial rows
 // are summed in a fixed order, and the group records the statistics or refines
-// its dimension.  Histogram groups: wave w adds rows w, w + 16, ... (lane =
+// its dimension.  Histogram groups: wave w adds rows w, w + T / 64, ... (lane =
 // column, so each load instruction reads consecutive columns of one row), 32
 // loads in flight, with two-sums.  Group 0 spreads its rows over all lanes and
-// folds each wave with a butterfly.  After one barrier wave 0 adds the 16 wave
+// folds each wave with a butterfly.  After one barrier wave 0 adds the wave
 // partials in order.  For N <= 64 wave 0 then refines with the column values
 // still in its registers.
+template <int T>
 __device__ static void merge_group(const MergeArgs& a, const int g)
 {
     const int ncol = g == 0 ? 2 : a.N;
@@ -357,7 +358,7 @@ __device__ static void merge_group(const MergeArgs& a, const int g)
         for (int k = threadIdx.x; k < ncol; k += blockDim.x) a.last[off + k] = 0.0;
         return;
     }
-    constexpr int kWaves = kMergeThreads / 64;
+    constexpr int kWaves = T / 64;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     __shared__ double ws_s[kWaves][kMaxBins + 1], ws_c[kWaves][kMaxBins + 1];
     __shared__ double fin[kMaxBins + 1], Eo[kMaxBins + 1];
@@ -379,7 +380,7 @@ __device__ static void merge_group(const MergeArgs& a, const int g)
         // then an exact two-sum butterfly over the pairs of the wave
         const int col = lane & 1;
         double s = 0.0, c = 0.0;
-        for (int r = int(threadIdx.x) >> 1; r < a.rows; r += kMergeThreads / 2)
+        for (int r = int(threadIdx.x) >> 1; r < a.rows; r += T / 2)
             twosum_add(s, c, a.partials[size_t(r) * a.rstride + col]);
 #pragma unroll
         for (int o = 2; o < 64; o <<= 1) {

@@ -110,7 +110,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(BatchMin
     for (;;) {
         if (threadIdx.x == 0) s_item = a.item_lo + int(atomicAdd(a.queue, 1u));
         __syncthreads();
-        const int item = s_item;
+        const int item = __builtin_amdgcn_readfirstlane(s_item);
         if (item >= a.item_hi) break;  // every block leaves once the queue is empty
         const BatchItem it = a.items[item];
         const BatchProblem& pr = a.probs[it.prob];
@@ -172,7 +172,8 @@ const void* VEGAS_PART_NAME(VEGAS_BATCH_PREC, VEGAS_BATCH_KIND)(int dmax, bool h
 // Per problem and column group: reduce the problem's item rows, record the
 // iteration, refine (adaptation iterations).  Also resets the work queue for
 // the next event launch on the stream.
-__global__ __launch_bounds__(kMergeThreads) void k_batch_finish(BatchArgs a, int kind, int rec_idx, int flags)
+template <int T>
+__global__ __launch_bounds__(T) void k_batch_finish(BatchArgs a, int kind, int rec_idx, int flags)
 {
     const int g = blockIdx.x, p = blockIdx.y;
     if (p == 0 && g == 0 && threadIdx.x < kMaxBuckets) a.queue[threadIdx.x] = 0u;
@@ -199,7 +200,7 @@ __global__ __launch_bounds__(kMergeThreads) void k_batch_finish(BatchArgs a, int
     m.kind = kind;
     m.flags = MERGE_BEGIN | MERGE_END | flags;
     m.rec_idx = rec_idx;
-    merge_group(m, g);
+    merge_group<T>(m, g);
 }
 
 // Restart every problem: uniform grid and tables, no recorded iterations.
@@ -239,15 +240,23 @@ hipError_t launch_batch_combine(const BatchArgs& a, int n_rec, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_batch_finish(const BatchArgs& a, int dmax, int kind, int rec_idx, int flags, hipStream_t s)
+// groups: column groups over all problems. Where they fit the chip at once as
+// blocks of 1024 threads (two on a CU, by their 67 KiB of LDS), those finish
+// first, a wave's chain of rows being a quarter as long. With more of them,
+// blocks of 256 threads, of which a CU holds eight: the 256-problem batch
+// (2600 groups, 24 MB of rows) took 51 us with the one and 19 with the other.
+hipError_t launch_batch_finish(const BatchArgs& a, int dmax, int groups, int kind, int rec_idx, int flags,
+                               hipStream_t s)
 {
-    hipLaunchKernelGGL(k_batch_finish, dim3(dmax + 1, a.n_probs), dim3(kMergeThreads), 0, s, a, kind, rec_idx, flags);
+    const bool wide = groups <= 512;
+    hipLaunchKernelGGL(wide ? k_batch_finish<kMergeThreads> : k_batch_finish<256>, dim3(dmax + 1, a.n_probs),
+                       dim3(wide ? kMergeThreads : 256), 0, s, a, kind, rec_idx, flags);
     return hipGetLastError();
 }
 
 hipError_t launch_batch_reset(const BatchArgs& a, int dmax, int n_rec, int kind, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_batch_reset, dim3(dmax + 1, a.n_probs), dim3(kMergeThreads), 0, s, a, n_rec, kind);
+    hipLaunchKernelGGL(k_batch_reset, dim3(dmax + 1, a.n_probs), dim3(256), 0, s, a, n_rec, kind);
     return hipGetLastError();
 }
 

@@ -347,7 +347,7 @@ int sample_max_blocks_per_cu(int prec, int kind, int d, int N, int threads, int 
 hipError_t launch_batch_sample(int prec, int kind, int dmax, size_t lds, const BatchArgs& a, int blocks,
                                int threads, bool hist, hipStream_t s);
 int batch_max_blocks_per_cu(int prec, int kind, int dmax, size_t lds, int threads);
-hipError_t launch_batch_finish(const BatchArgs& a, int dmax, int kind, int rec_idx, int flags, hipStream_t s);
+hipError_t launch_batch_finish(const BatchArgs& a, int dmax, int groups, int kind, int rec_idx, int flags, hipStream_t s);
 hipError_t launch_batch_reset(const BatchArgs& a, int dmax, int n_rec, int kind, hipStream_t s);
 hipError_t launch_batch_combine(const BatchArgs& a, int n_rec, hipStream_t s);
 #endif
