@@ -434,6 +434,10 @@ vegas_status init_ctx(vegas_ctx** out, const vegas_desc* desc, const char* sourc
     static const double kRepFactorHigh[5] = {0.05, 0.1, 0.2, 0.45, 1.0};
     double best = -1.0;
     int per_cu = 1;
+    // Blocks of 256 threads count 0.85: at equal waves they leave four histograms
+    // to add to the slots where one of 1024 leaves one (the d = 4 Gaussian, FP64,
+    // in 7 of them per CU took 33.3 us per 1e7 events and 4.9 per 1e5, in 3 of 512
+    // threads 31.2 and 3.8).
     // 768 comes after 512, so it is taken only where it holds strictly more
     // waves (two blocks per CU where the LDS admits two and the registers
     // allow 6 or 7 waves per SIMD: the FP64 kernels up to d = 8)
@@ -453,7 +457,7 @@ vegas_status init_ctx(vegas_ctx** out, const vegas_desc* desc, const char* sourc
             const double* kRepFactor = c->d > 8                                                       ? kRepFactorHigh
                                        : !source && sample_in_sets(c->prec, c->kind, c->d, c->N, 1 << l2) ? kRepFactorSets
                                                                                                       : kRepFactorLow;
-            const double score = double(bpc * th / 64) * kRepFactor[l2] * (th == 256 ? 0.92 : 1.0);
+            const double score = double(bpc * th / 64) * kRepFactor[l2] * (th == 256 ? 0.85 : 1.0);
             if (score > best + 1e-9) {
                 best = score;
                 per_cu = bpc;

@@ -116,7 +116,38 @@ struct TabLog2 {
     static constexpr int value = sizeof(typename TabEntry<P, KIND>::type) == 16 ? 4 : 3;
 };
 
-__device__ __forceinline__ double exp_unit(double z) { return exp(z); }  // e^z
+// 2^(e + s k), k = kh + kl, magic = 1.5 2^52 + e: n = round(s k) is read off the
+// sum with magic (its low word is e + n), the rest f = s k - n in [-1/2, 1/2] is
+// formed with one rounding, and 2^f is a polynomial of degree 11 (minimax for
+// the relative error with the constant 1 and the linear coefficient RN(ln 2)
+// held: 9e-18). s is cut at smax, |k| smax = 4000, where the result is 0 or
+// infinite for every e of a finite C. Against exp(s kexp) times C: 17
+// instructions for 24 (the loop is bound by their issue), and no rounding of the
+// product s kexp, which at |s kexp| = 30 costs 15 units in the last place. Per
+// 1e7 events, N = 50, without histograms: the d = 8 Gaussian 45.1 -> 43.4 us,
+// d = 4 28.9 -> 27.0, the bimodal integrand (two of them) d = 8 55.8 -> 52.2.
+// held: the coefficients of f^10 to f^6, see EvalConsts.
+__device__ __forceinline__ double exp2_scaled(double s, double kh, double kl, double smax, double magic,
+                                              const double (&held)[5])
+{
+#pragma clang fp contract(off)
+    s = fmin(s, smax);
+    const double t = fma(s, kh, magic), n = t - magic;
+    const double f = fma(s, kl, fma(s, kh, -n));
+    double p = 0x1.e8112113876cbp-32;
+    p = fma(p, f, held[0]);
+    p = fma(p, f, held[1]);
+    p = fma(p, f, held[2]);
+    p = fma(p, f, held[3]);
+    p = fma(p, f, held[4]);
+    p = fma(p, f, 0x1.5d87fe78b3b99p-10);
+    p = fma(p, f, 0x1.3b2ab6fba110cp-7);
+    p = fma(p, f, 0x1.c6b08d704a0d4p-5);
+    p = fma(p, f, 0x1.ebfbdff82c59cp-3);
+    p = fma(p, f, 0x1.62e42fefa39efp-1);
+    p = fma(p, f, 1.0);
+    return ldexp(p, __double2loint(t));
+}
 __device__ __forceinline__ float exp2_unit(float z) { return __builtin_amdgcn_exp2f(z); }
 
 // The word k stands for y = (k + 1/2)/2^32, so yN = (kN + N/2) / 2^32.  With
@@ -170,7 +201,17 @@ struct EvalConsts {
     real p1[DMAX], p2[DMAX];
     double c64[DMAX];   // FP32 path, DISC: c_i / S (exponent summed in FP64, d > 8)
     float c32[DMAX];    // FP32 path, DISC: RN32(c_i / S) (exponent summed in FP32, d <= 8)
-    real kexp, dscale;  // dscale: FP32 path, 1/S = 2^-(ws + 32)
+    // FP64 path: the exponential of GAUSS, BIMODAL and DISC (DevConst), and the
+    // width product's start: the constant's mantissa (PEAK: 1) times 2^128 per
+    // group of four dimensions (beyond kWhole, where that overflows, 2^128, and
+    // the groups after the first multiply by it)
+    static constexpr bool kExp = P::is64 && KIND != GENZ_PEAK, kWhole = DMAX <= 24;
+    double k2h, k2l, smax, magic, w0;
+    // coefficients of exp2_scaled, in scalar registers where those are free
+    // (GAUSS): the compiler holds all in vector registers, and the d = 18
+    // kernel (N = 100) spilled 28 instead of 24 (136 against 131 us)
+    double held[5];
+    real dscale;        // FP32 path, 1/S = 2^-(ws + 32)
     double k2;          // FP32 path: log2(e)/(a S)^2 (GAUSS, BIMODAL), log2(e) (DISC)
     BinConsts bc;
     // LDS address of each dimension's table, as a scalar the compiler cannot
@@ -185,6 +226,13 @@ struct EvalConsts {
     // inside
     uint32_t kv;
     bool never;
+
+    // For records of w and f: both without C.
+    __device__ __forceinline__ void leave_out_constant(int d)
+    {
+        w0 = ldexp(1.0, kWhole ? 128 * ((d + 3) / 4) : 128);
+        magic = 0x1.8p52;
+    }
 
     // thr_g: the d thresholds T_i of the discontinuous integrand in
     // P = b 2^32 + lo (disc_threshold; other kinds: unused, may be null).
@@ -221,7 +269,17 @@ struct EvalConsts {
                 }
             }
         }
-        kexp = P::is64 ? real(c->kexp64) : real(0);
+        constexpr double coef[5] = {0x1.e61229bbb383ap-28, 0x1.b5260c8388969p-24, 0x1.62bfcd861ec29p-20, 0x1.ffcbfbf914474p-17, 0x1.4309130c28fc2p-13};
+#pragma unroll
+        for (int k = 0; k < 5; ++k) {
+            held[k] = coef[k];
+            if constexpr (kExp && KIND == GAUSS) asm("" : "+s"(held[k]));
+        }
+        k2h = c->k2h;
+        k2l = c->k2l;
+        smax = c->smax;
+        magic = c->magic;
+        w0 = ldexp(kExp ? c->mant : 1.0, kWhole ? 128 * ((d + 3) / 4) : 128);
         k2 = (P::is64 || KIND == GENZ_DISC) ? c->kexp2_64 : c->kexp2_64 * ds2;
         dscale = real(ds);
         const uint32_t N = uint32_t(c->n_bins);
@@ -252,7 +310,8 @@ struct EvalConsts {
 // Computes, for the event's d uniforms, the bins, the offsets u_i = x_i - c_i
 // from the integrand's centres, the width product wp and the integrand's
 // significand F; the event value is v = ldexp(F * wp, ew + fe) * C
-// (FP64: ew = fe = 0).  EXACT: d == DMAX, so no per-dimension guards are needed.
+// (FP64: ew = fe = 0, and C is in F and wp where the integrand has an
+// exponential).  EXACT: d == DMAX, so no per-dimension guards are needed.
 template <class P, int KIND, int DMAX, bool EXACT = false>
 struct EventEval {
     using real = typename P::real;
@@ -283,7 +342,7 @@ struct EventEval {
         // method's tolerance
         constexpr bool kQ32 = !P::is64 && DMAX <= 8;
         using q_t = typename pick_type<kQ32, float, double>::type;
-        real w = P::is64 ? real(0x1p128) : real(1);
+        real w = P::is64 ? real(c.w0) : real(1);
         real sa = real(0), sb = real(0);  // FP64 path: GAUSS/BIMODAL sums of squares; DISC: sum c u
         q_t qa = q_t(0), qb = q_t(0);     // FP32 path: the same sums
         real den = real(1);               // PEAK: product of denominators
@@ -297,7 +356,7 @@ struct EventEval {
         for (int g = 0; g < (DMAX + 3) / 4; ++g) {
             if (4 * g < d) {
                 const U4 k = philox4x32_10(elo, ehi, t, ctr3 + uint32_t(g), key0, key1);
-                if constexpr (P::is64)
+                if constexpr (P::is64 && !EvalConsts<P, KIND, DMAX>::kWhole)
                     if (g > 0) w *= real(0x1p128);
                 // the group's four bins and table entries first, so that its
                 // LDS reads are in flight together before any is used
@@ -402,11 +461,11 @@ struct EventEval {
         if constexpr (P::is64) {
             fe = 0;
             if constexpr (KIND == GAUSS)
-                F = exp_unit(-sa * c.kexp);
+                F = exp2_scaled(sa, c.k2h, c.k2l, c.smax, c.magic, c.held);
             else if constexpr (KIND == BIMODAL)
-                F = exp_unit(-sa * c.kexp) + exp_unit(-sb * c.kexp);
+                F = exp2_scaled(sa, c.k2h, c.k2l, c.smax, c.magic, c.held) + exp2_scaled(sb, c.k2h, c.k2l, c.smax, c.magic, c.held);
             else if constexpr (KIND == GENZ_DISC)
-                F = inside ? exp_unit(sa) : 0.0;  // sa = sum c (x - a)
+                F = inside ? exp2_scaled(sa, c.k2h, c.k2l, c.smax, c.magic, c.held) : 0.0;  // sa = sum c (x - a)
             else
                 F = real(1) / den;
         } else {
@@ -441,7 +500,9 @@ struct EventEval {
     __device__ __forceinline__ double value(const EvalConsts<P, KIND, DMAX>& c) const
     {
 #pragma clang fp contract(off)
-        if constexpr (P::is64)
+        if constexpr (EvalConsts<P, KIND, DMAX>::kExp)
+            return F * wp;  // (C is in both)
+        else if constexpr (P::is64)
             return F * wp * c.C;
         else
             return ldexp(double(F * wp), ew + fe) * c.C;

@@ -60,7 +60,10 @@ __device__ __forceinline__ void write_table_entry(int i, int b, double lo, doubl
     const double h = (N & 1) ? 0x1p-33 : 0.0;     // h / 2^32
     const double w = hi - lo;
     const double w32 = w * 0x1p-32;
-    tab64[size_t(i) * N + b] = make_double2((N & 1) ? fma(0.5, w32, lo - cA) : lo - cA, w32);
+    // (rounded once: the difference's error joins h W first)
+    const double diff = lo - cA, back = diff - lo;
+    const double rest = (lo - (diff - back)) - (cA + back);
+    tab64[size_t(i) * N + b] = make_double2((N & 1) ? diff + fma(0.5, w32, rest) : diff, w32);
     const double W = double(float(w));
     const double g = lo + h * W;
     const float Ws = float(W * sw);

@@ -163,9 +163,9 @@ __device__ static void prepare_consts(int prec, int kind, int d, int N, const do
                                       DevConst* __restrict__ c)
 {
     __shared__ double factor[kMaxDim];
-    const double pi = 3.14159265358979323846;
     const double log2e = 1.4426950408889634074;
     const int i = threadIdx.x;
+    bool not_a_number = false;
     if (i < kMaxDim) {
         double p1 = 0.0, p2 = 0.0, cA = 0.0, cB = 0.0, f = 1.0;
         float p1f = 0.0f;
@@ -195,24 +195,35 @@ __device__ static void prepare_consts(int prec, int kind, int d, int N, const do
         c->cA64[i] = cA;
         c->cB64[i] = cB;
         c->p1_32[i] = p1f;
-        c->p2_32[i] = 0.0f;
         factor[i] = f;
+        not_a_number = p1 != p1 || p2 != p2;
     }
-    __syncthreads();
+    // (an event's minimum with smax would hide it)
+    const bool bad = __syncthreads_or(not_a_number);
     if (threadIdx.x != 0) return;
     c->n_bins = N;
     c->pad1 = 0;
     c->dscale32 = width_scale32(N);
     const int ws = int(rint(log2(double(N))));
-    double nd = 1.0;
-    for (int k = 0; k < d; ++k) nd = nd * double(N);
-    const double Cw = ldexp(nd, prec == FP64 ? -32 * ((4 - d % 4) % 4) : -ws * d);
-    double kexp64 = 0.0, kexp2_64 = 0.0, inv_a = 0.0, Cf = 1.0;
+    // the constants every event is multiplied by, as sums of two (an error here
+    // does not average out): N^d and the normalisation
+    const auto times = [](double& hi, double& lo, double f) {
+        const double p = hi * f;
+        lo = fma(lo, f, fma(hi, f, -p));
+        hi = p;
+    };
+    double nd = 1.0, nd_lo = 0.0, Cf = 1.0, Cf_lo = 0.0;
+    for (int k = 0; k < d; ++k) times(nd, nd_lo, double(N));
+    const int shift = prec == FP64 ? -32 * ((4 - d % 4) % 4) : -ws * d;
+    const double Cw = ldexp(nd, shift), Cw_lo = ldexp(nd_lo, shift);
+    double kexp64 = 0.0, kexp2_64 = 0.0, inv_a = 0.0;
     float kexp32 = 0.0f, ka32 = 0.0f;
     if (kind == GAUSS || kind == BIMODAL) {
-        const double a = q[0];
-        Cf = pow(a * sqrt(pi), double(-d));
+        const double a = q[0], sqrt_pi = 0x1.c5bf891b4ef6bp+0, sqrt_pi_lo = -0x1.618f13eb7ca89p-54;
+        const double x = a * sqrt_pi, r = fma(a, sqrt_pi, -x) + a * sqrt_pi_lo;
+        Cf = pow(x, double(-d));
         if (kind == BIMODAL) Cf = 0.5 * Cf;
+        Cf_lo = Cf * (double(-d) * (r / x));
         kexp64 = 1.0 / (a * a);
         kexp2_64 = log2e / (a * a);
         inv_a = 1.0 / a;
@@ -222,8 +233,12 @@ __device__ static void prepare_consts(int prec, int kind, int d, int N, const do
         if (kind == GENZ_DISC) kexp2_64 = log2e;
         // (a user integrand carries its own normalisation: C = N^d)
         if (kind != USER)
-            for (int k = 0; k < d; ++k) Cf = Cf * factor[k];
+            for (int k = 0; k < d; ++k) times(Cf, Cf_lo, factor[k]);
     }
+    double C = Cf * Cw;
+    const double rest = fma(Cf, Cw, -C) + (Cf * Cw_lo + Cf_lo * Cw);
+    if (fabs(rest) < fabs(C)) C += rest;  // (not beyond the range of the parts)
+    if (fabs(Cf_lo) < fabs(Cf)) Cf += Cf_lo;
     c->Cw = Cw;
     c->kexp64 = kexp64;
     c->kexp2_64 = kexp2_64;
@@ -232,7 +247,26 @@ __device__ static void prepare_consts(int prec, int kind, int d, int N, const do
     c->ka32 = ka32;
     c->pad0 = 0.0f;
     c->Cf = Cf;
-    c->C = Cf * Cw;
+    c->C = C;
+    // the exponential's factor in two parts: log2(e) as two, times 1/a^2 as two
+    // (a^2 = p + r exactly)
+    const double log2e_lo = 0x1.777d0ffda0d24p-56;
+    double kh = log2e, kl = log2e_lo;
+    if (kind == GAUSS || kind == BIMODAL) {
+        const double a = q[0], p = a * a, r = fma(a, a, -p);
+        const double i1 = -kexp64, i2 = i1 * (fma(-kexp64, p, 1.0) - kexp64 * r);
+        kh = i1 * log2e;
+        kl = fma(i1, log2e, -kh) + fma(i1, log2e_lo, i2 * log2e);
+        if (!(fabs(kh) < 1e300)) kh = kh != kh ? kh : -1e300;
+        if (!(fabs(kl) < fabs(kh))) kl = 0.0;  // (beyond the range of the parts)
+    }
+    int e = 0;
+    const double m = frexp(C, &e);
+    c->k2h = kh;
+    c->k2l = kl;
+    c->smax = 4000.0 / fabs(kh);
+    c->mant = bad ? __builtin_nan("") : m;
+    c->magic = 0x1.8p52 + double(e);
 }
 
 __global__ void k_prepare(int prec, int kind, int d, int N, const double* __restrict__ q,

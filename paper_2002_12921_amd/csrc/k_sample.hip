@@ -168,6 +168,7 @@ __global__ __launch_bounds__(kBlock) void k_dump(DumpArgs a)
     __syncthreads();
     EvalConsts<P, KIND, DMAX> cst;
     cst.load(a.cst, a.thr, a.d, a.N, ltab);
+    cst.leave_out_constant(a.d);
     const uint64_t stride = uint64_t(gridDim.x) * kBlock;
     for (uint64_t k = uint64_t(blockIdx.x) * kBlock + threadIdx.x; k < a.n; k += stride) {
         EventEval<P, KIND, DMAX> ev;

@@ -41,6 +41,9 @@ enum Prec { FP64 = 0, FP32 = 1 };
 //        FP64: times 2^(32 pad), pad the dimensions that the last group of four lacks),
 // and the event value v = f w = 2^(ew + fe) (F * wp) * C with C = Cf * Cw,
 // Cf the integrand normalisation and Cw = N^d (FP32: N^d 2^(-ws d); FP64: N^d 2^(-32 pad)).
+// The FP64 kernels of the integrands with an exponential take C in two parts:
+// its mantissa starts the width product, its exponent is added to the
+// exponential's (v = F wp, no product with C).
 struct DevConst {
     double C;        // Cf * Cw
     double Cf;       // f = 2^fe F Cf
@@ -57,7 +60,9 @@ struct DevConst {
     double p1_64[kMaxDim];  // GAUSS mu | BIMODAL muA | DISC c | PEAK c^2
     double p2_64[kMaxDim];  //          | BIMODAL muB - muA | DISC a | PEAK a
     float p1_32[kMaxDim];   // PEAK c^2
-    float p2_32[kMaxDim];   // (unused)
+    double k2h, k2l;        // GAUSS, BIMODAL: -log2(e)/a^2, DISC: log2(e); as a sum of two
+    double smax;            // |k2| smax = 4000
+    double mant, magic;     // C = mant 2^e; 1.5 2^52 + e
     double cA64[kMaxDim];   // table centres: GAUSS mu | BIMODAL muA | DISC, PEAK a
     double cB64[kMaxDim];   // BIMODAL muB
 };

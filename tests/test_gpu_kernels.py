@@ -24,8 +24,8 @@ def _params(kind, d):
     return list(r.uniform(0.7, 1.4, d)) + list(r.uniform(0.3, 0.7, d))
 
 
-def _check(kind, prec, d, N, M, replicas=(0,)):
-    params = _params(kind, d)
+def _check(kind, prec, d, N, M, replicas=(0,), params=None):
+    params = params or _params(kind, d)
     pr = oracle.Problem(d, N, KINDS[kind], params, seed=11)
     # a grid away from uniform, its own in every dimension
     r = np.random.default_rng(d)
@@ -34,6 +34,12 @@ def _check(kind, prec, d, N, M, replicas=(0,)):
     E /= E[:, -1:]
     E[:, -1] = 1.0
     o1, o2, Ho = oracle.accumulate(pr, E, 0, M)
+    if kind == "genz_disc":
+        # the oracle's normalisation has e^c - e^(c a), of which c (1 - a) remain:
+        # a relative 2^-53 / c, 1e-10 at c = 1e-6
+        c, a = np.array(params[:d]), np.array(params[d:])
+        r = np.prod((np.exp(c) - np.exp(c * a)) / (np.expm1(c * (1.0 - a)) * np.exp(c * a)))
+        o1, o2, Ho = o1 * r, o2 * r * r, Ho * (r * r)
     tol = 1e-12 if prec == "fp64" else 1e-6 * max(1.0, d / 8)
     sums = set()
     for rep in replicas:
@@ -154,3 +160,29 @@ def test_edges_there_and_back(d, N):
     assert first["n_iter"] == 1 and abs(first["integral"] - S1 / 3e7) <= 1e-13 * abs(first["integral"])
     v.iterate(1000, hist=False)
     assert v.result()["n_iter"] == 2
+
+
+@pytest.mark.parametrize("kind,d,params", [
+    ("gauss", 1, [1e-150, 0.5]), ("gauss", 1, [50.0, 0.5]), ("gauss", 4, [0.02] + [0.4] * 4), ("gauss", 13, [3.0] + [0.9] * 13),
+    ("bimodal", 2, [0.02, 0.3, 0.3, 0.7, 0.7]), ("bimodal", 28, [0.5] + [0.2] * 28 + [0.9] * 28),
+    ("genz_disc", 2, [200.0, 150.0, 0.1, 0.2]), ("genz_disc", 5, [1e-6] * 5 + [0.05] * 5)])
+def test_exponential_range(kind, d, params):
+    """Exponents from 0 past where the exponential is cut (2^-4000), normalisations
+    from 1e-9 to 1e150, and the width product's two forms (d up to 24 and beyond)."""
+    _check(kind, "fp64", d, 12, 6007, params=params)
+
+
+@pytest.mark.parametrize("kind", ["gauss", "bimodal", "genz_disc"])
+def test_nan_parameter_is_not_hidden(kind):
+    """A parameter set on the device that is not a number gives results that are
+    not numbers, although the FP64 exponential's argument goes through a minimum."""
+    import torch
+    d = 3
+    q = _params(kind, d)
+    v = Vegas(d, 20, kind, q, "fp64")
+    for k in range(len(q)):
+        p = torch.tensor(q, dtype=torch.float64, device="cuda")
+        p[k] = float("nan")
+        v.set_params_device(p)
+        v.iterate(1000, refine=False, hist=False)
+        assert np.isnan(v.last_iteration()[0]), k
