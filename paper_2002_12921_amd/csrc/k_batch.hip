@@ -40,9 +40,10 @@ __device__ __forceinline__ void batch_item_events(const BatchArgs& a, const Batc
     const uint32_t key0 = pr.key0, key1 = pr.key1, ctr3 = pr.ctr3;
     double s1 = 0.0, c1 = 0.0, s2 = 0.0, c2 = 0.0, g1 = 0.0, g2 = 0.0;
     int ng = 0;
-    for (uint64_t k = threadIdx.x; k < it.n; k += blockDim.x) {
+    const uint64_t end = it.e0 + it.n;
+    for (uint64_t e = it.e0 + threadIdx.x; e < end; e += blockDim.x) {
         EventEval<P, KIND, DM, (DE > 0)> ev;
-        ev.run(cst, ltab, it.e0 + k, a.t, ctr3, key0, key1, d, N);
+        ev.run(cst, ltab, e, a.t, ctr3, key0, key1, d, N);
         double v, v2;
         {
             // rounded as written in every variant (with or without histograms)

@@ -101,9 +101,10 @@ __global__ __attribute__((amdgpu_flat_work_group_size(1, MaxThreads<P, KIND, DMA
     // event k = j * stride + threadIdx.x * gridDim.x + blockIdx.x in pass j:
     // the last, partial pass is spread over every block rather than a few
     const uint64_t stride = uint64_t(gridDim.x) * blockDim.x;
-    for (uint64_t k = uint64_t(threadIdx.x) * gridDim.x + blockIdx.x; k < a.n; k += stride) {
+    const uint64_t end = a.e0 + a.n;
+    for (uint64_t e = a.e0 + uint64_t(threadIdx.x) * gridDim.x + blockIdx.x; e < end; e += stride) {
         EventEval<P, KIND, DMAX, EXACT> ev;
-        ev.run(cst, ltab, a.e0 + k, a.t, a.ctr3, a.key0, a.key1, d, a.N);
+        ev.run(cst, ltab, e, a.t, a.ctr3, a.key0, a.key1, d, a.N);
         double v, v2;
         {
             // rounded as written in every variant (with or without histograms)
@@ -301,9 +302,10 @@ k_sample_grad(SampleArgs a, double* gpart)
 #pragma unroll
     for (int j = 0; j <= DMAX; ++j) g[j] = 0.0;
     const uint64_t stride = uint64_t(gridDim.x) * blockDim.x;
-    for (uint64_t k = uint64_t(threadIdx.x) * gridDim.x + blockIdx.x; k < a.n; k += stride) {
+    const uint64_t end = a.e0 + a.n;
+    for (uint64_t e = a.e0 + uint64_t(threadIdx.x) * gridDim.x + blockIdx.x; e < end; e += stride) {
         EventEval<P, GAUSS, DMAX, EXACT> ev;
-        ev.run(cst, ltab, a.e0 + k, a.t, a.ctr3, a.key0, a.key1, d, a.N);
+        ev.run(cst, ltab, e, a.t, a.ctr3, a.key0, a.key1, d, a.N);
         double v, v2;
         {
 #pragma clang fp contract(off)

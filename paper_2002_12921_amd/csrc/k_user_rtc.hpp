@@ -174,9 +174,10 @@ __device__ __forceinline__ void sample(const SampleArgs& a, const double* __rest
     double g1 = 0.0, g2 = 0.0;
     int ng = 0;
     const uint64_t stride = uint64_t(gridDim.x) * blockDim.x;
-    for (uint64_t k = uint64_t(threadIdx.x) * gridDim.x + blockIdx.x; k < a.n; k += stride) {
+    const uint64_t end = a.e0 + a.n;
+    for (uint64_t e = a.e0 + uint64_t(threadIdx.x) * gridDim.x + blockIdx.x; e < end; e += stride) {
         Event ev;
-        ev.run(mc, a.e0 + k, a.t, a.ctr3, a.key0, a.key1, ds);
+        ev.run(mc, e, a.t, a.ctr3, a.key0, a.key1, ds);
         const vegas_real f = vegas_integrand(ev.x, D, params);
         double v, v2;
         {
