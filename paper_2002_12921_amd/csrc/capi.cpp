@@ -410,27 +410,25 @@ vegas_status init_ctx(vegas_ctx** out, const vegas_desc* desc, const char* sourc
     }
     // Launch shape of the event kernel: block size and histogram replicas.
     // Score = resident waves per CU x a replica factor x a block-size factor.
-    // The factors come from the d = 8 workload on gfx950: fewer replicas leave
-    // more LDS bank conflicts in the histogram atomics (4 replicas ran 17 %
-    // slower than 16 at equal occupancy), and 256-thread blocks pay more
-    // per-block set-up and partial rows than they gain (7 x 256 threads with
-    // 4 replicas ran 11 % slower than 3 x 512 with 8 in FP64).  Ties keep the
-    // larger block and the more replicas.
+    // Fewer replicas leave more LDS bank conflicts in the histogram's atomics, and
+    // those share the LDS with the table reads. Up to d = 8 (only runtime-compiled
+    // integrands get here with 8 or 4 replicas), per 1e7 events of a d = 8
+    // Gaussian written as source, FP64, by blocks of 512 threads: N = 50, two with
+    // 16 replicas 70.8 us, three with 8 74.9, three with 4 81.6; N = 100, one with
+    // 16 72.1, two with 8 70.8, three with 4 77.7; N = 200, one with 8 79.9, two
+    // with 4 80.6. Ties keep the larger block and the more replicas.
     // Beyond d = 8 each event makes more histogram atomics per instruction and
-    // the replicas weigh more: at d = 16 (Genz, FP32-mixed) one block of 16
-    // replicas ran 14 % faster than three blocks of 4 and 3 % faster than two
-    // of 8, so the factors are steeper there: per 1e7 events, the FP32-mixed
-    // Gaussian took 88 us with one block of 16 and 114 us with two of 8
-    // (d = 16, N = 50), 110 us with one block of 8 and 130 us with two of 4
-    // (N = 100).
+    // the replicas weigh more: per 1e7 events, the FP32-mixed Gaussian took 88 us
+    // with one block of 16 and 114 us with two of 8 (d = 16, N = 50), 110 us with
+    // one block of 8 and 130 us with two of 4 (N = 100).
     // Where the kernel takes the dimensions in sets, 8 and 4 replicas have no
     // conflicts either, and up to d = 8 more resident waves win over them: per
     // 1e7 events, the d = 8 Gaussian with N = 200, FP32-mixed, took 46 us with 4
     // replicas in two blocks and 47 with 8 in one; with N = 160, FP64, 57 and 58
     // us; but d = 7, N = 255, FP64, 72 us with two (conflicting) replicas in two
     // blocks and 60 with 8 in one.
-    static const double kRepFactorLow[5] = {0.4, 0.55, 0.8, 0.93, 1.0};   // 1, 2, 4, 8, 16 replicas
-    static const double kRepFactorSets[5] = {0.4, 0.55, 0.95, 0.98, 1.0};
+    static const double kRepFactorLow[5] = {0.05, 0.12, 0.28, 0.6, 1.0};  // 1, 2, 4, 8, 16 replicas
+    static const double kRepFactorSets[5] = {0.05, 0.12, 0.95, 0.98, 1.0};
     static const double kRepFactorHigh[5] = {0.05, 0.1, 0.2, 0.45, 1.0};
     double best = -1.0;
     int per_cu = 1;
