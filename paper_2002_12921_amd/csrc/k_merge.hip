@@ -17,6 +17,9 @@
 // need.  (Behind a finished kernel even an empty one takes 4 us; alone, the d = 8
 // reduction with refinement takes 2.0 us, 3.2 with crossbar exchanges and
 // 1024-thread blocks; 3 iterations of 2000 events with a wait: 37 -> 31 us.)
+// It stays a kernel of its own: counting the event kernel's blocks to let the
+// last one reduce takes a release, an acquire and an atomic on one address in
+// every block, which alone made that kernel 4 us longer at 1e5 events, 7 at 1e6.
 #include <cstring>
 
 #include "grid_ops.hpp"
