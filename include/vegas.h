@@ -322,10 +322,11 @@ vegas_status vegas_get_iteration_index(const vegas_ctx* ctx, int64_t* t);
  * beyond FP64 rounding. */
 vegas_status vegas_set_launch(vegas_ctx* ctx, int32_t n_blocks);
 /* Histogram replicas per bin in the event kernel's LDS (1, 2, 4, 8 or 16;
- * lane l of a wave adds into replica l mod replicas, so with 16 every lane
- * has its own LDS bank pair); 0 restores the automatic choice (the most that
- * fit without losing a resident block).  Results do not depend on it beyond
- * FP64 rounding. */
+ * lane l of a wave adds into replica l mod replicas, so that with 16, and with 8
+ * and 4 where the kernel takes two or four dimensions at a time, the lanes an
+ * atomic serves together have an LDS bank pair each); 0 restores the automatic
+ * choice (a score of resident waves and replicas).  Results do not depend on it
+ * beyond FP64 rounding. */
 vegas_status vegas_set_hist_replicas(vegas_ctx* ctx, int32_t replicas);
 /* The automatic choice: blocks (compute units x resident blocks per unit),
  * resident blocks per compute unit, threads per block (1024, 768, 512 or

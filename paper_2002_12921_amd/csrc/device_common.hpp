@@ -116,24 +116,23 @@ struct TabLog2 {
     static constexpr int value = sizeof(typename TabEntry<P, KIND>::type) == 16 ? 4 : 3;
 };
 
-// 2^(e + s k), k = kh + kl, magic = 1.5 2^52 + e: n = round(s k) is read off the
-// sum with magic (its low word is e + n), the rest f = s k - n in [-1/2, 1/2] is
-// formed with one rounding, and 2^f is a polynomial of degree 11 (minimax for
-// the relative error with the constant 1 and the linear coefficient RN(ln 2)
-// held: 9e-18). s is cut at smax, |k| smax = 4000, where the result is 0 or
-// infinite for every e of a finite C. Against exp(s kexp) times C: 17
-// instructions for 24 (the loop is bound by their issue), and no rounding of the
-// product s kexp, which at |s kexp| = 30 costs 15 units in the last place. Per
-// 1e7 events, N = 50, without histograms: the d = 8 Gaussian 45.1 -> 43.4 us,
-// d = 4 28.9 -> 27.0, the bimodal integrand (two of them) d = 8 55.8 -> 52.2.
-// held: the coefficients of f^10 to f^6, see EvalConsts.
-__device__ __forceinline__ double exp2_scaled(double s, double kh, double kl, double smax, double magic,
-                                              const double (&held)[5])
+// e^x 2^e, magic = 1.5 2^52 + e: n = round(x log2 e) is read off the sum with magic
+// (its low word is e + n), the rest f = x log2 e - n in [-1/2, 1/2] is formed with
+// one rounding (log2 e as a sum of two), and 2^f is a polynomial of degree 11
+// (minimax for the relative error with the constant 1 and the linear coefficient
+// RN(ln 2) held: 9e-18). |x| log2 e is at most 4000 here, where the result is 0 or
+// infinite for every e of a finite C. Against exp(x) times C: 17 instructions
+// for 23 (the loop is bound by their issue). Per 1e7 events, N = 50, without
+// histograms: the d = 8 Gaussian 45.1 -> 43.4 us, d = 4 28.9 -> 27.0, the bimodal
+// integrand (two of them) d = 8 55.8 -> 52.2. held: the coefficients of f^10 to
+// f^6, see EvalConsts.
+constexpr double kExpCut = 2772.0;  // 4000 ln 2
+__device__ __forceinline__ double exp_scaled(double x, double magic, const double (&held)[5])
 {
 #pragma clang fp contract(off)
-    s = fmin(s, smax);
-    const double t = fma(s, kh, magic), n = t - magic;
-    const double f = fma(s, kl, fma(s, kh, -n));
+    const double log2e = 0x1.71547652b82fep+0, log2e_lo = 0x1.777d0ffda0d24p-56;
+    const double t = fma(x, log2e, magic), n = t - magic;
+    const double f = fma(x, log2e_lo, fma(x, log2e, -n));
     double p = 0x1.e8112113876cbp-32;
     p = fma(p, f, held[0]);
     p = fma(p, f, held[1]);
@@ -206,8 +205,8 @@ struct EvalConsts {
     // group of four dimensions (beyond kWhole, where that overflows, 2^128, and
     // the groups after the first multiply by it)
     static constexpr bool kExp = P::is64 && KIND != GENZ_PEAK, kWhole = DMAX <= 24;
-    double k2h, k2l, smax, magic, w0;
-    // coefficients of exp2_scaled, in scalar registers where those are free
+    double kexp, magic, w0;  // kexp: GAUSS, BIMODAL: -1/a^2
+    // coefficients of exp_scaled, in scalar registers where those are free
     // (GAUSS): the compiler holds all in vector registers, and the d = 18
     // kernel (N = 100) spilled 28 instead of 24 (136 against 131 us)
     double held[5];
@@ -275,9 +274,7 @@ struct EvalConsts {
             held[k] = coef[k];
             if constexpr (kExp && KIND == GAUSS) asm("" : "+s"(held[k]));
         }
-        k2h = c->k2h;
-        k2l = c->k2l;
-        smax = c->smax;
+        kexp = -c->kexp64;
         magic = c->magic;
         w0 = ldexp(kExp ? c->mant : 1.0, kWhole ? 128 * ((d + 3) / 4) : 128);
         k2 = (P::is64 || KIND == GENZ_DISC) ? c->kexp2_64 : c->kexp2_64 * ds2;
@@ -461,11 +458,12 @@ struct EventEval {
         if constexpr (P::is64) {
             fe = 0;
             if constexpr (KIND == GAUSS)
-                F = exp2_scaled(sa, c.k2h, c.k2l, c.smax, c.magic, c.held);
+                F = exp_scaled(fmax(sa * c.kexp, -kExpCut), c.magic, c.held);
             else if constexpr (KIND == BIMODAL)
-                F = exp2_scaled(sa, c.k2h, c.k2l, c.smax, c.magic, c.held) + exp2_scaled(sb, c.k2h, c.k2l, c.smax, c.magic, c.held);
+                F = exp_scaled(fmax(sa * c.kexp, -kExpCut), c.magic, c.held) +
+                    exp_scaled(fmax(sb * c.kexp, -kExpCut), c.magic, c.held);
             else if constexpr (KIND == GENZ_DISC)
-                F = inside ? exp2_scaled(sa, c.k2h, c.k2l, c.smax, c.magic, c.held) : 0.0;  // sa = sum c (x - a)
+                F = inside ? exp_scaled(fmin(sa, kExpCut), c.magic, c.held) : 0.0;  // sa = sum c (x - a)
             else
                 F = real(1) / den;
         } else {

@@ -201,7 +201,7 @@ __device__ static void prepare_consts(int prec, int kind, int d, int N, const do
         factor[i] = f;
         not_a_number = p1 != p1 || p2 != p2;
     }
-    // (an event's minimum with smax would hide it)
+    // (the exponential's cut would hide it)
     const bool bad = __syncthreads_or(not_a_number);
     if (threadIdx.x != 0) return;
     c->n_bins = N;
@@ -251,23 +251,8 @@ __device__ static void prepare_consts(int prec, int kind, int d, int N, const do
     c->pad0 = 0.0f;
     c->Cf = Cf;
     c->C = C;
-    // the exponential's factor in two parts: log2(e) as two, times 1/a^2 as two
-    // (a^2 = p + r exactly)
-    const double log2e_lo = 0x1.777d0ffda0d24p-56;
-    double kh = log2e, kl = log2e_lo;
-    if (kind == GAUSS || kind == BIMODAL) {
-        const double a = q[0], p = a * a, r = fma(a, a, -p);
-        const double i1 = -kexp64, i2 = i1 * (fma(-kexp64, p, 1.0) - kexp64 * r);
-        kh = i1 * log2e;
-        kl = fma(i1, log2e, -kh) + fma(i1, log2e_lo, i2 * log2e);
-        if (!(fabs(kh) < 1e300)) kh = kh != kh ? kh : -1e300;
-        if (!(fabs(kl) < fabs(kh))) kl = 0.0;  // (beyond the range of the parts)
-    }
     int e = 0;
     const double m = frexp(C, &e);
-    c->k2h = kh;
-    c->k2l = kl;
-    c->smax = 4000.0 / fabs(kh);
     c->mant = bad ? __builtin_nan("") : m;
     c->magic = 0x1.8p52 + double(e);
 }

@@ -60,8 +60,6 @@ struct DevConst {
     double p1_64[kMaxDim];  // GAUSS mu | BIMODAL muA | DISC c | PEAK c^2
     double p2_64[kMaxDim];  //          | BIMODAL muB - muA | DISC a | PEAK a
     float p1_32[kMaxDim];   // PEAK c^2
-    double k2h, k2l;        // GAUSS, BIMODAL: -log2(e)/a^2, DISC: log2(e); as a sum of two
-    double smax;            // |k2| smax = 4000
     double mant, magic;     // C = mant 2^e; 1.5 2^52 + e
     double cA64[kMaxDim];   // table centres: GAUSS mu | BIMODAL muA | DISC, PEAK a
     double cB64[kMaxDim];   // BIMODAL muB
