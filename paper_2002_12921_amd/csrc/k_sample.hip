@@ -24,7 +24,8 @@ constexpr int kHistNone = 0, kHistSets1 = 1, kHistSets2 = 2, kHistSets4 = 3;
 //     fit without spills, and the launch runs two 768-thread blocks per CU.  At
 //     8 waves (64 VGPRs, two 1024-thread blocks) the d = 8 Gaussian spilled 15
 //     registers and took 62.2-63.0 us per 1e7 events, at 7 (896-thread blocks)
-//     it still spilled 8 and took 70.0-70.8 us, at 6: 57.9-58.5 us.
+//     it still spilled 8 and took 70.0-70.8 us, at 6: 57.9-58.5 us (all with an
+//     earlier form of the loop; today's takes 51).
 //   FP32-mixed up to d = 8: 8, two 1024-thread blocks per CU (without the
 //     bound, the sums at the kernel's end took some past 64 VGPRs).
 //   FP64 discontinuous integrand, d = 14 to 24: 3, one 768-thread block per CU.
