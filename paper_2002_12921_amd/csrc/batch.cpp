@@ -186,7 +186,7 @@ void build_items(vegas_batch* b, uint64_t T, std::vector<BatchItem>& items)
         const size_t q = bucket_of(b->dims[p]);
         const double cost = double(event_cost(b->dims[p]));
         for (uint64_t e0 = 0; e0 < M;) {
-            const uint64_t share = uint64_t(left[q] / (2.0 * cost * b->buckets[q].blocks)) / kTileStep * kTileStep;
+            const uint64_t share = uint64_t(std::max(left[q], 0.0) / (2.0 * cost * b->buckets[q].blocks)) / kTileStep * kTileStep;
             BatchItem it{};
             it.prob = p;
             it.e0 = e0;

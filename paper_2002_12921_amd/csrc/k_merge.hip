@@ -440,6 +440,7 @@ hipError_t launch_copy_out(const double* src, int n, const HostPost& host, hipSt
     return hipGetLastError();
 }
 
+static_assert(sizeof(EdgeValues) + sizeof(ProblemPtrs) + 64 <= 4096, "a launch's arguments");
 hipError_t launch_set_edges(const double* host_edges, const ProblemPtrs& p, int kind, int d, int N, hipStream_t s)
 {
     const int per = kEdgeValues / (N + 1);  // dimensions a launch carries
