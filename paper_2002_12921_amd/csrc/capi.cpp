@@ -416,7 +416,8 @@ vegas_status init_ctx(vegas_ctx** out, const vegas_desc* desc, const char* sourc
     // Gaussian written as source, FP64, by blocks of 512 threads: N = 50, two with
     // 16 replicas 70.8 us, three with 8 74.9, three with 4 81.6; N = 100, one with
     // 16 72.1, two with 8 70.8, three with 4 77.7; N = 200, one with 8 79.9, two
-    // with 4 80.6. Ties keep the larger block and the more replicas.
+    // with 4 80.6; d = 6, N = 255, one with 8 72.1 and 51.1 without histograms (which
+    // run in the same blocks), two with 4 70.0 and 50.0. Ties keep the larger block and the more replicas.
     // Beyond d = 8 each event makes more histogram atomics per instruction and
     // the replicas weigh more: per 1e7 events, the FP32-mixed Gaussian took 88 us
     // with one block of 16 and 114 us with two of 8 (d = 16, N = 50), 110 us with
@@ -427,7 +428,7 @@ vegas_status init_ctx(vegas_ctx** out, const vegas_desc* desc, const char* sourc
     // replicas in two blocks and 47 with 8 in one; with N = 160, FP64, 57 and 58
     // us; but d = 7, N = 255, FP64, 72 us with two (conflicting) replicas in two
     // blocks and 60 with 8 in one.
-    static const double kRepFactorLow[5] = {0.05, 0.12, 0.28, 0.6, 1.0};  // 1, 2, 4, 8, 16 replicas
+    static const double kRepFactorLow[5] = {0.05, 0.2, 0.33, 0.6, 1.0};   // 1, 2, 4, 8, 16 replicas
     static const double kRepFactorSets[5] = {0.05, 0.12, 0.95, 0.98, 1.0};
     static const double kRepFactorHigh[5] = {0.05, 0.1, 0.2, 0.45, 1.0};
     double best = -1.0;
