@@ -75,11 +75,11 @@ __device__ __forceinline__ U4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c
 //   scaled, W = (E_{b+1} - E_b) 2^-32, the table entry is (E_b - c + h W, W) for
 //   the integrand's centre c, so u = x - c = fma(lo, W, first entry) is one
 //   convert and one fma (x itself is not formed; the centre is 0 for user
-//   integrands).  The width product takes the factors 2^-32 back four at a time:
-//   it is multiplied by 2^128 before each group of four dimensions, so it never
-//   falls below the product of the widths, and the constant Cw holds what a
-//   last, partial group took too much.  (Forming delta took an fma per dimension
-//   and, where 2^-32 and h sat in scalar registers, a copy of h.)
+//   integrands).  The width product takes the factors 2^-32 back ahead of them: it
+//   starts at 2^(32 d), or beyond d = 24, where that overflows, is multiplied by
+//   2^32 per dimension before each group of four, so it never falls below the
+//   product of the widths and ends as that.  (Forming delta took an fma per
+//   dimension and, where 2^-32 and h sat in scalar registers, a copy of h.)
 // FP32: the map works on u' = (x - c) S with S = 2^(ws + 32).  With
 //   delta = (lo + h)/2^32 (see bin_words) and W = RN32(width), the table entry is
 //     (RN32((E_b - c + h W / 2^32) S), W 2^ws),
@@ -201,11 +201,13 @@ struct EvalConsts {
     double c64[DMAX];   // FP32 path, DISC: c_i / S (exponent summed in FP64, d > 8)
     float c32[DMAX];    // FP32 path, DISC: RN32(c_i / S) (exponent summed in FP32, d <= 8)
     // FP64 path: the exponential of GAUSS, BIMODAL and DISC (DevConst), and the
-    // width product's start: the constant's mantissa (PEAK: 1) times 2^128 per
-    // group of four dimensions (beyond kWhole, where that overflows, 2^128, and
-    // the groups after the first multiply by it)
+    // width product's start: the constant's mantissa (PEAK: 1) times 2^32 per
+    // dimension (kWhole), or per dimension of the first group of four (where all
+    // of them overflow: the later groups multiply by 2^128, the last one by
+    // 2^32 for each dimension it has)
     static constexpr bool kExp = P::is64 && KIND != GENZ_PEAK, kWhole = DMAX <= 24;
     double kexp, magic, w0;  // kexp: GAUSS, BIMODAL: -1/a^2
+    uint32_t last_hi;        // high word of the last group's factor
     // coefficients of exp_scaled, in scalar registers where those are free
     // (GAUSS): the compiler holds all in vector registers, and the d = 18
     // kernel (N = 100) spilled 28 instead of 24 (136 against 131 us)
@@ -229,7 +231,7 @@ struct EvalConsts {
     // For records of w and f: both without C.
     __device__ __forceinline__ void leave_out_constant(int d)
     {
-        w0 = ldexp(1.0, kWhole ? 128 * ((d + 3) / 4) : 128);
+        w0 = ldexp(1.0, kWhole ? 32 * d : 128);
         magic = 0x1.8p52;
     }
 
@@ -276,7 +278,8 @@ struct EvalConsts {
         }
         kexp = -c->kexp64;
         magic = c->magic;
-        w0 = ldexp(kExp ? c->mant : 1.0, kWhole ? 128 * ((d + 3) / 4) : 128);
+        w0 = ldexp(kExp ? c->mant : 1.0, kWhole ? 32 * d : 128);
+        last_hi = uint32_t(1023 + 32 * ((d - 1) % 4 + 1)) << 20;
         k2 = (P::is64 || KIND == GENZ_DISC) ? c->kexp2_64 : c->kexp2_64 * ds2;
         dscale = real(ds);
         const uint32_t N = uint32_t(c->n_bins);
@@ -353,8 +356,11 @@ struct EventEval {
         for (int g = 0; g < (DMAX + 3) / 4; ++g) {
             if (4 * g < d) {
                 const U4 k = philox4x32_10(elo, ehi, t, ctr3 + uint32_t(g), key0, key1);
-                if constexpr (P::is64 && !EvalConsts<P, KIND, DMAX>::kWhole)
-                    if (g > 0) w *= real(0x1p128);
+                if constexpr (P::is64 && !EvalConsts<P, KIND, DMAX>::kWhole) {
+                    // (its high word alone: one scalar select)
+                    constexpr uint32_t kFour = uint32_t(1023 + 128) << 20;
+                    if (g > 0) w *= real(__hiloint2double(int(EXACT || 4 * g + 4 <= d ? kFour : c.last_hi), 0));
+                }
                 // the group's four bins and table entries first, so that its
                 // LDS reads are in flight together before any is used
                 int bq[4];

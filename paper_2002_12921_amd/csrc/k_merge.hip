@@ -217,7 +217,7 @@ __device__ static void prepare_consts(int prec, int kind, int d, int N, const do
     };
     double nd = 1.0, nd_lo = 0.0, Cf = 1.0, Cf_lo = 0.0;
     for (int k = 0; k < d; ++k) times(nd, nd_lo, double(N));
-    const int shift = prec == FP64 ? -32 * ((4 - d % 4) % 4) : -ws * d;
+    const int shift = prec == FP64 ? 0 : -ws * d;
     const double Cw = ldexp(nd, shift), Cw_lo = ldexp(nd_lo, shift);
     double kexp64 = 0.0, kexp2_64 = 0.0, inv_a = 0.0;
     float kexp32 = 0.0f, ka32 = 0.0f;
@@ -252,7 +252,11 @@ __device__ static void prepare_consts(int prec, int kind, int d, int N, const do
     c->Cf = Cf;
     c->C = C;
     int e = 0;
-    const double m = frexp(C, &e);
+    double m = frexp(C, &e);
+    if (e > 1021) {
+        m = ldexp(m, e - 1021);
+        e = 1021;
+    }
     c->mant = bad ? __builtin_nan("") : m;
     c->magic = 0x1.8p52 + double(e);
 }

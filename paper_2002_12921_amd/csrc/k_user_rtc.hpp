@@ -58,8 +58,8 @@ using map_real = float;
 constexpr int kEntryLog2 = 3;
 #else
 // FP64 context: x_i = fma(lo, W, E_b + h W), W the bin's width times 2^-32, the
-// built-in FP64 map with centre 0; the width product takes 2^128 per group of
-// four dimensions.
+// built-in FP64 map with centre 0; the width product takes 2^32 per dimension,
+// ahead of its width.
 using tab_t = double2;
 using map_real = double;
 constexpr int kEntryLog2 = 4;
@@ -80,17 +80,17 @@ struct Event {
 #ifdef VEGAS_FP32
         float w = 1.0f;
 #else
-        // 2^128 per group of four dimensions, at once where that is in range
-        double w = 0x1p128;
-        if (D <= 24)
-            for (int g = 1; g < (D + 3) / 4; ++g) w *= 0x1p128;
+        // 2^32 per dimension, at once where that is in range
+        double w = 1.0;
+#pragma unroll
+        for (int i = 0; i < (D <= 24 ? D : 4); ++i) w *= 0x1p32;
 #endif
         int ewl = 0;
 #pragma unroll
         for (int g = 0; g < (D + 3) / 4; ++g) {
             const U4 k = philox4x32_10(elo, ehi, t, ctr3 + uint32_t(g), key0, key1);
 #ifndef VEGAS_FP32
-            if (D > 24 && g > 0) w *= 0x1p128;
+            if (D > 24 && g > 0) w *= 4 * g + 4 <= D ? 0x1p128 : D % 4 == 1 ? 0x1p32 : D % 4 == 2 ? 0x1p64 : 0x1p96;
 #endif
 #pragma unroll
             for (int q = 0; q < 4; ++q) {

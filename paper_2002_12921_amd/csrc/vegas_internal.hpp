@@ -37,13 +37,13 @@ enum Prec { FP64 = 0, FP32 = 1 };
 // Derived per-problem constants, computed on the device from the raw FP64
 // parameters whenever they change.  The event kernels compute
 //   F  = the integrand's significand in the kernel precision,
-//   wp = product of the bin widths (FP32: each scaled by 2^ws, ws = round(log2 N);
-//        FP64: times 2^(32 pad), pad the dimensions that the last group of four lacks),
+//   wp = product of the bin widths (FP32: each scaled by 2^ws, ws = round(log2 N)),
 // and the event value v = f w = 2^(ew + fe) (F * wp) * C with C = Cf * Cw,
-// Cf the integrand normalisation and Cw = N^d (FP32: N^d 2^(-ws d); FP64: N^d 2^(-32 pad)).
+// Cf the integrand normalisation and Cw = N^d (FP32: N^d 2^(-ws d)).
 // The FP64 kernels of the integrands with an exponential take C in two parts:
 // its mantissa starts the width product, its exponent is added to the
-// exponential's (v = F wp, no product with C).
+// exponential's (v = F wp, no product with C; the exponent is at most 1021, so
+// that two exponentials of an argument up to 0 and their sum stay finite).
 struct DevConst {
     double C;        // Cf * Cw
     double Cf;       // f = 2^fe F Cf
@@ -60,7 +60,7 @@ struct DevConst {
     double p1_64[kMaxDim];  // GAUSS mu | BIMODAL muA | DISC c | PEAK c^2
     double p2_64[kMaxDim];  //          | BIMODAL muB - muA | DISC a | PEAK a
     float p1_32[kMaxDim];   // PEAK c^2
-    double mant, magic;     // C = mant 2^e; 1.5 2^52 + e
+    double mant, magic;     // C = mant 2^e, mant in [1/2, 1) where e < 1021; 1.5 2^52 + e
     double cA64[kMaxDim];   // table centres: GAUSS mu | BIMODAL muA | DISC, PEAK a
     double cB64[kMaxDim];   // BIMODAL muB
 };

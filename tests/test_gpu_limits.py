@@ -1,0 +1,62 @@
+"""Calls at the ends of what the entry points take."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2002_12921_amd import Vegas
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d", [1, 2, 3, 4, 5, 20, 23, 25, 26, 27, 28])
+def test_user_values_near_the_largest_double(d):
+    """f = 1e300 on the uniform grid (w = 1): S1 = 1e300 M, within the rounding of
+    M = 1000 sums, in every remainder of d by four, below and beyond d = 24."""
+    v = Vegas(d, 2, source="__device__ vegas_real vegas_integrand(const vegas_real* x, int dim, const double* p)\n"
+                           "{ return 1e300; }", precision="fp64")
+    for hist in (True, False):
+        v.iterate(1000, hist=hist)
+        S1 = v.last_iteration()[0]
+        assert abs(S1 / 1000 - 1e300) <= 1e-12 * 1e300, (d, hist, S1)
+
+
+@pytest.mark.parametrize("kind,d,a,x", [("gauss", 1, 3.0, 690), ("gauss", 2, 3.0, 690), ("gauss", 3, 2.0, 700), ("gauss", 4, 2.0, 700),
+                                        ("gauss", 5, 3.0, 690), ("bimodal", 5, 3.0, 690), ("gauss", 22, 0.6, 760),
+                                        ("gauss", 25, 0.6, 760), ("bimodal", 25, 0.6, 760), ("gauss", 27, 0.6, 770)])
+def test_values_near_the_smallest_double(kind, d, a, x):
+    """A Gaussian centred far outside, about e^-x in the middle: the values that
+    count are beyond 2^-1010 and keep their digits. An exponent near 700 has its
+    own rounding in the value: some 2^-53 700 (d + 5) of it, 3e-12 at d = 30; 4e-12."""
+    N, M = 2, 6007
+    mu = 0.5 + a * np.sqrt(x / d)
+    params = [a] + [mu] * d * (2 if kind == "bimodal" else 1)
+    pr = oracle.Problem(d, N, oracle.GAUSS if kind == "gauss" else oracle.BIMODAL, params, seed=11)
+    E = np.tile([0.0, 0.5, 1.0], (d, 1))
+    o1 = oracle.accumulate(pr, E, 0, M)[0]
+    v = Vegas(d, N, kind, params, "fp64", seed=11)
+    v.iterate(M, hist=False)
+    S1 = v.last_iteration()[0]
+    assert 2.0 ** -1000 < o1 < 2.0 ** -940
+    assert abs(S1 - o1) <= 4e-12 * o1, (S1, o1)
+
+
+def test_constant_near_the_largest_double():
+    """The bimodal integrand's normalisation times N^d between 2^1023 and 2^1024,
+    both peaks in one place: f w is of order one and so are the sums."""
+    d, N, M = 2, 3, 6007
+    a = 2.0 ** -511.6
+    params = [a] + [0.0] * (2 * d)
+    assert 1023 < np.log2(0.5 * N * N / np.pi) - 2 * np.log2(a) < 1024
+    E = np.tile([0.0, 2.0 ** -511, 0.5, 1.0], (d, 1))
+    v = Vegas(d, N, "bimodal", params, "fp64", seed=11)
+    v.set_edges(E)
+    ev = v.dump_events(0, M).cpu().numpy()
+    b, delta = ev[:, :d], ev[:, d:2 * d]
+    # f w = prod of (a sqrt(pi))^-1 e^{-(x/a)^2} N W over the events with both bins at the peak
+    peak = (b == 0).all(axis=1)
+    x = delta[peak] * 2.0 ** -511
+    val = np.exp(-((x / a) ** 2)) / np.sqrt(np.pi) * (N * (2.0 ** -511 / a))
+    o1 = val.prod(axis=1).sum()
+    v.iterate(M, hist=False)
+    S1 = v.last_iteration()[0]
+    assert np.isfinite(o1) and abs(S1 - o1) <= 1e-12 * o1, (S1, o1)
