@@ -168,7 +168,7 @@ __device__ static void prepare_consts(int prec, int kind, int d, int N, const do
     __shared__ double factor[kMaxDim];
     const double log2e = 1.4426950408889634074;
     const int i = threadIdx.x;
-    bool not_a_number = false;
+    bool no_exponent = false;
     if (i < kMaxDim) {
         double p1 = 0.0, p2 = 0.0, cA = 0.0, cB = 0.0, f = 1.0;
         float p1f = 0.0f;
@@ -199,10 +199,16 @@ __device__ static void prepare_consts(int prec, int kind, int d, int N, const do
         c->cB64[i] = cB;
         c->p1_32[i] = p1f;
         factor[i] = f;
-        not_a_number = p1 != p1 || p2 != p2;
+        // an exponent that is not a number, which the exponential's cut would
+        // hide: a parameter is not, infinity less infinity (u_B = u_A - (muB -
+        // muA)), or a square beyond the range over an infinite width
+        no_exponent = p1 != p1 || p2 != p2 || (kind == BIMODAL && isinf(p1));
+        if ((kind == GAUSS || kind == BIMODAL) && i < d) {
+            const double ka = 1.0 / (q[0] * q[0]), A = cA * cA * d * ka, B = cB * cB * d * ka;
+            no_exponent = no_exponent || A != A || B != B;
+        }
     }
-    // (the exponential's cut would hide it)
-    const bool bad = __syncthreads_or(not_a_number);
+    const bool bad = __syncthreads_or(no_exponent);
     if (threadIdx.x != 0) return;
     c->n_bins = N;
     c->pad1 = 0;
@@ -257,8 +263,8 @@ __device__ static void prepare_consts(int prec, int kind, int d, int N, const do
         m = ldexp(m, e - 1021);
         e = 1021;
     }
-    c->mant = bad ? __builtin_nan("") : m;
-    c->magic = 0x1.8p52 + double(e);
+    c->mant = m;
+    c->magic = bad ? __builtin_nan("") : 0x1.8p52 + double(e);
 }
 
 __global__ void k_prepare(int prec, int kind, int d, int N, const double* __restrict__ q,

@@ -60,7 +60,7 @@ struct DevConst {
     double p1_64[kMaxDim];  // GAUSS mu | BIMODAL muA | DISC c | PEAK c^2
     double p2_64[kMaxDim];  //          | BIMODAL muB - muA | DISC a | PEAK a
     float p1_32[kMaxDim];   // PEAK c^2
-    double mant, magic;     // C = mant 2^e, mant in [1/2, 1) where e < 1021; 1.5 2^52 + e
+    double mant, magic;     // C = mant 2^e, mant in [1/2, 1) where e < 1021; 1.5 2^52 + e (NaN: no exponent)
     double cA64[kMaxDim];   // table centres: GAUSS mu | BIMODAL muA | DISC, PEAK a
     double cB64[kMaxDim];   // BIMODAL muB
 };

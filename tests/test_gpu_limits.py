@@ -1,6 +1,7 @@
 """Calls at the ends of what the entry points take."""
 import numpy as np
 import pytest
+import torch
 
 import oracle
 from paper_2002_12921_amd import Vegas
@@ -60,3 +61,34 @@ def test_constant_near_the_largest_double():
     v.iterate(M, hist=False)
     S1 = v.last_iteration()[0]
     assert np.isfinite(o1) and abs(S1 - o1) <= 1e-12 * o1, (S1, o1)
+
+
+@pytest.mark.parametrize("kind,at,more", [("bimodal", 1, {}), ("bimodal", 2, {}), ("bimodal", 5, {0: np.inf}), ("gauss", 1, {0: np.inf})])
+@pytest.mark.parametrize("N", [20, 21])
+def test_infinite_parameter_is_not_hidden(kind, at, more, N):
+    """Infinite parameters set on the device whose exponent is not a number give
+    results that are not numbers."""
+    d = 3
+    q = [0.3] + [0.4] * d + ([0.6] * d if kind == "bimodal" else [])
+    v = Vegas(d, N, kind, q, "fp64")
+    p = torch.tensor(q, dtype=torch.float64, device="cuda")
+    p[at] = float("inf")
+    for k, x in more.items():
+        p[k] = x
+    v.set_params_device(p)
+    v.iterate(1000)
+    S1, S2, H = v.last_iteration()
+    assert np.isnan(S1) and np.isnan(S2) and np.isnan(H).any()
+    assert np.isnan(v.dump_events(0, 10)[:, -1].cpu().numpy()).all()
+
+
+@pytest.mark.parametrize("kind,at", [("gauss", 1), ("bimodal", 3), ("bimodal", 4), ("genz_disc", 0)])
+def test_nan_parameter_in_event_records(kind, at):
+    """A parameter that is not a number shows in the records of f as in the sums."""
+    d = 3
+    q = {"gauss": [0.3] + [0.4] * d, "bimodal": [0.3] + [0.4] * d + [0.6] * d, "genz_disc": [1.0] * d + [0.0] * d}[kind]
+    v = Vegas(d, 20, kind, q, "fp64")
+    p = torch.tensor(q, dtype=torch.float64, device="cuda")
+    p[at] = float("nan")
+    v.set_params_device(p)
+    assert np.isnan(v.dump_events(0, 10)[:, -1].cpu().numpy()).all()
