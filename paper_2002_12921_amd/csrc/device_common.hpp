@@ -120,10 +120,11 @@ struct TabLog2 {
 // (its low word is e + n), the rest f = x log2 e - n in [-1/2, 1/2] is formed with
 // one rounding (log2 e as a sum of two), and 2^f is a polynomial of degree 11
 // (minimax for the relative error with the constant 1 and the linear coefficient
-// RN(ln 2) held: 9e-18). |x| log2 e is at most 4000 here, where the result is 0 or
-// infinite for every e of a finite C. (magic is not a number where x is not: the
-// cut hides it, so the parameters are looked at instead, once.) Against exp(x)
-// times C: 17 instructions
+// RN(ln 2) held: 9e-18). x is cut at -4000 ln 2, where the result is 0 for every e
+// of a finite C; above, x log2 e stays below 10^8 (the discontinuous integrand's c
+// (1 - a) is at most 10^6 there), and the sum's low word holds any such n. (magic is
+// not a number where x is not, which the cut hides, or where it may be larger: the
+// parameters are looked at instead, once.) Against exp(x) times C: 17 instructions
 // for 23 (the loop is bound by their issue). Per 1e7 events, N = 50, without
 // histograms: the d = 8 Gaussian 45.1 -> 43.4 us, d = 4 28.9 -> 27.0, the bimodal
 // integrand (two of them) d = 8 55.8 -> 52.2. held: the coefficients of f^10 to
@@ -472,7 +473,7 @@ struct EventEval {
                 F = exp_scaled(fmax(sa * c.kexp, -kExpCut), c.magic, c.held) +
                     exp_scaled(fmax(sb * c.kexp, -kExpCut), c.magic, c.held);
             else if constexpr (KIND == GENZ_DISC)
-                F = inside ? exp_scaled(fmin(sa, kExpCut), c.magic, c.held) : 0.0;  // sa = sum c (x - a)
+                F = inside ? exp_scaled(fmax(sa, -kExpCut), c.magic, c.held) : 0.0;  // sa = sum c (x - a)
             else
                 F = real(1) / den;
         } else {

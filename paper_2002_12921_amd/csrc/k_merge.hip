@@ -207,6 +207,8 @@ __device__ static void prepare_consts(int prec, int kind, int d, int N, const do
             const double ka = 1.0 / (q[0] * q[0]), A = cA * cA * d * ka, B = cB * cB * d * ka;
             no_exponent = no_exponent || A != A || B != B;
         }
+        // (e^(c (1 - a)) is beyond the range from 710 on, and the constant 0: infinity times 0)
+        if (kind == GENZ_DISC && i < d) no_exponent = no_exponent || p1 * (1.0 - p2) > 1e6;
     }
     const bool bad = __syncthreads_or(no_exponent);
     if (threadIdx.x != 0) return;

@@ -92,3 +92,30 @@ def test_nan_parameter_in_event_records(kind, at):
     p[at] = float("nan")
     v.set_params_device(p)
     assert np.isnan(v.dump_events(0, 10)[:, -1].cpu().numpy()).all()
+
+
+@pytest.mark.parametrize("c", [-3.0, -2e3, -1e10, -1e300])
+def test_negative_genz_constant(c):
+    """c is not checked where it comes from the device: f = nu e^{c x} falls then,
+    down to 0, and never grows."""
+    N, M, a = 20, 6007, 0.25
+    v = Vegas(1, N, "genz_disc", [1.0, a], "fp64", seed=11)
+    v.set_params_device(torch.tensor([c, a], dtype=torch.float64, device="cuda"))
+    v.iterate(M)
+    S1, S2, H = v.last_iteration()
+    x = v.dump_events(0, M, iteration=0)[:, 2].cpu().numpy()
+    with np.errstate(under="ignore", over="ignore"):
+        f = np.where(x > a, c / np.expm1(c * (1.0 - a)) * np.exp(c * (x - a)), 0.0)
+    # (x - a is rounded: c 2^-53 of f each)
+    tol = max(1e-12, 4 * abs(c) * 2.0 ** -53) if abs(c) < 1e9 else 0.0
+    assert abs(S1 - f.sum()) <= tol * f.sum() and abs(S2 - (f * f).sum()) <= 2 * tol * (f * f).sum()
+    assert np.all(np.abs(H.sum() - (f * f).sum()) <= 2 * tol * (f * f).sum())
+
+
+@pytest.mark.parametrize("c", [1e3, 1e7, 1e10, 1e300])
+def test_genz_constant_beyond_the_range(c):
+    """Where e^(c (1 - a)) overflows, the normalisation is 0 and the sums are not numbers."""
+    v = Vegas(2, 20, "genz_disc", [1.0, 1.0, 0.25, 0.0], "fp64", seed=11)
+    v.set_params_device(torch.tensor([1.0, c, 0.25, 0.0], dtype=torch.float64, device="cuda"))
+    v.iterate(6007, hist=False)
+    assert np.isnan(v.last_iteration()[0])
