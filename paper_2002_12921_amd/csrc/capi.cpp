@@ -63,7 +63,7 @@ vegas_status check_params(int kind, int d, const double* q)
 // LDS of the runtime-compiled event kernel: table, histogram replicas, wave partials.
 size_t user_lds(int prec, int d, int N, int rep, bool hist)
 {
-    return lds_bytes(prec, USER, d, N, hist ? rep : 0) + red_bytes(2);
+    return with_sums(lds_bytes(prec, USER, d, N, hist ? rep : 0));
 }
 
 // LDS per block of the event kernel with one histogram copy per bin (the
@@ -246,9 +246,12 @@ hipError_t launch_event_kernel(const vegas_ctx* c, const SampleArgs& a, int bloc
     if (c->kind != USER) return launch_sample(c->prec, c->kind, a, blocks, c->threads, s);
     const bool hist = a.hist != 0;
     const double* params = c->P.params;
-    void* args[] = {const_cast<SampleArgs*>(&a), const_cast<double**>(&params)};
+    const size_t data = lds_bytes(c->prec, USER, c->d, c->N, hist ? 1 << a.hrep_log2 : 0);
+    SampleArgs b = a;
+    b.red_at = sums_at(data);
+    void* args[] = {&b, const_cast<double**>(&params)};
     return hipModuleLaunchKernel(c->usample[hist ? 0 : 1], unsigned(blocks), 1, 1, unsigned(c->threads), 1, 1,
-                                 unsigned(event_lds(c, 1 << a.hrep_log2, hist)), s, args, nullptr);
+                                 unsigned(with_sums(data)), s, args, nullptr);
 }
 
 // Values a copy to the host may have for one block of a kernel to write them

@@ -72,7 +72,7 @@ __global__ __attribute__((amdgpu_flat_work_group_size(1, MaxThreads<P, KIND, DMA
     const size_t hist_bytes = HM == kHistNone ? 0 : size_t(nh) * sizeof(double) << rl2;
     tab_t* tab = reinterpret_cast<tab_t*>(smem);
     double* hist = reinterpret_cast<double*>(smem + tab_bytes);
-    double* red = reinterpret_cast<double*>(smem + tab_bytes + hist_bytes);
+    double* red = reinterpret_cast<double*>(smem + a.red_at);
     const uint32_t ltab = lds_address(smem);
     static_assert(GL == 0 || EXACT, "sets of dimensions: kernels without guards only");
     const HistAdder<TabLog2<P, KIND>::value> hadd(ltab, ltab + uint32_t(tab_bytes), rl2);
@@ -131,6 +131,7 @@ __global__ __attribute__((amdgpu_flat_work_group_size(1, MaxThreads<P, KIND, DMA
 
     // block_sums synchronises, which also completes every histogram atomic
     const double v12[2] = {s1 - c1, s2 - c2};
+    if (a.red_at == 0) __syncthreads();  // every wave is done with the table
     const double S = block_sums(v12, red);
     if (threadIdx.x < 2) a.partials[size_t(blockIdx.x) * 2 + threadIdx.x] = S;
     // the block's histogram (replicas summed) goes into slot
@@ -551,11 +552,16 @@ hipError_t launch_sample_grad(int prec, const SampleArgs& a, double* gpart, int 
     return hipLaunchKernel(fn, dim3(blocks), dim3(threads), args, lds, s);
 }
 
+// LDS of the table and histogram.
+static size_t sample_data(int prec, int kind, int d, int N, int rep, bool hist)
+{
+    const int hm = hist_mode(prec, kind, d, N, rep, hist);
+    return lds_bytes(prec, kind, d, N, hist ? rep : 0, hm > kHistSets1 ? hm - 1 : 0);
+}
+
 size_t sample_lds(int prec, int kind, int d, int N, int rep, bool hist)
 {
-    // the wave partials of the block sums follow the table and histogram
-    const int hm = hist_mode(prec, kind, d, N, rep, hist);
-    return lds_bytes(prec, kind, d, N, hist ? rep : 0, hm > kHistSets1 ? hm - 1 : 0) + red_bytes(2);
+    return with_sums(sample_data(prec, kind, d, N, rep, hist));
 }
 
 bool sample_in_sets(int prec, int kind, int d, int N, int rep)
@@ -568,8 +574,11 @@ hipError_t launch_sample(int prec, int kind, const SampleArgs& a, int blocks, in
     const bool hist = a.hist != 0;
     const int rep = 1 << a.hrep_log2;
     const void* fn = sample_kernel(prec, kind, a.d, hist_mode(prec, kind, a.d, a.N, rep, hist));
-    void* args[] = {const_cast<SampleArgs*>(&a)};
-    return hipLaunchKernel(fn, dim3(blocks), dim3(threads), args, sample_lds(prec, kind, a.d, a.N, rep, hist), s);
+    const size_t data = sample_data(prec, kind, a.d, a.N, rep, hist);
+    SampleArgs b = a;
+    b.red_at = sums_at(data);
+    void* args[] = {&b};
+    return hipLaunchKernel(fn, dim3(blocks), dim3(threads), args, with_sums(data), s);
 }
 
 hipError_t launch_dump(int prec, int kind, const DumpArgs& a, hipStream_t s)

@@ -137,6 +137,14 @@ inline size_t lds_bytes(int prec, int kind, int d, int N, int rep = 1, int gl = 
 // LDS of a block's sums of n values per thread: a partial per wave and value.
 inline size_t red_bytes(int n) { return sizeof(double) * size_t(n) * (kBlock / 64); }
 
+// LDS of the event kernel with `data` bytes of table and histogram, and where in
+// it the block's sums of S1 and S2 go: behind the data, or where that exceeds the
+// LDS, over the table (offset 0, with a barrier after the last event). One
+// partial per wave has to fit in any case: a launch (d N = 2046 with 8 replicas,
+// 4089 with 4) is not refused for the second.
+inline size_t with_sums(size_t data) { return data + red_bytes(data + red_bytes(2) <= kLdsLimit ? 2 : 1); }
+inline uint32_t sums_at(size_t data) { return data + red_bytes(2) <= kLdsLimit ? uint32_t(data) : 0u; }
+
 // Device pointers of one problem's state.
 struct ProblemPtrs {
     double* params;
@@ -193,6 +201,7 @@ struct SampleArgs {
     int d, N;
     int hrep_log2;       // log2 of the histogram replicas per bin
     int hist;            // 0: no histograms this launch (only S1, S2 are written)
+    uint32_t red_at;     // LDS offset of the block sums' partials (0: over the table)
 };
 
 // Where a kernel writes results for the host (pinned memory), and the mark it

@@ -4,7 +4,7 @@ import pytest
 import torch
 
 import oracle
-from paper_2002_12921_amd import Vegas
+from paper_2002_12921_amd import Vegas, VegasError
 
 pytestmark = pytest.mark.gpu
 
@@ -119,3 +119,56 @@ def test_genz_constant_beyond_the_range(c):
     v.set_params_device(torch.tensor([1.0, c, 0.25, 0.0], dtype=torch.float64, device="cuda"))
     v.iterate(6007, hist=False)
     assert np.isnan(v.last_iteration()[0])
+
+
+def _largest(prec, kind):
+    """(d, N, replicas) whose table, histogram copies and 128 bytes of partial
+    sums fit 160 KiB with less than another 128 bytes to spare."""
+    entry = 8 if prec == "fp32_mixed" and kind not in ("bimodal",) else 16
+    out = []
+    for d in range(1, 65):
+        for N in range(2, 256):
+            for rep in (1, 2, 4, 8, 16):
+                need = (d * N * entry + 127) // 128 * 128 + d * N * 8 * rep + 128
+                if 160 * 1024 - 128 < need <= 160 * 1024:
+                    out.append((d, N, rep))
+    return out
+
+
+@pytest.mark.parametrize("prec,kind", [("fp64", "gauss"), ("fp32_mixed", "gauss"), ("fp32_mixed", "bimodal"), ("fp64", "genz_disc")])
+def test_replicas_that_just_fit(prec, kind):
+    """Replica counts whose LDS fits by less than 128 bytes are accepted, and the
+    launch, whose sums then lie over the table, gives the oracle's sums and bins."""
+    sizes = _largest(prec, kind)
+    assert len(sizes) >= 2
+    tol = 1e-12 if prec == "fp64" else 1e-6
+    for d, N, rep in sizes:
+        if kind.startswith("genz"):
+            params = [1.0] * d + [0.01] * d
+        else:
+            params = [0.4] + [0.5] * d * (2 if kind == "bimodal" else 1)
+        v = Vegas(d, N, kind, params, prec, seed=11)
+        v.set_hist_replicas(rep)
+        v.iterate(9001)
+        S1, S2, H = v.last_iteration()
+        k = {"gauss": oracle.GAUSS, "bimodal": oracle.BIMODAL, "genz_disc": oracle.GENZ_DISC}[kind]
+        pr = oracle.Problem(d, N, k, params, seed=11)
+        o1, o2, Ho = oracle.accumulate(pr, np.tile(np.arange(N + 1) / N, (d, 1)), 0, 9001)
+        t = tol * max(1.0, d / 8) if prec != "fp64" else tol
+        assert abs(S1 - o1) <= t * o1 and abs(S2 - o2) <= t * o2, (d, N, rep)
+        assert np.all(np.abs(H - Ho) <= t * Ho.sum(axis=1, keepdims=True)), (d, N, rep)
+        v.iterate(9001, hist=False)
+
+
+@pytest.mark.parametrize("d,N,prec,rep", [(11, 186, "fp64", 8), (62, 33, "fp64", 8), (22, 186, "fp32_mixed", 4)])
+def test_user_replicas_that_just_fit(d, N, prec, rep):
+    """The same for a runtime-compiled integrand (f = 1 on the uniform grid): S1 = M
+    and every bin's S2 counts its events; one replica count more is refused."""
+    v = Vegas(d, N, source="__device__ vegas_real vegas_integrand(const vegas_real* x, int dim, const double* p)\n"
+                           "{ return 1; }", precision=prec)
+    v.set_hist_replicas(rep)
+    v.iterate(9001)
+    S1, S2, H = v.last_iteration()
+    assert abs(S1 - 9001) <= 1e-6 * 9001 and np.all(np.abs(H.sum(axis=1) - S2) <= 1e-9 * S2)
+    with pytest.raises(VegasError):
+        v.set_hist_replicas(2 * rep)
