@@ -296,7 +296,9 @@ vegas_status vegas_dump_events(vegas_ctx* ctx, int64_t iteration, int64_t first,
                                double* dev_out, vegas_stream_t stream);
 
 /* Copy grid edges (host FP64 [d][N+1]) out of / into the context.
- * vegas_get_edges synchronises; vegas_set_edges rebuilds the kernel tables. */
+ * vegas_get_edges synchronises; vegas_set_edges rebuilds the kernel tables.
+ * Under stream capture vegas_set_edges records a copy: every replay reads
+ * host_edges as it is then, unchecked, so the array has to outlive the graph. */
 vegas_status vegas_get_edges(vegas_ctx* ctx, double* host_edges, vegas_stream_t stream);
 vegas_status vegas_set_edges(vegas_ctx* ctx, const double* host_edges, vegas_stream_t stream);
 

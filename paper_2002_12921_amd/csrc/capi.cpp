@@ -865,8 +865,14 @@ vegas_status vegas_set_edges(vegas_ctx* c, const double* host, vegas_stream_t st
     if (st != VEGAS_OK) return st;
     hipStream_t s = static_cast<hipStream_t>(stream);
     // in the arguments of one launch or two (5.1 us at d = 4, 7.7 with a copy
-    // call), beyond (d (N + 1) > 960 or so) as a copy
-    if (2 * (kEdgeValues / (c->N + 1)) >= c->d) {
+    // call), beyond (d (N + 1) > 960 or so) as a copy; under capture as a copy in
+    // any case: a replay reads the caller's array
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess) {  // (the default stream beside another's capture)
+        (void)hipGetLastError();
+        cap = hipStreamCaptureStatusActive;
+    }
+    if (cap == hipStreamCaptureStatusNone && 2 * (kEdgeValues / (c->N + 1)) >= c->d) {
         VEGAS_HIP(launch_set_edges(host, c->P, c->kind, c->d, c->N, s));
     } else {
         VEGAS_HIP(hipMemcpyAsync(c->P.edges, host, sizeof(double) * c->d * (c->N + 1), hipMemcpyHostToDevice, s));

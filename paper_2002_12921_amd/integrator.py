@@ -261,8 +261,12 @@ class Vegas:
         return e
 
     def set_edges(self, edges: np.ndarray):
+        """Under stream capture the replays read `edges` (a contiguous FP64 array)
+        as it is then; an array made here of anything else is kept."""
         e = np.ascontiguousarray(np.asarray(edges, dtype=np.float64))
         assert e.shape == (self.dim, self.n_bins + 1)
+        if e is not edges and torch.cuda.is_current_stream_capturing():
+            self._captured_edges = getattr(self, "_captured_edges", []) + [e]
         check(lib().vegas_set_edges(self._ctx, e.ctypes.data_as(ctypes.POINTER(ctypes.c_double)),
                                     self._s()), "set_edges")
 

@@ -172,3 +172,60 @@ def test_user_replicas_that_just_fit(d, N, prec, rep):
     assert abs(S1 - 9001) <= 1e-6 * 9001 and np.all(np.abs(H.sum(axis=1) - S2) <= 1e-9 * S2)
     with pytest.raises(VegasError):
         v.set_hist_replicas(2 * rep)
+
+
+@pytest.mark.parametrize("d,N", [(2, 10), (16, 100)])
+def test_captured_edges_follow_the_host_array(d, N):
+    """vegas_set_edges recorded into a graph reads the caller's edges at each
+    replay, whether they are few or many."""
+    def grid(seed):
+        r = np.random.default_rng(seed)
+        E = np.zeros((d, N + 1))
+        E[:, 1:] = np.cumsum(r.uniform(0.5, 1.5, (d, N)), axis=1)
+        E /= E[:, -1:]
+        E[:, -1] = 1.0
+        return E
+    params = [0.3] + [0.5] * d
+    v = Vegas(d, N, "gauss", params, "fp64", seed=7)
+    other = Vegas(d, N, "gauss", params, "fp64", seed=7)
+    s = torch.cuda.Stream()
+    v.stream = s
+    host = grid(0)
+    g = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g, stream=s):
+        v.set_edges(host)
+        v.iterate(5003)
+    for rep in range(3):
+        E = grid(rep)
+        host[:] = E
+        with torch.cuda.stream(s):
+            g.replay()
+        assert np.array_equal(v.edges(), E), rep
+        S1 = v.last_iteration()[0]
+        pr = oracle.Problem(d, N, oracle.GAUSS, params, seed=7)
+        o1 = oracle.accumulate(pr, E, 0, 5003)[0]
+        assert abs(S1 - o1) <= 1e-12 * o1, rep
+        # eager work between replays
+        other.set_edges(E)
+        other.iterate(1000)
+        torch.cuda.synchronize()
+
+
+def test_captured_edges_made_by_the_call_are_kept():
+    """A list of edges captured: the array made of it lives as long as the Vegas
+    object, so the replays read its values."""
+    v = Vegas(1, 4, "gauss", [0.3, 0.5], "fp64", seed=7)
+    s = torch.cuda.Stream()
+    v.stream = s
+    E = [[0.0, 0.1, 0.4, 0.7, 1.0]]
+    g = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g, stream=s):
+        v.set_edges(E)
+    for _ in range(3):
+        v.set_edges([[0.0, 0.2, 0.3, 0.9, 1.0]])
+        with torch.cuda.stream(s):
+            g.replay()
+        assert v.edges().tolist() == E
+    assert len(v._captured_edges) == 1
