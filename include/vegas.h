@@ -417,7 +417,7 @@ vegas_status vegas_batch_results(vegas_batch* batch, vegas_result_t* host_out,
  * Environment: VEGAS_BATCH_TILE, VEGAS_BATCH_THREADS, VEGAS_BATCH_REPLICAS
  * force a value (that dimension is not tuned); VEGAS_BATCH_TUNE_CACHE names
  * a file where unforced choices are kept per (device, batch) and read back
- * instead of tuning again.
+ * instead of tuning again (not those of a library with another schedule).
  * vegas_batch_schedule: the tile, the largest bucket launch (blocks), the
  * work items per iteration and the chosen buckets' summed time (ms; 0 when
  * nothing was timed).  Any pointer may be NULL. */

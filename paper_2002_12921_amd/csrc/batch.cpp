@@ -329,8 +329,10 @@ vegas_status time_schedule(vegas_batch* b, Timer& tm, std::vector<double>& per)
     return VEGAS_OK;
 }
 
-// Tuning-cache key: the device (architecture, compute units) and the batch
-// (precision, integrand, sizes of every problem, iteration counts).
+// Tuning-cache key: what a stored choice means and was timed with (v1: tiles of
+// one size, other kernels; raised when the schedule or the kernels change), the
+// device (architecture, compute units) and the batch (precision, integrand, sizes
+// of every problem, iteration counts).
 std::string tune_key(const vegas_batch* b, int dev, int cus)
 {
     hipDeviceProp_t prop;
@@ -351,7 +353,7 @@ std::string tune_key(const vegas_batch* b, int dev, int cus)
         mix(uint64_t(b->events[p]));
     }
     std::ostringstream o;
-    o << "vegas-batch-v1 " << arch << " cu" << cus << " p" << b->prec << " k" << b->kind << " n" << b->n << " i"
+    o << "vegas-batch-v2 " << arch << " cu" << cus << " p" << b->prec << " k" << b->kind << " n" << b->n << " i"
       << b->n_iter << " a" << b->n_adapt << " h" << std::hex << h;
     return o.str();
 }

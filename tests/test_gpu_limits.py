@@ -5,6 +5,7 @@ import torch
 
 import oracle
 from paper_2002_12921_amd import Vegas, VegasError
+from paper_2002_12921_amd.batch import VegasBatch
 
 pytestmark = pytest.mark.gpu
 
@@ -229,3 +230,19 @@ def test_captured_edges_made_by_the_call_are_kept():
             g.replay()
         assert v.edges().tolist() == E
     assert len(v._captured_edges) == 1
+
+
+def test_tuning_cache_of_an_earlier_schedule(monkeypatch, tmp_path):
+    """A stored choice under the tag of an earlier kind of schedule (fixed tiles)
+    is not taken: the plan tunes and stores its own."""
+    path = tmp_path / "tune.txt"
+    monkeypatch.setenv("VEGAS_BATCH_TUNE_CACHE", str(path))
+    probs = [{"dim": d, "n_bins": 20, "params": [0.2] + [0.5] * d, "n_events": 20_000, "precision": "fp64"} for d in (2, 3, 6)]
+    assert not VegasBatch(probs, 3, 2).schedule()["from_cache"]
+    line = path.read_text()
+    tag = line.split()[0]
+    assert tag.startswith("vegas-batch-v")
+    path.write_text(line.replace(tag, "vegas-batch-v1"))
+    assert not VegasBatch(probs, 3, 2).schedule()["from_cache"]
+    assert len(path.read_text().splitlines()) == 2
+    assert VegasBatch(probs, 3, 2).schedule()["from_cache"]
