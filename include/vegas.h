@@ -19,7 +19,14 @@
  *  - Argument validation happens before any HIP call.
  *  - Streams are hipStream_t values passed as void* (NULL = default stream).
  *    Every call only enqueues work on the given stream, except those marked
- *    "synchronises", which wait for the stream to finish.
+ *    "synchronises". When such a call returns, the work enqueued on the stream
+ *    before it is done and what that wrote is visible to the host and to every
+ *    stream. vegas_result, vegas_get_edges and vegas_get_iteration learn this
+ *    from a mark that their own last kernel stores, and may return while that
+ *    kernel, with nothing left to read or write, retires: hipStreamQuery may
+ *    say "not ready" for some microseconds more, and a device error that comes
+ *    up after the mark is reported by the next call that waits. The others wait
+ *    for the stream itself.
  *  - Device memory is owned by the caller: the context lives in one
  *    caller-allocated device workspace (see vegas_workspace_size).  The
  *    library itself never allocates device memory; it owns only a small host

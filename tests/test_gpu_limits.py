@@ -246,3 +246,70 @@ def test_tuning_cache_of_an_earlier_schedule(monkeypatch, tmp_path):
     assert not VegasBatch(probs, 3, 2).schedule()["from_cache"]
     assert len(path.read_text().splitlines()) == 2
     assert VegasBatch(probs, 3, 2).schedule()["from_cache"]
+
+
+def test_reads_behind_long_runs():
+    """Results, edges and sums asked for while more than the millisecond for which
+    the host looks for the mark is still queued are those of the queued work,
+    and so are the next reads, which find the mark."""
+    d, N = 8, 50
+    params = [0.2] + [0.45] * d
+    v = Vegas(d, N, "gauss", params, "fp64", seed=3)
+    M = 1_000_000_000
+    v.timing_enable()
+    reads = []
+    for k, read in enumerate((v.result, v.edges, v.last_iteration)):
+        v.iterate(M, refine=True)
+        reads.append(read())
+        v.iterate(1000, hist=False)
+        assert v.result()["n_iter"] == 2 * k + 2
+    ms = v.timing_read()[0] / 3
+    assert ms > 2.0, ms
+    w = Vegas(d, N, "gauss", params, "fp64", seed=3)
+    for k in range(3):
+        w.iterate(M, refine=True)
+        torch.cuda.synchronize()
+        got = (w.result, w.edges, w.last_iteration)[k]()
+        if k == 0:
+            assert abs(got["integral"] - reads[0]["integral"]) <= 1e-12 * abs(got["integral"])
+            assert got["n_events"] == reads[0]["n_events"] == M
+        elif k == 1:
+            assert np.max(np.abs(got - reads[1])) <= 1e-9
+        else:
+            assert abs(got[0] - reads[2][0]) <= 1e-9 * got[0]
+        w.iterate(1000, hist=False)
+
+
+def test_device_buffers_are_final_after_a_read():
+    """After result(), edges() or last_iteration() returns, work on another stream,
+    ordered behind nothing, sees what the call's stream has done."""
+    d, N, M = 4, 50, 200_003
+    s, other = torch.cuda.Stream(), torch.cuda.Stream()
+    v = Vegas(d, N, "gauss", [0.2] + [0.45] * d, "fp64", seed=3)
+    torch.cuda.synchronize()
+    v.stream = s
+    out = torch.zeros(2, dtype=torch.float64, device="cuda")
+    torch.cuda.synchronize()
+    for k in range(50):
+        v.iterate(M, refine=True)
+        E = S = None
+        if k % 3 == 0:
+            r = v.result()
+        elif k % 3 == 1:
+            E = v.edges()
+        else:
+            S = v.last_iteration()
+        v.stream = other
+        v.last_iteration_device(out)
+        other.synchronize()
+        got = out.cpu().numpy()
+        again = v.last_iteration()
+        assert got[0] == again[0] / M, k
+        if E is not None:
+            assert np.array_equal(E, v.edges()), k
+        elif S is not None:
+            assert S[0] == again[0] and np.array_equal(S[2], again[2]), k
+        else:
+            assert r["last_integral"] == got[0], k
+        other.synchronize()
+        v.stream = s
