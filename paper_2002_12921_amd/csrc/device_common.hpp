@@ -76,10 +76,11 @@ __device__ __forceinline__ U4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c
 //   the integrand's centre c, so u = x - c = fma(lo, W, first entry) is one
 //   convert and one fma (x itself is not formed; the centre is 0 for user
 //   integrands).  The width product takes the factors 2^-32 back ahead of them: it
-//   starts at 2^(32 d), or beyond d = 24, where that overflows, is multiplied by
-//   2^32 per dimension before each group of four, so it never falls below the
-//   product of the widths and ends as that.  (Forming delta took an fma per
-//   dimension and, where 2^-32 and h sat in scalar registers, a copy of h.)
+//   starts at 2^(32 d), or beyond d = 24, where that overflows, at 2^32 for each
+//   dimension of the last group of four and of one group before, and each group
+//   from the third on multiplies by 2^128; so it never falls below the product of
+//   the widths and ends as that.  (Forming delta took an fma per dimension and,
+//   where 2^-32 and h sat in scalar registers, a copy of h.)
 // FP32: the map works on u' = (x - c) S with S = 2^(ws + 32).  With
 //   delta = (lo + h)/2^32 (see bin_words) and W = RN32(width), the table entry is
 //     (RN32((E_b - c + h W / 2^32) S), W 2^ws),
@@ -192,6 +193,16 @@ __device__ __forceinline__ void bin_words(uint32_t k, const BinConsts& bc, int& 
     lo = uint32_t(P);
 }
 
+// Binary exponent the FP64 width product starts at: all 2^32 of it (whole), or
+// those of the last group of four and of one more group (d > 4; the groups from
+// the third on multiply by 2^128. Choosing the last group's factor in the loop
+// instead made the d = 40 discontinuous kernel without histograms 157 -> 190 us
+// per 4e6 events: a scalar register more, of which it spills hundreds).
+__device__ __forceinline__ constexpr int width_start(bool whole, int d)
+{
+    return whole ? 32 * d : 256 - 32 * ((4 - d % 4) % 4);
+}
+
 // Integrand constants of one problem, read once per thread into registers
 // (they are uniform, so they normally live in scalar registers).
 template <class P, int KIND, int DMAX>
@@ -204,13 +215,10 @@ struct EvalConsts {
     double c64[DMAX];   // FP32 path, DISC: c_i / S (exponent summed in FP64, d > 8)
     float c32[DMAX];    // FP32 path, DISC: RN32(c_i / S) (exponent summed in FP32, d <= 8)
     // FP64 path: the exponential of GAUSS, BIMODAL and DISC (DevConst), and the
-    // width product's start: the constant's mantissa (PEAK: 1) times 2^32 per
-    // dimension (kWhole), or per dimension of the first group of four (where all
-    // of them overflow: the later groups multiply by 2^128, the last one by
-    // 2^32 for each dimension it has)
+    // width product's start: the constant's mantissa (PEAK: 1) times the power of
+    // two of width_start
     static constexpr bool kExp = P::is64 && KIND != GENZ_PEAK, kWhole = DMAX <= 24;
     double kexp, magic, w0;  // kexp: GAUSS, BIMODAL: -1/a^2
-    uint32_t last_hi;        // high word of the last group's factor
     // coefficients of exp_scaled, in scalar registers where those are free
     // (GAUSS): the compiler holds all in vector registers, and the d = 18
     // kernel (N = 100) spilled 28 instead of 24 (136 against 131 us)
@@ -235,7 +243,7 @@ struct EvalConsts {
     // exponent is not a number).
     __device__ __forceinline__ void leave_out_constant(int d)
     {
-        w0 = ldexp(1.0, kWhole ? 32 * d : 128);
+        w0 = ldexp(1.0, width_start(kWhole, d));
         magic = magic == magic ? 0x1.8p52 : magic;
     }
 
@@ -282,8 +290,7 @@ struct EvalConsts {
         }
         kexp = -c->kexp64;
         magic = c->magic;
-        w0 = ldexp(kExp ? c->mant : 1.0, kWhole ? 32 * d : 128);
-        last_hi = uint32_t(1023 + 32 * ((d - 1) % 4 + 1)) << 20;
+        w0 = ldexp(kExp ? c->mant : 1.0, width_start(kWhole, d));
         k2 = (P::is64 || KIND == GENZ_DISC) ? c->kexp2_64 : c->kexp2_64 * ds2;
         dscale = real(ds);
         const uint32_t N = uint32_t(c->n_bins);
@@ -360,11 +367,8 @@ struct EventEval {
         for (int g = 0; g < (DMAX + 3) / 4; ++g) {
             if (4 * g < d) {
                 const U4 k = philox4x32_10(elo, ehi, t, ctr3 + uint32_t(g), key0, key1);
-                if constexpr (P::is64 && !EvalConsts<P, KIND, DMAX>::kWhole) {
-                    // (its high word alone: one scalar select)
-                    constexpr uint32_t kFour = uint32_t(1023 + 128) << 20;
-                    if (g > 0) w *= real(__hiloint2double(int(EXACT || 4 * g + 4 <= d ? kFour : c.last_hi), 0));
-                }
+                if constexpr (P::is64 && !EvalConsts<P, KIND, DMAX>::kWhole)
+                    if (g > 1) w *= real(0x1p128);
                 // the group's four bins and table entries first, so that its
                 // LDS reads are in flight together before any is used
                 int bq[4];

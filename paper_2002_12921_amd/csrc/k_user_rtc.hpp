@@ -80,17 +80,16 @@ struct Event {
 #ifdef VEGAS_FP32
         float w = 1.0f;
 #else
-        // 2^32 per dimension, at once where that is in range
         double w = 1.0;
 #pragma unroll
-        for (int i = 0; i < (D <= 24 ? D : 4); ++i) w *= 0x1p32;
+        for (int i = 0; i < width_start(D <= 24, D); i += 32) w *= 0x1p32;
 #endif
         int ewl = 0;
 #pragma unroll
         for (int g = 0; g < (D + 3) / 4; ++g) {
             const U4 k = philox4x32_10(elo, ehi, t, ctr3 + uint32_t(g), key0, key1);
 #ifndef VEGAS_FP32
-            if (D > 24 && g > 0) w *= 4 * g + 4 <= D ? 0x1p128 : D % 4 == 1 ? 0x1p32 : D % 4 == 2 ? 0x1p64 : 0x1p96;
+            if (D > 24 && g > 1) w *= 0x1p128;
 #endif
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
