@@ -60,10 +60,10 @@ vegas_status check_params(int kind, int d, const double* q)
     return VEGAS_OK;
 }
 
-// LDS of the runtime-compiled event kernel: table, histogram replicas, wave partials.
-size_t user_lds(int prec, int d, int N, int rep, bool hist)
+// LDS of the event kernel's table and histogram replicas.
+size_t event_data(int prec, int kind, int d, int N, int rep, bool hist)
 {
-    return with_sums(lds_bytes(prec, USER, d, N, hist ? rep : 0));
+    return kind == USER ? lds_bytes(prec, USER, d, N, hist ? rep : 0) : sample_data(prec, kind, d, N, rep, hist);
 }
 
 // LDS per block of the event kernel with one histogram copy per bin (the
@@ -71,8 +71,7 @@ size_t user_lds(int prec, int d, int N, int rep, bool hist)
 // partials of the block reduction.  Exactly what the launch asks for.
 size_t event_lds_min(int prec, int kind, int d, int N)
 {
-    if (kind == USER) return user_lds(prec, d, N, 1, true);
-    return sample_lds(prec, kind, d, N, 1, true);
+    return with_sums(event_data(prec, kind, d, N, 1, true));
 }
 
 vegas_status check_desc(const vegas_desc* d)
@@ -186,9 +185,17 @@ int sample_blocks(const vegas_ctx* c, int64_t n)
     return nb;
 }
 
+// LDS of the event kernel, and threads of its block: with and without
+// histograms the same, for the same bits of S1 and S2.
 size_t event_lds(const vegas_ctx* c, int rep, bool hist)
 {
-    return c->kind == USER ? user_lds(c->prec, c->d, c->N, rep, hist) : sample_lds(c->prec, c->kind, c->d, c->N, rep, hist);
+    return with_sums(event_data(c->prec, c->kind, c->d, c->N, rep, hist));
+}
+
+int launch_threads(const vegas_ctx* c)
+{
+    const int rep = 1 << (c->hrep_user >= 0 ? c->hrep_user : c->hrep_log2);
+    return event_threads(event_data(c->prec, c->kind, c->d, c->N, rep, true), c->threads);
 }
 
 SampleArgs sample_args(const vegas_ctx* c, int64_t e0, int64_t n, bool no_hist)
@@ -243,15 +250,13 @@ MergeArgs merge_args(const vegas_ctx* c, int rows, int flags, double M)
 // The event kernel of a context: built-in, or the runtime-compiled one.
 hipError_t launch_event_kernel(const vegas_ctx* c, const SampleArgs& a, int blocks, hipStream_t s)
 {
-    if (c->kind != USER) return launch_sample(c->prec, c->kind, a, blocks, c->threads, s);
+    const int threads = launch_threads(c);
+    if (c->kind != USER) return launch_sample(c->prec, c->kind, a, blocks, threads, s);
     const bool hist = a.hist != 0;
     const double* params = c->P.params;
-    const size_t data = lds_bytes(c->prec, USER, c->d, c->N, hist ? 1 << a.hrep_log2 : 0);
-    SampleArgs b = a;
-    b.red_at = sums_at(data);
-    void* args[] = {&b, const_cast<double**>(&params)};
-    return hipModuleLaunchKernel(c->usample[hist ? 0 : 1], unsigned(blocks), 1, 1, unsigned(c->threads), 1, 1,
-                                 unsigned(with_sums(data)), s, args, nullptr);
+    void* args[] = {const_cast<SampleArgs*>(&a), const_cast<double**>(&params)};
+    return hipModuleLaunchKernel(c->usample[hist ? 0 : 1], unsigned(blocks), 1, 1, unsigned(threads), 1, 1,
+                                 unsigned(event_lds(c, 1 << a.hrep_log2, hist)), s, args, nullptr);
 }
 
 // Values a copy to the host may have for one block of a kernel to write them
@@ -446,8 +451,8 @@ vegas_status init_ctx(vegas_ctx** out, const vegas_desc* desc, const char* sourc
     for (int th : {1024, 512, 768, 256}) {
         if (source && th > kUserThreads) continue;
         for (int l2 = 4; l2 >= 0; --l2) {
-            const size_t lds = event_lds(c, 1 << l2, true);
-            if (lds > kLdsLimit) continue;
+            const size_t data = event_data(c->prec, c->kind, c->d, c->N, 1 << l2, true), lds = with_sums(data);
+            if (lds > kLdsLimit || event_threads(data, th) != th) continue;
             int bpc = 1;
             if (!source) {
                 bpc = sample_max_blocks_per_cu(c->prec, c->kind, c->d, c->N, th, 1 << l2);
@@ -590,7 +595,7 @@ vegas_status iterate_impl(vegas_ctx* c, int64_t n, uint32_t flags, double* dev_G
     const bool timed = c->timing && c->n_timed < kTimedCalls;
     if (timed) VEGAS_HIP(hipEventRecord(c->tev[3 * c->n_timed], s));
     if (dev_G)
-        VEGAS_HIP(launch_sample_grad(c->prec, a, c->P.adj_part, blocks, c->threads, s));
+        VEGAS_HIP(launch_sample_grad(c->prec, a, c->P.adj_part, blocks, launch_threads(c), s));
     else
         VEGAS_HIP(launch_event_kernel(c, a, blocks, s));
     if (timed) VEGAS_HIP(hipEventRecord(c->tev[3 * c->n_timed + 1], s));
@@ -1010,7 +1015,7 @@ vegas_status vegas_get_launch(const vegas_ctx* c, int32_t* auto_blocks, int32_t*
     if (!c) return fail(VEGAS_EINVAL, "ctx is NULL");
     if (auto_blocks) *auto_blocks = c->blocks_auto;
     if (blocks_per_cu) *blocks_per_cu = c->cu_count > 0 ? c->blocks_auto / c->cu_count : 0;
-    if (threads) *threads = c->threads;
+    if (threads) *threads = launch_threads(c);
     if (replicas) *replicas = 1 << (c->hrep_user >= 0 ? c->hrep_user : c->hrep_log2);
     return VEGAS_OK;
 }

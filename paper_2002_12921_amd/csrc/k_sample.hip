@@ -72,7 +72,7 @@ __global__ __attribute__((amdgpu_flat_work_group_size(1, MaxThreads<P, KIND, DMA
     const size_t hist_bytes = HM == kHistNone ? 0 : size_t(nh) * sizeof(double) << rl2;
     tab_t* tab = reinterpret_cast<tab_t*>(smem);
     double* hist = reinterpret_cast<double*>(smem + tab_bytes);
-    double* red = reinterpret_cast<double*>(smem + a.red_at);
+    double* red = reinterpret_cast<double*>(smem + tab_bytes + hist_bytes);
     const uint32_t ltab = lds_address(smem);
     static_assert(GL == 0 || EXACT, "sets of dimensions: kernels without guards only");
     const HistAdder<TabLog2<P, KIND>::value> hadd(ltab, ltab + uint32_t(tab_bytes), rl2);
@@ -131,7 +131,6 @@ __global__ __attribute__((amdgpu_flat_work_group_size(1, MaxThreads<P, KIND, DMA
 
     // block_sums synchronises, which also completes every histogram atomic
     const double v12[2] = {s1 - c1, s2 - c2};
-    if (a.red_at == 0) __syncthreads();  // every wave is done with the table
     const double S = block_sums(v12, red);
     if (threadIdx.x < 2) a.partials[size_t(blockIdx.x) * 2 + threadIdx.x] = S;
     // the block's histogram (replicas summed) goes into slot
@@ -552,16 +551,10 @@ hipError_t launch_sample_grad(int prec, const SampleArgs& a, double* gpart, int 
     return hipLaunchKernel(fn, dim3(blocks), dim3(threads), args, lds, s);
 }
 
-// LDS of the table and histogram.
-static size_t sample_data(int prec, int kind, int d, int N, int rep, bool hist)
+size_t sample_data(int prec, int kind, int d, int N, int rep, bool hist)
 {
     const int hm = hist_mode(prec, kind, d, N, rep, hist);
     return lds_bytes(prec, kind, d, N, hist ? rep : 0, hm > kHistSets1 ? hm - 1 : 0);
-}
-
-size_t sample_lds(int prec, int kind, int d, int N, int rep, bool hist)
-{
-    return with_sums(sample_data(prec, kind, d, N, rep, hist));
 }
 
 bool sample_in_sets(int prec, int kind, int d, int N, int rep)
@@ -574,11 +567,9 @@ hipError_t launch_sample(int prec, int kind, const SampleArgs& a, int blocks, in
     const bool hist = a.hist != 0;
     const int rep = 1 << a.hrep_log2;
     const void* fn = sample_kernel(prec, kind, a.d, hist_mode(prec, kind, a.d, a.N, rep, hist));
-    const size_t data = sample_data(prec, kind, a.d, a.N, rep, hist);
-    SampleArgs b = a;
-    b.red_at = sums_at(data);
-    void* args[] = {&b};
-    return hipLaunchKernel(fn, dim3(blocks), dim3(threads), args, with_sums(data), s);
+    void* args[] = {const_cast<SampleArgs*>(&a)};
+    const size_t lds = with_sums(sample_data(prec, kind, a.d, a.N, rep, hist));
+    return hipLaunchKernel(fn, dim3(blocks), dim3(threads), args, lds, s);
 }
 
 hipError_t launch_dump(int prec, int kind, const DumpArgs& a, hipStream_t s)
@@ -611,8 +602,8 @@ int sample_max_blocks_per_cu(int prec, int kind, int d, int N, int threads, int 
     const void* fn = sample_kernel(prec, kind, d, hist_mode(prec, kind, d, N, rep, true));
     hipFuncAttributes at;
     if (hipFuncGetAttributes(&at, fn) == hipSuccess && threads > at.maxThreadsPerBlock) return 0;  // not launchable
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, threads, sample_lds(prec, kind, d, N, rep, true)) != hipSuccess)
-        return 1;
+    const size_t lds = with_sums(sample_data(prec, kind, d, N, rep, true));
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, threads, lds) != hipSuccess) return 1;
     return n > 0 ? n : 1;
 }
 

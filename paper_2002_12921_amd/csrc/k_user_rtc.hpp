@@ -144,7 +144,7 @@ struct Event {
 __device__ __forceinline__ float map_scale(const DevConst* c) { return ldexpf(c->dscale32, -32); }
 
 // LDS: table [d][N] (128-byte aligned), histogram [d][N][rep] (HIST only),
-// and the block reduction's wave partials (SampleArgs::red_at).
+// then the block reduction's wave partials.
 template <bool HIST>
 __device__ __forceinline__ void sample(const SampleArgs& a, const double* __restrict__ params)
 {
@@ -153,9 +153,10 @@ __device__ __forceinline__ void sample(const SampleArgs& a, const double* __rest
     const int dN = D * N;
     const size_t tab_bytes = (size_t(dN) * sizeof(tab_t) + 127) & ~size_t(127);
     const int rl2 = a.hrep_log2, rep = 1 << rl2;
+    const size_t hist_bytes = HIST ? size_t(dN) * rep * sizeof(double) : 0;
     tab_t* tab = reinterpret_cast<tab_t*>(smem);
     double* hist = reinterpret_cast<double*>(smem + tab_bytes);
-    double* red = reinterpret_cast<double*>(smem + a.red_at);
+    double* red = reinterpret_cast<double*>(smem + tab_bytes + hist_bytes);
     const uint32_t ltab = lds_address(smem);
     const HistAdder<kEntryLog2> hadd(ltab, ltab + uint32_t(tab_bytes), rl2);
     const MapConsts mc(N, ltab, kEntryLog2);
@@ -198,7 +199,6 @@ __device__ __forceinline__ void sample(const SampleArgs& a, const double* __rest
 
     // block_sums synchronises, which also completes every histogram atomic
     const double v12[2] = {s1 - c1, s2 - c2};
-    if (a.red_at == 0) __syncthreads();  // every wave is done with the table
     const double S = block_sums(v12, red);
     if (threadIdx.x < 2) a.partials[size_t(blockIdx.x) * 2 + threadIdx.x] = S;
     if constexpr (HIST) {

@@ -137,13 +137,17 @@ inline size_t lds_bytes(int prec, int kind, int d, int N, int rep = 1, int gl = 
 // LDS of a block's sums of n values per thread: a partial per wave and value.
 inline size_t red_bytes(int n) { return sizeof(double) * size_t(n) * (kBlock / 64); }
 
-// LDS of the event kernel with `data` bytes of table and histogram, and where in
-// it the block's sums of S1 and S2 go: behind the data, or where that exceeds the
-// LDS, over the table (offset 0, with a barrier after the last event). One
-// partial per wave has to fit in any case: a launch (d N = 2046 with 8 replicas,
-// 4089 with 4) is not refused for the second.
+// LDS of an event kernel with `data` bytes of table and histogram, and threads of
+// its block: where the partials of S1 and S2 of 16 waves (256 bytes) do not fit,
+// those of 8 may, and a launch that leaves 128 bytes (d N = 2046 with 8 replicas,
+// 4089 with 4) is not refused. (Sums over the table after one more barrier would
+// keep 1024 threads there, but their offset, formed after the loop, cost the
+// d = 16 discontinuous FP64 kernel 2-3 %, and as an argument 14 % at d = 22.)
 inline size_t with_sums(size_t data) { return data + red_bytes(data + red_bytes(2) <= kLdsLimit ? 2 : 1); }
-inline uint32_t sums_at(size_t data) { return data + red_bytes(2) <= kLdsLimit ? uint32_t(data) : 0u; }
+inline int event_threads(size_t data, int threads)
+{
+    return threads > 512 && data + red_bytes(2) > kLdsLimit ? 512 : threads;
+}
 
 // Device pointers of one problem's state.
 struct ProblemPtrs {
@@ -201,7 +205,6 @@ struct SampleArgs {
     int d, N;
     int hrep_log2;       // log2 of the histogram replicas per bin
     int hist;            // 0: no histograms this launch (only S1, S2 are written)
-    uint32_t red_at;     // LDS offset of the block sums' partials (0: over the table)
 };
 
 // Where a kernel writes results for the host (pinned memory), and the mark it
@@ -327,7 +330,8 @@ struct BatchArgs {
 // Launch wrappers (defined in the .hip files).
 
 hipError_t launch_sample(int prec, int kind, const SampleArgs& a, int blocks, int threads, hipStream_t s);
-size_t sample_lds(int prec, int kind, int d, int N, int rep, bool hist = true);
+// LDS of the table and histogram
+size_t sample_data(int prec, int kind, int d, int N, int rep, bool hist = true);
 // whether the event kernel with this many replicas takes the dimensions in sets
 bool sample_in_sets(int prec, int kind, int d, int N, int rep);
 hipError_t launch_dump(int prec, int kind, const DumpArgs& a, hipStream_t s);

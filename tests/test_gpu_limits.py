@@ -139,7 +139,7 @@ def _largest(prec, kind):
 @pytest.mark.parametrize("prec,kind", [("fp64", "gauss"), ("fp32_mixed", "gauss"), ("fp32_mixed", "bimodal"), ("fp64", "genz_disc")])
 def test_replicas_that_just_fit(prec, kind):
     """Replica counts whose LDS fits by less than 128 bytes are accepted, and the
-    launch, whose sums then lie over the table, gives the oracle's sums and bins."""
+    launch gives the oracle's sums and bins, and without histograms the same bits."""
     sizes = _largest(prec, kind)
     assert len(sizes) >= 2
     tol = 1e-12 if prec == "fp64" else 1e-6
@@ -158,7 +158,10 @@ def test_replicas_that_just_fit(prec, kind):
         t = tol * max(1.0, d / 8) if prec != "fp64" else tol
         assert abs(S1 - o1) <= t * o1 and abs(S2 - o2) <= t * o2, (d, N, rep)
         assert np.all(np.abs(H - Ho) <= t * Ho.sum(axis=1, keepdims=True)), (d, N, rep)
-        v.iterate(9001, hist=False)
+        w = Vegas(d, N, kind, params, prec, seed=11)
+        w.set_hist_replicas(rep)
+        w.iterate(9001, hist=False)
+        assert w.last_iteration()[:2] == (S1, S2), (d, N, rep)
 
 
 @pytest.mark.parametrize("d,N,prec,rep", [(11, 186, "fp64", 8), (62, 33, "fp64", 8), (22, 186, "fp32_mixed", 4)])
