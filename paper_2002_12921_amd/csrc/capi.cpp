@@ -417,15 +417,10 @@ vegas_status init_ctx(vegas_ctx** out, const vegas_desc* desc, const char* sourc
             return bail(fail(VEGAS_EHIP, "hipModuleGetFunction: %s", hipGetErrorString(he)));
     }
     // Launch shape of the event kernel: block size and histogram replicas.
-    // Score = resident waves per CU x a replica factor x a block-size factor.
-    // Fewer replicas leave more LDS bank conflicts in the histogram's atomics, and
-    // those share the LDS with the table reads. Up to d = 8 (only runtime-compiled
-    // integrands get here with 8 or 4 replicas), per 1e7 events of a d = 8
-    // Gaussian written as source, FP64, by blocks of 512 threads: N = 50, two with
-    // 16 replicas 70.8 us, three with 8 74.9, three with 4 81.6; N = 100, one with
-    // 16 72.1, two with 8 70.8, three with 4 77.7; N = 200, one with 8 79.9, two
-    // with 4 80.6; d = 6, N = 255, one with 8 72.1 and 51.1 without histograms (which
-    // run in the same blocks), two with 4 70.0 and 50.0. Ties keep the larger block and the more replicas.
+    // Score = resident waves per CU x a replica factor x a block-size factor; ties
+    // keep the larger block and the more replicas. Fewer replicas leave more LDS
+    // bank conflicts in the histogram's atomics, and those share the LDS with the
+    // table reads.
     // Beyond d = 8 each event makes more histogram atomics per instruction and
     // the replicas weigh more: per 1e7 events, the FP32-mixed Gaussian took 88 us
     // with one block of 16 and 114 us with two of 8 (d = 16, N = 50), 110 us with
@@ -439,6 +434,22 @@ vegas_status init_ctx(vegas_ctx** out, const vegas_desc* desc, const char* sourc
     static const double kRepFactorLow[5] = {0.05, 0.2, 0.33, 0.6, 1.0};   // 1, 2, 4, 8, 16 replicas
     static const double kRepFactorSets[5] = {0.05, 0.12, 0.95, 0.98, 1.0};
     static const double kRepFactorHigh[5] = {0.05, 0.1, 0.2, 0.45, 1.0};
+    // Runtime-compiled integrands may cost anything an event, and the more they
+    // do, the more the waves weigh: one of sines and an exponential took, per 1e7
+    // events, 499 us in one block of 512 threads with 16 replicas and 391 in two
+    // with 8 (d = 16, N = 50, FP32-mixed). So waves count nearly in full up to 16
+    // and little beyond: two blocks of 16 replicas before three of 8 (the d = 8
+    // Gaussian, N = 50, FP64, 64.2 and 67.7 us, without histograms, in the same
+    // blocks, 57.7 and 56.0), but two or three of 4 before one of 16 (N = 128: the
+    // Gaussian 78.3 and 72.9 us, without 56.4 and 64.1, an oscillatory one 80.4
+    // and 75.2, without 61.6 and 68.6). Fitted to the launches of these three in
+    // every shape, d = 2 to 20, N = 13 to 255, both precisions, 1e6 to 2e7 events;
+    // against the factors above, three launches with histograms and two without
+    // took 1 % less in the mean (the Gaussian, the oscillatory one; at most 8 %
+    // more) and 3 % less (the dear one; at most 25 % less, 4 % more).
+    static const double kUserWaves[9] = {0.0, 4.5, 6.7, 12.7, 18.0, 20.0, 21.0, 21.2, 21.4};  // 0, 4 ... 32 waves
+    static const double kUserRepLow[5] = {0.25, 0.38, 0.6, 0.84, 1.0};
+    static const double kUserRepHigh[5] = {0.1, 0.18, 0.33, 0.55, 1.0};
     double best = -1.0;
     int per_cu = 1;
     // Blocks of 256 threads count 0.85: at equal waves they leave four histograms
@@ -461,10 +472,16 @@ vegas_status init_ctx(vegas_ctx** out, const vegas_desc* desc, const char* sourc
                        bpc < 1) {
                 bpc = 1;
             }
-            const double* kRepFactor = c->d > 8                                                       ? kRepFactorHigh
-                                       : !source && sample_in_sets(c->prec, c->kind, c->d, c->N, 1 << l2) ? kRepFactorSets
-                                                                                                      : kRepFactorLow;
-            const double score = double(bpc * th / 64) * kRepFactor[l2] * (th == 256 ? 0.85 : 1.0);
+            double score;
+            if (source) {
+                score = kUserWaves[std::min(bpc * th / 256, 8)] * (c->d > 8 ? kUserRepHigh : kUserRepLow)[l2] *
+                        (th == 256 ? 0.93 : 1.0);
+            } else {
+                const double* rep = c->d > 8                                                    ? kRepFactorHigh
+                                    : sample_in_sets(c->prec, c->kind, c->d, c->N, 1 << l2) ? kRepFactorSets
+                                                                                            : kRepFactorLow;
+                score = double(bpc * th / 64) * rep[l2] * (th == 256 ? 0.85 : 1.0);
+            }
             if (score > best + 1e-9) {
                 best = score;
                 per_cu = bpc;

@@ -316,3 +316,18 @@ def test_device_buffers_are_final_after_a_read():
             assert r["last_integral"] == got[0], k
         other.synchronize()
         v.stream = s
+
+
+def test_dear_user_integrands_keep_their_waves():
+    """A runtime-compiled integrand is not held to one block of 512 threads a compute
+    unit for the sake of histogram replicas where its registers admit two."""
+    dear = """__device__ vegas_real vegas_integrand(const vegas_real* x, int dim, const double* p)
+{ vegas_real s = 0, q = 1;
+  for (int i = 0; i < VEGAS_DIM; ++i) { s += sin(x[i] * vegas_real(3)); q *= vegas_real(1) + x[i] * x[i]; }
+  return exp(-s * s) / q; }"""
+    for d, N in ((16, 50), (20, 100), (10, 200)):
+        v = Vegas(d, N, source=dear, precision="fp32_mixed")
+        info = v.launch_info()
+        assert info["blocks_per_cu"] * info["threads"] >= 1024, info
+        v.iterate(3000)
+        assert np.isfinite(v.last_iteration()[0])
