@@ -458,7 +458,10 @@ vegas_status init_ctx(vegas_ctx** out, const vegas_desc* desc, const char* sourc
     // threads 31.2 and 3.8).
     // 768 comes after 512, so it is taken only where it holds strictly more
     // waves (two blocks per CU where the LDS admits two and the registers
-    // allow 6 or 7 waves per SIMD: the FP64 kernels up to d = 8)
+    // allow 6 or 7 waves per SIMD: the FP64 kernels up to d = 8). Beyond d = 8 two
+    // blocks of 768 are no gain over one of 1024, for which those kernels are
+    // compiled: product peak d = 16, N = 37, FP32-mixed, per 8e6 events 80.1 and
+    // 71.5 us, without histograms 58.5 and 58.8 (per 1e6 19.4, 15.7, 13.4, 12.5).
     for (int th : {1024, 512, 768, 256}) {
         if (source && th > kUserThreads) continue;
         for (int l2 = 4; l2 >= 0; --l2) {
@@ -468,6 +471,7 @@ vegas_status init_ctx(vegas_ctx** out, const vegas_desc* desc, const char* sourc
             if (!source) {
                 bpc = sample_max_blocks_per_cu(c->prec, c->kind, c->d, c->N, th, 1 << l2);
                 if (bpc < 1) continue;  // beyond the kernel's largest block
+                if (th == 768 && c->d > 8) bpc = 1;
             } else if (hipModuleOccupancyMaxActiveBlocksPerMultiprocessor(&bpc, c->usample[0], th, lds) != hipSuccess ||
                        bpc < 1) {
                 bpc = 1;

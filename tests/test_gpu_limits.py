@@ -331,3 +331,13 @@ def test_dear_user_integrands_keep_their_waves():
         assert info["blocks_per_cu"] * info["threads"] >= 1024, info
         v.iterate(3000)
         assert np.isfinite(v.last_iteration()[0])
+
+
+@pytest.mark.parametrize("kind,d,N,prec", [("genz_peak", 16, 37, "fp32_mixed"), ("genz_peak", 9, 50, "fp64"), ("gauss", 12, 37, "fp64"),
+                                           ("bimodal", 9, 50, "fp32_mixed")])
+def test_one_large_block_beyond_eight_dimensions(kind, d, N, prec):
+    """The histogram kernels beyond d = 8 are compiled for one block of 1024 threads
+    a compute unit and are not launched as two of 768."""
+    q = {"gauss": [0.2] + [0.5] * d, "bimodal": [0.2] + [0.4] * d + [0.6] * d, "genz_peak": [1.0] * d + [0.1] * d}[kind]
+    info = Vegas(d, N, kind, q, prec).launch_info()
+    assert info["threads"] != 768, info
