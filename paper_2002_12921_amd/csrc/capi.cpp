@@ -259,8 +259,9 @@ hipError_t launch_event_kernel(const vegas_ctx* c, const SampleArgs& a, int bloc
                                  unsigned(event_lds(c, 1 << a.hrep_log2, hist)), s, args, nullptr);
 }
 
-// Values a copy to the host may have for one block of a kernel to write them
-// (32 KiB, about 3 us over the host link).
+// Values a copy to the host may have for one block of a kernel to write them:
+// 4096 from an idle context take 13.6 us (a copy call 11.2), behind an iteration
+// 20.9 (31.6).
 constexpr size_t kPostValues = 4096;
 
 // A kernel that writes to the staging buffer posts the next mark behind it.
