@@ -1,7 +1,7 @@
 // Batch entry points: many independent Vegas integrations run together (see
 // include/vegas.h).  All iterations of all problems are recorded once as a
-// HIP graph and replayed with one graph launch.  The tile size (events per
-// work item, which also fixes events per thread) is chosen at plan time by
+// HIP graph and replayed with one graph launch.  The tile (the most events of a
+// work item; items shrink towards a bucket's end) is chosen at plan time by
 // timing candidate schedules on the batch itself.
 #include <algorithm>
 #include <cmath>
@@ -25,7 +25,9 @@ constexpr int kBatchMaxIter = 1024;
 constexpr int kMaxProblems = 65535;
 const uint64_t kTileCandidates[] = {1u << 13, 1u << 14, 1u << 15, 1u << 16, 1u << 17};
 constexpr uint64_t kTileMin = 1u << 13;
-constexpr uint64_t kTileStep = 1u << 12;  // items are whole groups of kGroup events per thread, at any block size
+// shrinking items are multiples of this: whole groups of kGroup events per thread
+// in blocks of 256 and 512 threads, four events per thread in those of 1024
+constexpr uint64_t kTileStep = 1u << 12;
 constexpr int kTuneWarmRuns = 3;  // untimed schedule timings before the tuning's own
 
 size_t a256(size_t x) { return (x + 255) & ~size_t(255); }
@@ -564,7 +566,7 @@ vegas_status vegas_batch_plan(vegas_batch** out, const vegas_desc* descs, const 
             return bail(fail(VEGAS_EHIP, "batch prepare: %s", hipGetErrorString(he)));
     }
 
-    // the schedule: tile size (events per work item), then each bucket's
+    // the schedule: tile (most events of a work item), then each bucket's
     // launch shape, timed on this batch (or read from the tuning cache)
     const char* forced = std::getenv("VEGAS_BATCH_TILE");
     uint64_t tile = forced ? uint64_t(std::strtoull(forced, nullptr, 10)) : 0;

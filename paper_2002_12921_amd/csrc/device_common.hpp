@@ -545,17 +545,6 @@ __device__ __forceinline__ void twosum_add(double& s, double& c, double v)
     s = t;
 }
 
-// Neumaier step: the sum is s + c.
-__device__ __forceinline__ void neumaier_add(double& s, double& c, double v)
-{
-    const double t = s + v;
-    if (fabs(s) >= fabs(v))
-        c += (s - t) + v;
-    else
-        c += (v - t) + s;
-    s = t;
-}
-
 // The value a DPP control takes from another lane (0 where it takes none).
 template <int CTRL, int ROW_MASK>
 __device__ __forceinline__ double dpp_move(double v)

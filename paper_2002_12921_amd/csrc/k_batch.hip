@@ -1,8 +1,8 @@
 // Batched Vegas iterations: many independent problems (own dimension, grid,
 // event count and integrand parameters) in one persistent launch.
 //
-// The event kernel's blocks take work items -- a tile of events of one
-// problem -- from an atomic counter until none is left.  Items are ordered by
+// The event kernel's blocks take work items -- a range of one problem's
+// events -- from an atomic counter until none is left.  Items are ordered by
 // cost (larger dimension first), so the tail of the launch is made of cheap
 // items.  When a block moves to another problem it reloads that problem's
 // grid table into LDS; each item leaves one partial row (S1, S2, H[d][N]).

@@ -228,7 +228,7 @@ __device__ static void prepare_consts(int prec, int kind, int d, int N, const do
     const int shift = prec == FP64 ? 0 : -ws * d;
     const double Cw = ldexp(nd, shift), Cw_lo = ldexp(nd_lo, shift);
     double kexp64 = 0.0, kexp2_64 = 0.0, inv_a = 0.0;
-    float kexp32 = 0.0f, ka32 = 0.0f;
+    float ka32 = 0.0f;
     if (kind == GAUSS || kind == BIMODAL) {
         const double a = q[0], sqrt_pi = 0x1.c5bf891b4ef6bp+0, sqrt_pi_lo = -0x1.618f13eb7ca89p-54;
         const double x = a * sqrt_pi, r = fma(a, sqrt_pi, -x) + a * sqrt_pi_lo;
@@ -238,7 +238,6 @@ __device__ static void prepare_consts(int prec, int kind, int d, int N, const do
         kexp64 = 1.0 / (a * a);
         kexp2_64 = log2e / (a * a);
         inv_a = 1.0 / a;
-        kexp32 = float(log2e / (a * a));
         ka32 = float(1.0 / (a * a));
     } else {
         if (kind == GENZ_DISC) kexp2_64 = log2e;
@@ -254,7 +253,7 @@ __device__ static void prepare_consts(int prec, int kind, int d, int N, const do
     c->kexp64 = kexp64;
     c->kexp2_64 = kexp2_64;
     c->inv_a = inv_a;
-    c->kexp32 = kexp32;
+    c->pad2 = 0.0f;
     c->ka32 = ka32;
     c->pad0 = 0.0f;
     c->Cf = Cf;

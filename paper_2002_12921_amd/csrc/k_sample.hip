@@ -34,11 +34,14 @@ constexpr int kHistNone = 0, kHistSets1 = 1, kHistSets2 = 2, kHistSets4 = 3;
 //     123.4-123.6 us per 1e7 events; d = 20 with N = 100: 232 against 172 us.
 //     FP32-mixed likewise at d = 17 to 19 (FP64 c_i beside 20 bins; N = 100, d =
 //     19: 211 against 134 us).
-//   Beyond d = 8 with histograms: at most 4.  They run one 1024-thread block per
-//     CU (their LDS holds one block's table and replicated histogram), which the
+//   Beyond d = 8 with histograms: at most 4.  From d N of about 600 on the LDS
+//     holds one 1024-thread block's table and replicated histogram, which the
 //     compiler cannot know from the dynamic LDS size: told so, it may use up to
 //     128 registers and keep an event's table reads in flight together instead
-//     of waiting on each (the d = 20 bimodal kernel waited on every one).
+//     of waiting on each (the d = 20 bimodal kernel waited on every one).  Below,
+//     smaller blocks share a CU, or two of 1024 where 64 registers do (the
+//     FP32-mixed Gaussian at d = 12 and 16); a variant compiled for more waves
+//     has not been measured there.
 //   4 to 8 elsewhere.
 template <class P, int KIND, int DMAX, bool EXACT, int HM>
 struct Waves {
@@ -263,9 +266,9 @@ __global__ __launch_bounds__(64) void k_adjoint_merge(AdjointArgs a, int rows)
 // also sums each event's v d ln f / d theta_j, as k_adjoint does, into
 // per-block rows gpart[block][d + 1] (merged by k_merge's gradient block).
 // It launches like the event kernel (two 1024-thread blocks per CU, 8 waves
-// per SIMD), so FP32 with d = 4 or 8 is compiled for 8 waves: at its natural
+// per SIMD), so FP32 up to d = 8 is compiled for 8 waves: at its natural
 // 70 registers (d = 8) only one block fitted per CU and the grid ran in two
-// rounds of 4 waves per SIMD.
+// rounds of 4 waves per SIMD (at 64, d = 8 spills 28 bytes a lane).
 template <class P, int DMAX, bool EXACT>
 struct GradMinWaves {
     static constexpr int value = (!P::is64 && DMAX <= 8 && EXACT) ? 8 : 1;

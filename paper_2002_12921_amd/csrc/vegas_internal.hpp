@@ -53,7 +53,7 @@ struct DevConst {
     double inv_a;    // GAUSS, BIMODAL: 1/a (adjoint)
     int32_t n_bins;  // N (binning)
     int32_t pad1;
-    float kexp32;    // (unused by the kernels; kept for the layout)
+    float pad2;
     float dscale32;  // 2^-ws
     float ka32;      // GAUSS: RN32(1/a^2) (adjoint)
     float pad0;
