@@ -77,9 +77,9 @@ __device__ __forceinline__ U4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c
 //   convert and one fma (x itself is not formed; the centre is 0 for user
 //   integrands).  The width product takes the factors 2^-32 back ahead of them: it
 //   starts at 2^(32 d), or beyond d = 24, where that overflows, at 2^32 for each
-//   dimension of the last group of four and of one group before, and each group
-//   from the third on multiplies by 2^128; so it never falls below the product of
-//   the widths and ends as that.  (Forming delta took an fma per dimension and,
+//   dimension of the first groups of four and of a last, partial one, and each other
+//   group multiplies by 2^128; so it never falls below the product of the widths
+//   and ends as that.  (Forming delta took an fma per dimension and,
 //   where 2^-32 and h sat in scalar registers, a copy of h.)
 // FP32: the map works on u' = (x - c) S with S = 2^(ws + 32).  With
 //   delta = (lo + h)/2^32 (see bin_words) and W = RN32(width), the table entry is
@@ -194,13 +194,15 @@ __device__ __forceinline__ void bin_words(uint32_t k, const BinConsts& bc, int& 
 }
 
 // Binary exponent the FP64 width product starts at: all 2^32 of it (whole), or
-// those of the last group of four and of one more group (d > 4; the groups from
-// the third on multiply by 2^128. Choosing the last group's factor in the loop
-// instead made the d = 40 discontinuous kernel without histograms 157 -> 190 us
-// per 4e6 events: a scalar register more, of which it spills hundreds).
+// those of the first kWidthGroups groups of four (d >= 17 there) and of a partial
+// one. (Choosing the last group's factor in the loop instead made the d = 40
+// discontinuous kernel without histograms 157 -> 190 us per 4e6 events: a scalar
+// register more, of which it spills hundreds; a factor at the end the bimodal one
+// with histograms 228 -> 240.)
+constexpr int kWidthGroups = 2;
 __device__ __forceinline__ constexpr int width_start(bool whole, int d)
 {
-    return whole ? 32 * d : 256 - 32 * ((4 - d % 4) % 4);
+    return whole ? 32 * d : 128 * kWidthGroups + 32 * (d % 4);
 }
 
 // Integrand constants of one problem, read once per thread into registers
@@ -367,8 +369,6 @@ struct EventEval {
         for (int g = 0; g < (DMAX + 3) / 4; ++g) {
             if (4 * g < d) {
                 const U4 k = philox4x32_10(elo, ehi, t, ctr3 + uint32_t(g), key0, key1);
-                if constexpr (P::is64 && !EvalConsts<P, KIND, DMAX>::kWhole)
-                    if (g > 1) w *= real(0x1p128);
                 // the group's four bins and table entries first, so that its
                 // LDS reads are in flight together before any is used
                 int bq[4];
@@ -378,6 +378,8 @@ struct EventEval {
                 for (int q = 0; q < 4; ++q) {
                     const int i = 4 * g + q;
                     if (i < d) {
+                        if constexpr (P::is64 && !EvalConsts<P, KIND, DMAX>::kWhole)
+                            if (g >= kWidthGroups && q == 3) w *= real(0x1p128);
                         bin_words(k.w[q], c.bc, bq[q], loq[q]);
                         constexpr int L = TabLog2<P, KIND>::value;
                         lds_ptr<const tab_t> pq;

@@ -89,7 +89,7 @@ struct Event {
         for (int g = 0; g < (D + 3) / 4; ++g) {
             const U4 k = philox4x32_10(elo, ehi, t, ctr3 + uint32_t(g), key0, key1);
 #ifndef VEGAS_FP32
-            if (D > 24 && g > 1) w *= 0x1p128;
+            if (D > 24 && g >= kWidthGroups && 4 * g + 4 <= D) w *= 0x1p128;
 #endif
 #pragma unroll
             for (int q = 0; q < 4; ++q) {

@@ -42,6 +42,33 @@ def test_values_near_the_smallest_double(kind, d, a, x):
     assert abs(S1 - o1) <= 4e-12 * o1, (S1, o1)
 
 
+@pytest.mark.parametrize("d", [24, 25, 26, 27, 28, 33])
+def test_narrow_bins_in_all_dimensions(d):
+    """Widths whose product is near 2^-1020: an event's weight keeps its digits,
+    also while the product is formed. Gaussian against the oracle (about 100
+    roundings of each value: 1e-13), and a constant as source on the same bins."""
+    N, M = 10, 60007
+    a, E = 2.0 ** (-930.0 / d), np.tile(np.append(np.arange(N) * 2.0 ** (-1020.0 / d), 1.0), (d, 1))
+    pr = oracle.Problem(d, N, oracle.GAUSS, [a] + [0.0] * d, seed=11)
+    o1, o2, _ = oracle.accumulate(pr, E, 0, M)
+    v = Vegas(d, N, "gauss", [a] + [0.0] * d, "fp64", seed=11)
+    v.set_edges(E)
+    v.iterate(M, hist=False)
+    S1, S2, _ = v.last_iteration()
+    assert o1 > 0 and abs(S1 - o1) <= 1e-13 * o1 and abs(S2 - o2) <= 2e-13 * o2
+    # every event inside counts 2^930 (N 2^(-1020/d))^d: S1^2 / S2 of them
+    u = Vegas(d, N, source="__device__ vegas_real vegas_integrand(const vegas_real* x, int dim, const double* p)\n"
+                           "{ for (int i = 0; i < dim; ++i) if (x[i] >= %s) return 0; return 0x1p930; }" % E[0, N - 1].hex(),
+              precision="fp64", seed=11)
+    u.set_edges(E)
+    u.iterate(M, hist=False)
+    S1, S2, _ = u.last_iteration()
+    b = v.dump_events(0, M, iteration=0)[:, :d].cpu().numpy()
+    inside = int((b < N - 1).all(axis=1).sum())
+    value = 2.0 ** 930 * np.prod(N * (E[:, 1] - E[:, 0]))
+    assert inside > 100 and abs(S1 - inside * value) <= 1e-13 * S1 and abs(S2 - inside * value * value) <= 2e-13 * S2
+
+
 def test_constant_near_the_largest_double():
     """The bimodal integrand's normalisation times N^d between 2^1023 and 2^1024,
     both peaks in one place: f w is of order one and so are the sums."""
